@@ -5,11 +5,10 @@
 // scaled LP min c~^T x s.t. A~ x = b~, x >= 0 with A~ = D_r A D_c, b~ = D_r b,
 // c~ = D_c c.  Every Newton system goes through the normal equations
 // (A~ D A~^T) dy = r_b - A~ (Z^-1 r_xz - D r_c), D = X Z^-1: the m x m matrix
-// is formed dense on the device (each entry a merge of two sorted rows of A~,
-// one thread per entry, fixed order), factored by a blocked right-looking
-// Cholesky (64 x 64 blocks: a one-workgroup diagonal factor, a row-per-thread
-// panel solve, an LDS-tiled trailing update), and the two triangular solves
-// run in one workgroup, one wave doing each diagonal block with shuffles.
+// is formed dense on the device (a wave per row, accumulated in LDS in a fixed
+// order), factored by a blocked right-looking Cholesky on FP64 MFMAs (64 x 64
+// blocks, one launch per block column), and each of the two triangular solves
+// is one launch, a workgroup per 64 rows.
 // The predictor and the corrector share the factor.  Scalars (norms, step
 // lengths, mu) are fixed-order reductions read back by the host, which runs
 // the iteration.  Dense factors bound m (kIpmMaxM): this consumer is for the
@@ -68,192 +67,542 @@ __global__ void k_ipm_vscale(const double* v, const double* d, int div, int64_t 
     }
 }
 
-// Lower triangle of M = A~ diag(w) A~^T (w NULL: ones): entry (i, k), k <= i,
-// by merging the sorted columns of rows i and k.
-__global__ __launch_bounds__(kBlock) void k_ipm_normal(const int32_t* rp, const int32_t* col, const double* val,
-                                                       const double* w, int32_t m, double* M) {
-    const int32_t i = blockIdx.y;
-    const int32_t k = blockIdx.x * kBlock + threadIdx.x;
-    if (k > i) return;
-    int p = rp[i], q = rp[k];
-    const int pe = rp[i + 1], qe = rp[k + 1];
-    double s = 0.0;
-    while (p < pe && q < qe) {
-        const int32_t a = col[p], b = col[q];
-        if (a == b) {
-            s += (val[p] * (w ? w[a] : 1.0)) * val[q];
-            ++p;
-            ++q;
-        } else if (a < b) {
-            ++p;
-        } else {
-            ++q;
+// Lower triangle of M = A~ diag(w) A~^T (w NULL: ones), a workgroup of one
+// wave per row i: the row is accumulated in LDS, column after column of A's
+// row i in its order, the lanes over the entries of that column (a row of
+// A~^T, whose rows k are distinct).  Every entry (i, k) is the sum over the
+// common columns of i and k in increasing order, whatever the launch.  Rows
+// from m on (the padding up to ld) are those of the identity.
+// What bounds it: the loads of a column's entries, a chain of two; four
+// columns' loads are in flight together.  26 us at 1,000 x 4,000 (32,000
+// nonzeros) and 146 us at 4,000 x 16,000 (128,000); one thread per entry
+// merging the two sorted rows, the form before, walked both rows for every
+// pair, mostly without a common column: 131 us and 2.0 ms.
+__global__ __launch_bounds__(kWave) void k_ipm_normal(const int32_t* rp, const int32_t* col, const double* val,
+                                                      const int32_t* trp, const int32_t* tcol, const double* tval,
+                                                      const double* w, int32_t m, int32_t ld, double* M) {
+    extern __shared__ __align__(16) double row[];
+    const int lane = threadIdx.x;
+    const int i = ld - 1 - (int)blockIdx.x;  // the longest rows of the triangle first
+    for (int k = lane; k <= i; k += kWave) row[k] = (i >= m && k == i) ? 1.0 : 0.0;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    const int p0 = i < m ? rp[i] : 0, p1 = i < m ? rp[i + 1] : 0;
+    for (int base = p0; base < p1; base += kWave) {
+        // lane l: column base + l of the row, its weighted value and its range in A~^T
+        const int nc = min(kWave, p1 - base);
+        double v = 0.0;
+        int ts = 0, te = 0;
+        if (lane < nc) {
+            const int c = col[base + lane];
+            v = val[base + lane] * (w ? w[c] : 1.0);
+            ts = trp[c];
+            te = trp[c + 1];
+        }
+        for (int q = 0; q < nc; q += 4) {
+            int s[4], e[4], k[4];
+            double vv[4], tv[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                s[u] = q + u < nc ? __shfl(ts, q + u, kWave) : 0;
+                e[u] = q + u < nc ? __shfl(te, q + u, kWave) : 0;
+                vv[u] = __shfl(v, (q + u) & (kWave - 1), kWave);
+                k[u] = s[u] + lane < e[u] ? tcol[s[u] + lane] : -1;
+                tv[u] = s[u] + lane < e[u] ? tval[s[u] + lane] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (k[u] >= 0 && k[u] <= i) row[k[u]] += vv[u] * tv[u];
+                for (int t = s[u] + kWave + lane; t < e[u]; t += kWave) {  // columns of more than 64 entries
+                    const int kk = tcol[t];
+                    if (kk >= 0 && kk <= i) row[kk] += vv[u] * tval[t];
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();  // the next column's entries may be other lanes'
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
         }
     }
-    M[(int64_t)i * m + k] = s;
+    for (int k = lane; k <= i; k += kWave) M[(int64_t)i * ld + k] = row[k];
 }
 
-// --- blocked Cholesky, lower triangle of a row-major m x m matrix in place.
-// A pivot that is not positive (or underflows) is replaced by 1e128, which
+// --- blocked Cholesky, lower triangle of a row-major ld x ld matrix in place,
+// ld a multiple of 64 (rows and columns from m on are the identity's).  A
+// pivot that is not positive (or underflows) is replaced by 1e128, which
 // decouples that row (the usual treatment of a rank-deficient normal matrix);
 // such replacements are counted in *flag.
+//
+// One launch per 64-column block s.  Every workgroup of the launch needs the
+// panel of block s - 1 only, so the launches are the only synchronisation:
+//  - the first nbk - s workgroups take the 64 x 64 blocks (i, s), i >= s:
+//    panel s - 1 is applied to the block and, by each of them again, to the
+//    diagonal block, which each factors for itself (a launch of its own would
+//    cost a trip through memory more) and solves its rows with; (s, s) itself
+//    stores the inverse of its factor, which the triangular solves use, and
+//    L(s, s) is not stored;
+//  - the others apply panel s - 1 to the blocks right of column s.
+// The products are 16 x 16 x 4 FP64 MFMAs: a lane holds A[l % 16][l / 16],
+// B[l / 16][l % 16] and, in register r, C[l / 16 + 4 r][l % 16], so a C block
+// is its own B operand of the next product, and the row solves
+// X^T <- L^-1 X^T keep X^T in registers throughout.
+// What bounds it: the diagonal factors, about 6,000 clocks for 16 pivots and
+// 28,000 of a launch's 45,000, the rest the panel's loads and products before
+// them and the row solve after; at m = 4,000 also the trailing update, which
+// reads and writes 128 MB in the first launches.  A launch takes 21.7 us at
+// m = 1,000 (27.8 us mean at 4,000), a factorization 0.35 and 1.75 ms.  The
+// form before (a diagonal, a panel and an update launch per block, on vector
+// FMAs, the diagonal one column at a time through LDS) took 2.2 and 10.2 ms.
+// Measured beside it: the pivots of a block eliminated by lane reads in a row
+// per lane, 24.6 us a launch; four pivots at a time through a 4 x 4 inverse,
+// 25.1; the whole 64 x 64 factor by one wave, 25.5.
+typedef double d4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
+constexpr int kCholBlock = 320;  // 5 waves: one factors while four update
+constexpr int kLs = kNb + 2;     // LDS row stride (doubles): fragments fall on distinct banks
+constexpr int kTs = 18;          // the same for the 16 x 16 transposition
 
-// the nb x nb diagonal block at (k0, k0), one workgroup
-__global__ __launch_bounds__(kBlock) void k_chol_diag(double* M, int32_t m, int32_t k0, int32_t nb, int32_t* flag) {
-    __shared__ double L[kNb][kNb + 1];
-    for (int e = threadIdx.x; e < kNb * kNb; e += kBlock) {
-        const int i = e / kNb, j = e % kNb;
-        L[i][j] = (i < nb && j <= i) ? M[(int64_t)(k0 + i) * m + k0 + j] : 0.0;
+__device__ __forceinline__ d4 mfma16(double a, double b, d4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ double readlane_f64(double v, int l) {
+    union {
+        double d;
+        int i[2];
+    } u;
+    u.d = v;
+    u.i[0] = __builtin_amdgcn_readlane(u.i[0], l);
+    u.i[1] = __builtin_amdgcn_readlane(u.i[1], l);
+    return u.d;
+}
+
+// 1 / d for a finite positive d, to rounding: the hardware estimate and one
+// third-order step (a shorter chain than the division's scaling)
+__device__ __forceinline__ double recip(double d) {
+    const double x = __builtin_amdgcn_rcp(d);
+    const double e = fma(-d, x, 1.0);
+    return fma(x, fma(e, e, e), x);
+}
+
+// A 64 x 64 block of M to LDS, rows of kLs doubles
+__device__ __forceinline__ void block_to_lds(const double* src, int64_t ld, double* dst, int nthreads) {
+    for (int e = threadIdx.x; e < kNb * kNb / 2; e += nthreads) {
+        const int r = e / (kNb / 2), c = 2 * (e % (kNb / 2));
+        *(d2*)(dst + r * kLs + c) = *(const d2*)(src + r * ld + c);
     }
+}
+
+// 1 / sqrt(d) for a finite positive d, to rounding
+__device__ __forceinline__ double recip_sqrt(double d) {
+    const double y = __builtin_amdgcn_rsq(d);
+    const double e = fma(-d * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+// LDS writes of a wave before, reads after
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// a 16 x 16 block's four registers of every lane, [register][lane]
+__device__ __forceinline__ d4 load_frag(const double* B, int t) {
+    d4 v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = B[t * 256 + r * 64 + (threadIdx.x & (kWave - 1))];
+    return v;
+}
+__device__ __forceinline__ void store_frag(double* B, int t, d4 v) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) B[t * 256 + r * 64 + (threadIdx.x & (kWave - 1))] = v[r];
+}
+
+constexpr double kBadPivot = 1e128;
+
+// Index of block (i, j), i <= j < 4, of an upper triangle of 16 x 16 blocks
+__host__ __device__ constexpr int tri(int i, int j) { return i * 4 - i * (i - 1) / 2 + j - i; }
+
+// Diagonal block b of a 64 x 64 block whose upper triangle of 16 x 16 blocks
+// lies as fragments in B, factored by one wave: fragments 10 + b receive the A
+// operands of the inverse of its Cholesky factor L(b, b) (the factor itself
+// is not needed).  Eliminating with pivot j is one MFMA: row j of the block
+// lies in register j / 4 of the lanes with l / 16 = j % 4, which is where both
+// operands of a rank-1 product with k = j % 4 are read from, so the only data
+// that moves is the pivot itself; the same product applied to the identity
+// gives the inverse.  No square root is in the chain from pivot to pivot (the
+// rows are scaled at the end).  tr: LDS of the wave for a transposition.
+// Returns the number of pivots replaced.
+__device__ __forceinline__ int factor16(double* B, int b, double* tr) {
+    const int lane = threadIdx.x & (kWave - 1), l16 = lane & 15, lq = lane >> 4;
+    d4 C = load_frag(B, tri(b, b)), E, piv;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) E[r] = lq + 4 * r == l16 ? 1.0 : 0.0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int j = 4 * r + k;
+            const double d = readlane_f64(C[r], 16 * k + j);
+            const double f = d > 1e-300 ? -recip(d) : -1.0 / kBadPivot;
+            const double a = lq == k && l16 > j ? C[r] * f : 0.0;
+            if (j < 15) C = mfma16(a, C[r], C);
+            if (j < 15) E = mfma16(a, E[r], E);
+            piv[r] = k == 0 || lq == k ? d : piv[r];
+            __builtin_amdgcn_sched_barrier(0);  // the second product fills the first one's latency
+        }
+    int bad = 0;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const bool ok = piv[r] > 1e-300;
+        bad += __popcll(__ballot(!ok && l16 == 0));
+        tr[(lq + 4 * r) * kTs + l16] = E[r] * recip_sqrt(ok ? piv[r] : kBadPivot);
+    }
+    wave_lds_sync();
+    d4 F;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) F[r] = tr[l16 * kTs + 4 * r + lq];
+    store_frag(B, 10 + b, F);
+    return bad;
+}
+
+// Fragment B(b, i) <- L(i, b)^T
+__device__ __forceinline__ void solve16(double* B, int b, int i) {
+    const d4 F = load_frag(B, 10 + b), t = load_frag(B, tri(b, i));
+    d4 x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x = mfma16(F[r], t[r], x);
+    store_frag(B, tri(b, i), x);
+}
+
+// Fragment B(i, j) -= L(i, b) L(j, b)^T
+__device__ __forceinline__ void update16(double* B, int b, int i, int j) {
+    const d4 u = load_frag(B, tri(b, i)), v = load_frag(B, tri(b, j));
+    d4 x = load_frag(B, tri(i, j));
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x = mfma16(-u[r], v[r], x);
+    store_frag(B, tri(i, j), x);
+}
+
+// LDS: two 64 x 64 blocks; of the second, block column s uses the 10 + 4
+// fragments of the diagonal block and the transposition's 16 rows
+constexpr size_t kCholLds = sizeof(double) * 2 * kNb * kLs;
+static_assert(14 * 256 + 16 * kTs <= kNb * kLs, "fragments fit the second block");
+
+__global__ __launch_bounds__(kCholBlock, 3) void k_chol_step(double* M, int32_t ld, int32_t nbk, int32_t s, double* Linv,
+                                                          int32_t* flag) {
+    extern __shared__ __align__(16) double lds[];
+    double* const P = lds;               // block (s, s - 1), or (j, s - 1)
+    double* const D = lds + kNb * kLs;   // block (i, s - 1), or fragments: [block][register][lane]
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int64_t L = ld;
+    if ((int)blockIdx.x >= nbk - s) {  // block (i, j) right of column s: C -= P_i P_j^T
+        const int64_t t = (int)blockIdx.x - (nbk - s);
+        int64_t bi = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
+        while ((bi + 1) * (bi + 2) / 2 <= t) ++bi;
+        while (bi * (bi + 1) / 2 > t) --bi;
+        const int64_t bj = t - bi * (bi + 1) / 2;
+        const int64_t i = s + 1 + bi, j = s + 1 + bj;
+        block_to_lds(M + i * kNb * L + (int64_t)(s - 1) * kNb, L, D, kCholBlock);
+        block_to_lds(M + j * kNb * L + (int64_t)(s - 1) * kNb, L, P, kCholBlock);
+        __syncthreads();
+        if (wave >= 4) return;
+        const int rw = 32 * (wave >> 1), cw = 32 * (wave & 1);  // the wave's 32 x 32 quarter
+        double* C = M + (i * kNb + rw) * L + j * kNb + cw;
+        d4 acc[2][2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[u][v][r] = C[(16 * u + lq + 4 * r) * L + 16 * v + l16];
+#pragma unroll 4
+        for (int k = 0; k < kNb; k += 4) {
+            double a[2], b[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) a[u] = -D[(rw + 16 * u + l16) * kLs + k + lq];
+#pragma unroll
+            for (int v = 0; v < 2; ++v) b[v] = P[(cw + 16 * v + l16) * kLs + k + lq];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < 2; ++v) acc[u][v] = mfma16(a[u], b[v], acc[u][v]);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) C[(16 * u + lq + 4 * r) * L + 16 * v + l16] = acc[u][v][r];
+        return;
+    }
+    // block (i, s)
+    const int i = s + (int)blockIdx.x;
+    const bool diag = i == s;
+    // the diagonal block with panel s - 1 applied: the upper triangle of its
+    // ten 16 x 16 blocks (M holds the lower triangle), dealt so that no SIMD
+    // has more than three (waves 0 and 4 share one)
+    const int t0 = wave == 0 ? 0 : wave == 1 ? 1 : 2 * wave, nt = wave == 0 ? 1 : wave == 1 ? 3 : 2;
+    d4 dd[3];
+    int ti[3], tj[3];
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+        const int t = min(t0 + u, 9);
+        ti[u] = t < 4 ? 0 : t < 7 ? 1 : t < 9 ? 2 : 3;
+        tj[u] = t - tri(ti[u], ti[u]) + ti[u];
+        if (u >= nt) continue;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int x = 16 * ti[u] + lq + 4 * r, y = 16 * tj[u] + l16;
+            dd[u][r] = M[((int64_t)s * kNb + max(x, y)) * L + (int64_t)s * kNb + min(x, y)];
+        }
+    }
+    if (s > 0) {
+        block_to_lds(M + (int64_t)s * kNb * L + (int64_t)(s - 1) * kNb, L, P, kCholBlock);
+        __syncthreads();
+#pragma unroll 4
+        for (int k = 0; k < kNb; k += 4)
+#pragma unroll
+            for (int u = 0; u < 3; ++u)
+                if (u < nt)
+                    dd[u] = mfma16(-P[(16 * ti[u] + l16) * kLs + k + lq], P[(16 * tj[u] + l16) * kLs + k + lq], dd[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < 3; ++u)
+        if (u < nt) store_frag(D, t0 + u, dd[u]);
     __syncthreads();
-    for (int j = 0; j < nb; ++j) {
-        if (threadIdx.x == 0) {
-            double d = L[j][j];
-            if (!(d > 1e-300)) {
-                d = 1e128;
-                atomicAdd(flag, 1);
+    // wave 4 factors the diagonal block; the others apply panel s - 1 to X^T,
+    // the wave's 16 rows of block (i, s) as columns (the identity's rows for
+    // (s, s), whose solution is the inverse)
+    d4 X[4];
+    double* const Xg = M + ((int64_t)i * kNb + 16 * wave + l16) * L + (int64_t)s * kNb;
+    int bad = 0;
+    if (wave < 4) {
+#pragma unroll
+        for (int jb = 0; jb < 4; ++jb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int c = 16 * jb + lq + 4 * r;
+                X[jb][r] = diag ? (c == 16 * wave + l16 ? 1.0 : 0.0) : Xg[c];
             }
-            L[j][j] = sqrt(d);
-        }
-        __syncthreads();
-        for (int i = j + 1 + threadIdx.x; i < nb; i += kBlock) L[i][j] /= L[j][j];
-        __syncthreads();
-        // trailing part of the block: L[i][c] -= L[i][j] L[c][j], j < c <= i < nb
-        const int w = nb - j - 1;
-        for (int e = threadIdx.x; e < w * w; e += kBlock) {
-            const int i = j + 1 + e / w, c = j + 1 + e % w;
-            if (c <= i) L[i][c] -= L[i][j] * L[c][j];
-        }
-        __syncthreads();
     }
-    for (int e = threadIdx.x; e < kNb * kNb; e += kBlock) {
-        const int i = e / kNb, j = e % kNb;
-        if (i < nb && j <= i) M[(int64_t)(k0 + i) * m + k0 + j] = L[i][j];
+    // the panel's 64 columns are applied to X^T 16 at a time, under the four
+    // diagonal factors; the next diagonal block is brought up to date by wave
+    // 4 alone, which goes on to factor it while the others update the rest
+    const bool upd = s > 0 && !diag && wave < 4;
+    const double* Pg = M + ((int64_t)i * kNb + 16 * (wave & 3) + l16) * L + (int64_t)(s - 1) * kNb + lq;
+    double p[4], pn[4];
+    if (upd)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pn[k] = Pg[4 * k];
+#pragma unroll 1
+    for (int b = 0; b < 4; ++b) {
+        if (wave == 4) bad += factor16(D, b, D + 14 * 256);
+        if (upd) {
+            const double* Pf = P + l16 * kLs + lq + 16 * b;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                p[k] = pn[k];
+                pn[k] = Pg[16 * min(b + 1, 3) + 4 * k];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int jb = 0; jb < 4; ++jb) X[jb] = mfma16(-Pf[16 * jb * kLs + 4 * k], p[k], X[jb]);
+        }
+        __syncthreads();
+        if (b == 3) break;
+        if (wave == 4) solve16(D, b, b + 1);
+        else if (wave < 2 - b) solve16(D, b, b + 2 + wave);
+        __syncthreads();
+        if (wave == 4) update16(D, b, b + 1, b + 1);
+        else if (b == 0) {
+            if (wave == 0) update16(D, 0, 1, 2);
+            else if (wave == 1) update16(D, 0, 1, 3);
+            else if (wave == 2) update16(D, 0, 2, 2);
+            else update16(D, 0, 2, 3);
+            if (wave == 1) update16(D, 0, 3, 3);
+        } else if (b == 1) {
+            if (wave == 0) update16(D, 1, 2, 3);
+            else if (wave == 1) update16(D, 1, 3, 3);
+        }
+    }
+    if (wave == 4) {
+        if (diag && lane == 0 && bad) atomicAdd(flag, bad);
+        return;
+    }
+    // X^T <- L^-1 X^T, 16 rows at a time
+#pragma unroll
+    for (int jb = 0; jb < 4; ++jb) {
+        d4 acc = X[jb];
+#pragma unroll
+        for (int l = 0; l < jb; ++l) {
+            const d4 t = load_frag(D, tri(l, jb));
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc = mfma16(-t[r], X[l][r], acc);
+        }
+        const d4 t = load_frag(D, 10 + jb);
+        d4 x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x = mfma16(t[r], acc[r], x);
+        X[jb] = x;
+    }
+    if (diag) {  // X^T is L^-1
+        double* Li = Linv + (int64_t)s * kNb * kNb + 16 * wave + l16;
+#pragma unroll
+        for (int jb = 0; jb < 4; ++jb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Li[(16 * jb + lq + 4 * r) * kNb] = X[jb][r];
+    } else {
+#pragma unroll
+        for (int jb = 0; jb < 4; ++jb)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) Xg[16 * jb + lq + 4 * r] = X[jb][r];
     }
 }
 
-// rows below the block: X L11^T = A21, one row per thread (forward substitution)
-__global__ __launch_bounds__(kBlock) void k_chol_panel(double* M, int32_t m, int32_t k0, int32_t nb) {
-    __shared__ double L[kNb][kNb + 1];
-    for (int e = threadIdx.x; e < kNb * kNb; e += kBlock) {
-        const int i = e / kNb, j = e % kNb;
-        L[i][j] = (i < nb && j <= i) ? M[(int64_t)(k0 + i) * m + k0 + j] : 0.0;
+// --- triangular solves with the factor: one workgroup per 64 rows in one
+// launch, each taking the solution blocks it depends on from the others as
+// they are stored.  An entry not stored yet holds kUnset, a signalling NaN
+// that no arithmetic produces (results that are NaN are quiet), so the value
+// is its own flag: a block's step is one trip through memory and two
+// 64 x 64 products, of the newest block and of the inverted diagonal factor.
+// A workgroup waits only for workgroups that drew an earlier ticket, so they
+// have started and wait for none later; a wait is bounded all the same
+// (kMaxPolls), and a value that did not come is used as the NaN it is.
+// What bounds it: the chain over the 64-row blocks, 1.2 to 1.4 us each: 22 us
+// (lower) and 19 us (upper) at m = 1,000, 90 and 73 us at m = 4,000.  Before,
+// one workgroup swept the whole factor, a compute unit's read rate: 0.52 and
+// 0.62 ms, 5.8 and 10.0 ms.
+constexpr unsigned long long kUnset = 0x7ff4a55a5aa5a55aull;
+constexpr int kMaxPolls = 1 << 20;
+
+__global__ __launch_bounds__(kBlock) void k_trsv_prepare(unsigned long long* y1, unsigned long long* y2, int32_t ld,
+                                                         int32_t* ticket) {
+    const int i = blockIdx.x * kBlock + threadIdx.x;
+    if (i < 2) ticket[i] = 0;
+    if (i < ld) {
+        y1[i] = kUnset;
+        y2[i] = kUnset;
     }
+}
+
+__device__ __forceinline__ double poll(const double* p) {
+    const unsigned long long* q = (const unsigned long long*)p;
+    unsigned long long v = kUnset;
+    for (int k = 0; k < kMaxPolls; ++k) {
+        v = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (v != kUnset) break;
+    }
+    return __longlong_as_double((long long)v);
+}
+__device__ __forceinline__ void publish(double* p, double v) {
+    __hip_atomic_store((unsigned long long*)p, (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// y <- L^-1 b.  Thread 4 r + q: row r of the block, its columns 16 q .. 16 q + 15.
+__global__ __launch_bounds__(kBlock) void k_trsv_lower(const double* M, int32_t ld, const double* Linv, int32_t m,
+                                                       const double* b, double* y, int32_t* ticket) {
+    __shared__ double xs[2][4 * 18];
+    __shared__ int tk;
+    if (threadIdx.x == 0) tk = atomicAdd(ticket, 1);
     __syncthreads();
-    const int64_t i = (int64_t)k0 + nb + (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= m) return;
-    double* row = M + i * m + k0;
-    double x[kNb];
+    const int i = tk, r = threadIdx.x >> 2, q = threadIdx.x & 3;
+    const int64_t L = ld;
+    const double* Li = Linv + ((int64_t)i * kNb + r) * kNb + 16 * q;
+    const double* A = M + ((int64_t)i * kNb + r) * L + 16 * q;
+    d2 li[8], a[8], nx[8];
 #pragma unroll
-    for (int j = 0; j < kNb; ++j) x[j] = j < nb ? row[j] : 0.0;
+    for (int k = 0; k < 8; ++k) li[k] = *(const d2*)(Li + 2 * k);
+    const int row = i * kNb + r;
+    const double bi = row < m ? b[row] : 0.0;
+    if (i > 0)
 #pragma unroll
-    for (int j = 0; j < kNb; ++j) {
-        if (j < nb) {
-            double s = x[j];
-            for (int l = 0; l < j; ++l) s -= x[l] * L[j][l];
-            x[j] = s / L[j][j];
+        for (int k = 0; k < 8; ++k) nx[k] = *(const d2*)(A + 2 * k);
+    double acc = 0.0;
+    for (int j = 0; j < i; ++j) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) a[k] = nx[k];
+        if (j + 1 < i)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) nx[k] = *(const d2*)(A + (int64_t)(j + 1) * kNb + 2 * k);
+        double* x = xs[j & 1];
+        if (threadIdx.x < kNb) x[18 * (threadIdx.x >> 4) + (threadIdx.x & 15)] = poll(y + (int64_t)j * kNb + threadIdx.x);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const d2 v = *(const d2*)(x + 18 * q + 2 * k);
+            acc = fma(a[k][0], v[0], acc);
+            acc = fma(a[k][1], v[1], acc);
         }
     }
+    acc += __shfl_xor(acc, 1, kWave);
+    acc += __shfl_xor(acc, 2, kWave);
+    double* x = xs[i & 1];
+    if (q == 0) x[18 * (r >> 4) + (r & 15)] = bi - acc;
+    __syncthreads();
+    acc = 0.0;
 #pragma unroll
-    for (int j = 0; j < kNb; ++j)
-        if (j < nb) row[j] = x[j];
-}
-
-// trailing update M[i][j] -= sum_l L[i][k0 + l] L[j][k0 + l] over the lower
-// tiles (bi >= bj) of the region from k1 = k0 + nb; 64 x 64 tile per
-// workgroup, 4 x 4 outputs per thread
-__global__ __launch_bounds__(kBlock) void k_chol_update(double* M, int32_t m, int32_t k0, int32_t nb) {
-    constexpr int kL = kNb / 2;  // columns of the panel staged at a time (two 16 KB halves)
-    __shared__ double Pi[kL][kNb];  // Pi[l][a] = L[r0 + a][k0 + lc + l]
-    __shared__ double Pj[kL][kNb];
-    // linear tile index -> (bi, bj), bj <= bi
-    const int64_t t = blockIdx.x;
-    int64_t bi = (int64_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
-    while ((bi + 1) * (bi + 2) / 2 <= t) ++bi;
-    while (bi * (bi + 1) / 2 > t) --bi;
-    const int64_t bj = t - bi * (bi + 1) / 2;
-    const int64_t k1 = (int64_t)k0 + nb;
-    const int64_t r0 = k1 + bi * kNb, c0 = k1 + bj * kNb;
-    const int ty = threadIdx.x / 16, tx = threadIdx.x % 16;  // rows ty + 16 u, cols tx + 16 v
-    double acc[4][4] = {};
-    for (int lc = 0; lc < nb; lc += kL) {
-        for (int e = threadIdx.x; e < kNb * kL; e += kBlock) {
-            const int a = e / kL, l = e % kL;
-            const bool in = lc + l < nb;
-            Pi[l][a] = (r0 + a < m && in) ? M[(r0 + a) * m + k0 + lc + l] : 0.0;
-            Pj[l][a] = (c0 + a < m && in) ? M[(c0 + a) * m + k0 + lc + l] : 0.0;
-        }
-        __syncthreads();
-        for (int l = 0; l < kL; ++l) {
-            double a[4], b[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) a[u] = Pi[l][ty + 16 * u];
-#pragma unroll
-            for (int v = 0; v < 4; ++v) b[v] = Pj[l][tx + 16 * v];
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[u][v] += a[u] * b[v];
-        }
-        __syncthreads();
+    for (int k = 0; k < 8; ++k) {
+        const d2 v = *(const d2*)(x + 18 * q + 2 * k);
+        acc = fma(li[k][0], v[0], acc);
+        acc = fma(li[k][1], v[1], acc);
     }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int64_t i = r0 + ty + 16 * u, j = c0 + tx + 16 * v;
-            if (i < m && j <= i) M[i * m + j] -= acc[u][v];
-        }
+    acc += __shfl_xor(acc, 1, kWave);
+    acc += __shfl_xor(acc, 2, kWave);
+    if (q == 0) publish(y + row, acc);
 }
 
-// L x = b in place (x holds b), one workgroup
-__global__ __launch_bounds__(kBlock) void k_trsv_lower(const double* L, int32_t m, double* x) {
-    const int lane = threadIdx.x;
-    for (int32_t k0 = 0; k0 < m; k0 += kNb) {
-        const int nb = min(kNb, m - k0);
-        if (threadIdx.x < kWave) {
-            double xi = lane < nb ? x[k0 + lane] : 0.0, mine = 0.0;
-            for (int j = 0; j < nb; ++j) {
-                const double xj = __shfl(xi, j, kWave) / L[(int64_t)(k0 + j) * m + k0 + j];
-                if (lane == j) mine = xj;
-                if (lane > j && lane < nb) xi -= L[(int64_t)(k0 + lane) * m + k0 + j] * xj;
-            }
-            if (lane < nb) x[k0 + lane] = mine;
-        }
+// x <- L^-T b (b, y of ld entries; x of m).  Thread 64 w + c: column c of the
+// block, rows 16 w .. 16 w + 15.
+__global__ __launch_bounds__(kBlock) void k_trsv_upper_t(const double* M, int32_t ld, const double* Linv, int32_t nbk,
+                                                         int32_t m, const double* b, double* y, double* x_out,
+                                                         int32_t* ticket) {
+    __shared__ double xs[2][kNb];
+    __shared__ double part[4][kNb];
+    __shared__ int tk;
+    if (threadIdx.x == 0) tk = atomicAdd(ticket, 1);
+    __syncthreads();
+    const int i = nbk - 1 - tk, c = threadIdx.x & (kNb - 1), w = threadIdx.x >> 6;
+    const int64_t L = ld;
+    const double* Li = Linv + ((int64_t)i * kNb + 16 * w) * kNb + c;
+    const double* A = M + (int64_t)16 * w * L + (int64_t)i * kNb + c;  // block (0, i), the thread's first row
+    double li[16], a[16], nx[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) li[k] = Li[k * kNb];
+    if (i < nbk - 1)
+#pragma unroll
+        for (int k = 0; k < 16; ++k) nx[k] = A[((int64_t)(nbk - 1) * kNb + k) * L];
+    double acc = 0.0;
+    for (int j = nbk - 1; j > i; --j) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) a[k] = nx[k];
+        if (j - 1 > i)
+#pragma unroll
+            for (int k = 0; k < 16; ++k) nx[k] = A[((int64_t)(j - 1) * kNb + k) * L];
+        double* x = xs[j & 1];
+        if (w == 0) x[c] = poll(y + (int64_t)j * kNb + c);
         __syncthreads();
-        for (int64_t i = (int64_t)k0 + nb + threadIdx.x; i < m; i += kBlock) {
-            const double* row = L + i * m + k0;
-            double s = 0.0;
-            for (int l = 0; l < nb; ++l) s += row[l] * x[k0 + l];
-            x[i] -= s;
-        }
-        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < 16; ++k) acc = fma(a[k], x[16 * w + k], acc);
     }
-}
-
-// L^T x = b in place (x holds b), one workgroup
-__global__ __launch_bounds__(kBlock) void k_trsv_upper_t(const double* L, int32_t m, double* x) {
-    const int lane = threadIdx.x;
-    const int32_t nblk = (m + kNb - 1) / kNb;
-    for (int32_t kb = nblk - 1; kb >= 0; --kb) {
-        const int32_t k0 = kb * kNb;
-        const int nb = min(kNb, m - k0);
-        if (threadIdx.x < kWave) {
-            double xi = lane < nb ? x[k0 + lane] : 0.0, mine = 0.0;
-            for (int j = nb - 1; j >= 0; --j) {
-                const double xj = __shfl(xi, j, kWave) / L[(int64_t)(k0 + j) * m + k0 + j];
-                if (lane == j) mine = xj;
-                if (lane < j) xi -= L[(int64_t)(k0 + j) * m + k0 + lane] * xj;
-            }
-            if (lane < nb) x[k0 + lane] = mine;
-        }
-        __syncthreads();
-        for (int64_t i = threadIdx.x; i < k0; i += kBlock) {
-            double s = 0.0;
-            for (int l = 0; l < nb; ++l) s += L[(int64_t)(k0 + l) * m + i] * x[k0 + l];
-            x[i] -= s;
-        }
-        __syncthreads();
+    double* x = xs[i & 1];
+    part[w][c] = acc;
+    __syncthreads();
+    if (w == 0) x[c] = b[(int64_t)i * kNb + c] - (((part[0][c] + part[1][c]) + part[2][c]) + part[3][c]);
+    __syncthreads();
+    acc = 0.0;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) acc = fma(li[k], x[16 * w + k], acc);
+    part[w][c] = acc;
+    __syncthreads();
+    if (w == 0) {
+        const double v = ((part[0][c] + part[1][c]) + part[2][c]) + part[3][c];
+        const int row = i * kNb + c;
+        publish(y + row, v);
+        if (row < m) x_out[row] = v;
     }
 }
 
@@ -394,15 +743,20 @@ __global__ __launch_bounds__(kBlock) void k_ipm_summin(const double* a, const do
 struct IpmWs {
     double *M, *av, *atv, *bt, *ct, *x, *y, *z, *dx, *dy, *dz, *dxa, *dya, *dza, *d, *t, *v, *rb, *rc, *rhs;
     double *xc, *yc, *zc, *part, *scal;
-    int32_t* flag;
+    double *linv, *y1, *y2;  // inverted diagonal factors; the triangular solves' vectors
+    int32_t *flag, *ticket;
     void* cws;  // centering workspace
     size_t bytes;
 };
 
+// order of the dense matrix: m rounded up to whole blocks
+int64_t ipm_ld(int64_t m) { return (m + kNb - 1) / kNb * kNb; }
+
 IpmWs carve_ipm(void* base, int64_t m, int64_t n, int64_t nnz) {
     Carver cv(base, 0);
     IpmWs w;
-    w.M = cv.take<double>((size_t)(m * m));
+    const int64_t ld = ipm_ld(m);
+    w.M = cv.take<double>((size_t)(ld * ld));
     w.av = cv.take<double>(nnz);
     w.atv = cv.take<double>(nnz);
     w.bt = cv.take<double>(m);
@@ -427,7 +781,11 @@ IpmWs carve_ipm(void* base, int64_t m, int64_t n, int64_t nnz) {
     w.zc = cv.take<double>(n);
     w.part = cv.take<double>((size_t)kRedBlocks * 4);
     w.scal = cv.take<double>(16);
+    w.linv = cv.take<double>((size_t)(ld * kNb));
+    w.y1 = cv.take<double>((size_t)ld);
+    w.y2 = cv.take<double>((size_t)ld);
     w.flag = cv.take<int32_t>(4);
+    w.ticket = cv.take<int32_t>(4);
     w.cws = cv.take<char>(mipdhg_center_workspace_size((int32_t)n));
     w.bytes = cv.off;
     return w;
@@ -456,30 +814,38 @@ struct Ipm {
         MIP_LAUNCH_CHECK();
         return 0;
     }
+    // the kernels that may need more than 64 KB of LDS
+    int allow_lds() {
+        MIP_HIP(hipFuncSetAttribute((const void*)k_chol_step, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)kCholLds));
+        MIP_HIP(hipFuncSetAttribute((const void*)k_ipm_normal, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    (int)(kIpmMaxM * 8)));
+        return 0;
+    }
     // M = A~ diag(wt) A~^T (lower), then its Cholesky factor in place
     int factor(const double* wt) {
-        hipLaunchKernelGGL(k_ipm_normal, dim3((unsigned)((m + kBlock - 1) / kBlock), (unsigned)m), dim3(kBlock), 0, s,
-                           lp.a_rowptr, lp.a_col, (const double*)w.av, wt, (int32_t)m, w.M);
+        const int ld = (int)ipm_ld(m), nbk = ld / kNb;
+        hipLaunchKernelGGL(k_ipm_normal, dim3(ld), dim3(kWave), (size_t)ld * 8, s, lp.a_rowptr, lp.a_col,
+                           (const double*)w.av, lp.at_rowptr, lp.at_col, (const double*)w.atv, wt, (int32_t)m, ld,
+                           w.M);
         MIP_LAUNCH_CHECK();
-        for (int64_t k0 = 0; k0 < m; k0 += kNb) {
-            const int nb = (int)std::min<int64_t>(kNb, m - k0);
-            hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(kBlock), 0, s, w.M, (int32_t)m, (int32_t)k0, nb, w.flag);
-            const int64_t rest = m - k0 - nb;
-            if (rest > 0) {
-                hipLaunchKernelGGL(k_chol_panel, dim3((unsigned)((rest + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                                   w.M, (int32_t)m, (int32_t)k0, nb);
-                const int64_t T = (rest + kNb - 1) / kNb;
-                hipLaunchKernelGGL(k_chol_update, dim3((unsigned)(T * (T + 1) / 2)), dim3(kBlock), 0, s, w.M,
-                                   (int32_t)m, (int32_t)k0, nb);
-            }
-            MIP_LAUNCH_CHECK();
+        for (int k = 0; k < nbk; ++k) {
+            const int R = nbk - 1 - k;  // block rows below, and right of, column k
+            hipLaunchKernelGGL(k_chol_step, dim3(R + 1 + (k > 0 ? R * (R + 1) / 2 : 0)), dim3(kCholBlock), kCholLds, s,
+                               w.M, ld, nbk, k, w.linv, w.flag);
         }
+        MIP_LAUNCH_CHECK();
         return 0;
     }
     // x <- M^-1 x with the factor in M
     int solve(double* x) {
-        hipLaunchKernelGGL(k_trsv_lower, dim3(1), dim3(kBlock), 0, s, (const double*)w.M, (int32_t)m, x);
-        hipLaunchKernelGGL(k_trsv_upper_t, dim3(1), dim3(kBlock), 0, s, (const double*)w.M, (int32_t)m, x);
+        const int ld = (int)ipm_ld(m), nbk = ld / kNb;
+        hipLaunchKernelGGL(k_trsv_prepare, dim3((ld + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
+                           (unsigned long long*)w.y1, (unsigned long long*)w.y2, ld, w.ticket);
+        hipLaunchKernelGGL(k_trsv_lower, dim3(nbk), dim3(kBlock), 0, s, (const double*)w.M, ld, (const double*)w.linv,
+                           (int32_t)m, (const double*)x, w.y1, w.ticket);
+        hipLaunchKernelGGL(k_trsv_upper_t, dim3(nbk), dim3(kBlock), 0, s, (const double*)w.M, ld,
+                           (const double*)w.linv, nbk, (int32_t)m, (const double*)w.y1, w.y2, x, w.ticket + 1);
         MIP_LAUNCH_CHECK();
         return 0;
     }
@@ -706,6 +1072,7 @@ int ipm_setup(Ipm& P, const double* d_row, const double* d_col) {
                        MIPDHG_ERR_BAD_CSR;
         }
     const IpmWs& w = P.w;
+    if ((rc = P.allow_lds())) return rc;
     hipLaunchKernelGGL(k_ipm_scale_vals, dim3(grid_for(lp.m)), dim3(kBlock), 0, s, lp.a_rowptr, lp.a_col, lp.a_val,
                        lp.m, d_row, d_col, 0, w.av);
     hipLaunchKernelGGL(k_ipm_scale_vals, dim3(grid_for(lp.n)), dim3(kBlock), 0, s, lp.at_rowptr, lp.at_col, lp.at_val,

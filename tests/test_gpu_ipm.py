@@ -138,3 +138,31 @@ def test_refused_inputs():
     with pytest.raises(P.MipdhgError) as e:
         P.ipm_solve(bad)
     assert e.value.code == -2
+
+
+@pytest.mark.parametrize("m", [1, 2, 15, 63, 64, 65, 127, 128, 129, 193])
+def test_newton_steps_match_the_oracle_at_the_block_edges(m):
+    # orders at and around whole 16- and 64-row blocks of the factorization; three steps from Mehrotra's point
+    # are far from the boundary, where M is well conditioned: rounding times the steps, 1e-10 relative
+    lp = lpgen.tiny(m, 3 * m + 2, min(4, m), 7)
+    At, bt, ct, d_row, d_col = _scaled(lp)
+    ref = I.ipm(At, bt, ct, max_iter=3)
+    sol = P.ipm_solve(P.DeviceLP.from_lp(lp), _dev(d_row), _dev(d_col), max_iter=3)
+    assert sol.info["iters"] == ref.iters and sol.info["pivots_replaced"] == 0
+    for got, want in ((_np(sol.x) / d_col, ref.x), (_np(sol.y) / d_row, ref.y), (_np(sol.z) * d_col, ref.z)):
+        assert np.linalg.norm(got - want) <= 1e-10 * (1 + np.linalg.norm(want))
+
+
+@pytest.mark.parametrize("row", [0, 17, 64, 99])
+def test_an_empty_row_is_one_replaced_pivot_per_factorization(row):
+    lp = lpgen.tiny(99, 300, 4, 3)
+    A = sp.csr_matrix(sp.vstack([lp.A[:row], sp.csr_matrix((1, lp.n)), lp.A[row:]]))
+    AT = sp.csr_matrix(A.T)
+    AT.sort_indices()
+    b = np.insert(lp.b, row, 0.0)
+    full = P.ipm_solve(P.DeviceLP.from_lp(lp), max_iter=4)
+    sol = P.ipm_solve(P.DeviceLP(A, AT, b, lp.c, "cuda"), max_iter=4)
+    assert sol.info["pivots_replaced"] == 1 + sol.info["iters"] and full.info["pivots_replaced"] == 0
+    # the row decouples: its dual stays 0 (its pivot is 1e128), the others are those of the LP without it
+    assert abs(float(sol.y[row])) <= 1e-60
+    assert torch.linalg.norm(sol.x - full.x) <= 1e-10 * (1 + torch.linalg.norm(full.x))
