@@ -256,13 +256,11 @@ typedef struct mipdhg_options {
     double step0;
     /* Batched solve, > 0: two concurrent launches.  Instances whose y and
      * x_bar (the vectors kept in LDS) fit in batch_split bytes run in
-     * 256-thread workgroups at the occupancy that size allows; the others
-     * run in 1024-thread workgroups (four times the threads on each row and
-     * column).  0 = one launch of 256-thread workgroups sized by the largest
-     * instance.  The narrow class's results are bitwise those of the single
-     * launch; the wide class sums over other thread partitions, so its
-     * iterates agree to rounding.  mipdhg_autotune_batched picks the
-     * fastest.                                                              [0] */
+     * 256-thread workgroups; the others run in 1024-thread workgroups (four
+     * times the threads on each row and column).  0 = concurrent launches of
+     * workgroups of 64 to 1,024 threads, each instance by the LDS it needs
+     * with its matrices.  An instance's results do not depend on the
+     * workgroup that ran it.  mipdhg_autotune_batched picks the fastest.    [0] */
     int32_t batch_split;
     /* Batched solve, > 0: iterations per call.  Each unfinished instance
      * stops at its first evaluation at least batch_block_iters iterations
@@ -592,11 +590,11 @@ int mipdhg_ipm_warm(const mipdhg_lp *lp, const double *d_row, const double *d_co
 int mipdhg_read_probe(const void *buf, size_t bytes, int32_t blocks, void *stream, uint32_t *out);
 
 /* Times mipdhg_solve_batched on this batch with each candidate batch_split
- * (0, 2, 4, 8, 16, 32 KB: one launch, or the instances whose vectors fit the
- * budget in narrow workgroups beside wide workgroups for the others) and
+ * (0, 2, 4, 8, 16, 32 KB: by the instances' LDS needs, or the instances whose
+ * vectors fit the budget in narrow workgroups beside wide ones for the
+ * others) and
  * writes the fastest into opt->batch_split (0 kept unless another is more
- * than 3 % faster).  The candidates' results agree to rounding (bitwise for
- * the narrow class); the outputs hold the last candidate's.  Arguments as for
+ * than 3 % faster).  The candidates' results are the same.  Arguments as for
  * mipdhg_solve_batched; best_ms (host, nullable) receives the chosen
  * candidate's kernel time. */
 int mipdhg_autotune_batched(const mipdhg_batch *bt, mipdhg_options *opt, const double *eps_rel, void *workspace,

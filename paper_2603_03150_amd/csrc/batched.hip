@@ -6,8 +6,12 @@
 // the PDHG iterations, float64 evaluations on the original block and the
 // restart / primal-weight rule, with __syncthreads() as the only phase barrier.
 // The dual iterate y and the extrapolated primal x_bar, the two vectors the
-// SpMVs gather from, live in LDS; everything else stays in L2-resident global
-// memory.  Each thread owns fixed rows and columns of its instance, and every
+// SpMVs gather from, live in LDS; between evaluations each thread holds the
+// entries of its rows and columns and their vectors' entries in registers, and
+// LDS takes what they leave of the matrices (see Side and RegSide).  An
+// iteration is then two barriers and, for each row, a few gathers in LDS: it
+// is bound by their latency and by the instructions a wave issues (alone on a
+// compute unit, FP32: 2,500 clocks at 60 rows, 13,500 at 1,900).  Every
 // reduction is a fixed-order workgroup reduction whose result every thread
 // holds, so all threads take the same decisions without a broadcast and the
 // results do not depend on which workgroup ran the instance.
@@ -25,6 +29,8 @@
 
 namespace mip {
 
+constexpr int kClasses = 4;  // launch classes (see kClassBs)
+
 struct BInst {  // per-instance result, device side
     int32_t status, restarts;
     int64_t iters;
@@ -36,25 +42,21 @@ struct BState {  // an instance's solve state between resumable calls
     int64_t t, k;
     double omega, tau, sig, R0, R_prev;
     int32_t restarts, phase;  // phase: 1 suspended, 2 finished
+    int32_t levels, pad;      // the matrices' layout (see Side)
 };
 
 template <typename T, typename V>
 struct BArgs {
     int32_t B;
-    int32_t lds_m, lds_n;
+    int32_t lds;  // bytes of dynamic LDS per workgroup
     const int32_t* order;
     const int32_t* row_off;
     const int32_t* col_off;
-    const int32_t *a_rowptr, *a_col;
-    const double* a_val;
-    const int32_t *at_rowptr, *at_col;
-    const double* at_val;
-    const double *b, *c;
-    V *a_vs, *at_vs;
-    uint16_t *a_cl, *at_cl;  // instance-local columns of A, A^T
+    InstMat M;
+    InstStore<V> S;
     // the state relative to the epoch's anchor (x0, y0): x holds u = x - x0
     // (y's v = y - y0 is in LDS), ct and bt the anchor's residuals
-    // c~ - A~^T y0 and b~ - A~ x0
+    // c~ - A~^T y0 and b~ - A~ x0; all by position (see Side)
     T *x, *x0, *xhat, *ct, *y0, *yhat, *bt;
     double *d_row, *d_col, *pu, *pav;
     double *xo, *yo, *zo, *rpo, *rdo;
@@ -69,263 +71,316 @@ struct BArgs {
     int32_t ruiz, pc, power_iters, eval_every, halpern, restarts;
 };
 
-template <typename T, typename V, typename Acc, int BS>
-__device__ void solve_instance(const BArgs<T, V>& a, int inst, T* yL, T* xbL, double* sh) {
-    const int tid = threadIdx.x;
-    const int r0 = a.row_off[inst], r1 = a.row_off[inst + 1];
-    const int c0 = a.col_off[inst], c1 = a.col_off[inst + 1];
-    const int m = r1 - r0, n = c1 - c0;
-    double nomax[1] = {0.0};
-    BState& st = a.state[inst];
-    // phase of this instance in the workspace: 0 fresh, 1 suspended at the
-    // end of a block, 2 finished (read by every thread: uniform)
-    const int phase = a.resume ? st.phase : 0;
-    if (phase == 2) return;  // finished in an earlier call: its outputs and report stand
-    const double eps = a.eps[inst];
-    double eta, omega, tau, sig, tol_p, tol_d;
-    int64_t k, t;
-    double R0, R_prev;
-    int restarts;
-    if (phase == 0) {
-        const InstMat M{a.a_rowptr, a.a_col, a.a_val, a.at_rowptr, a.at_col, a.at_val, a.b, a.c};
-        const InstSetup su = inst_setup<T, V, BS>(M, r0, r1, c0, c1, a.d_row, a.d_col, a.pu, a.pav, a.a_vs,
-                                                  a.at_vs, a.a_cl, a.at_cl, a.bt, a.ct, a.ruiz, a.pc,
-                                                  a.power_iters, a.step_safety, xbL, yL, sh);
-        // the report's set-up fields are written now, so that they do not
-        // stay live (in registers) across the iterations
-        if (tid == 0) {
-            BInst& r = a.info[inst];
-            r.b_norm = su.b_norm;
-            r.c_norm = su.c_norm;
-            r.sigma_hat = su.sigma_hat;
-            r.eta = su.eta;
-            r.omega0 = su.omega0;
-        }
-        eta = su.eta;
-        omega = su.omega0;
-        tau = eta / omega;
-        sig = eta * omega;
-        tol_p = eps * (1.0 + su.b_norm);
-        tol_d = eps * (1.0 + su.c_norm);
-        k = 0;
-        t = 0;
-        R0 = NAN;
-        R_prev = INFINITY;
-        restarts = 0;
-        // initial point (0, 0)
-        for (int j = tid; j < n; j += BS) {
-            a.x[c0 + j] = (T)0;
-            a.x0[c0 + j] = (T)0;
-        }
-        for (int i = tid; i < m; i += BS) {
-            yL[i] = (T)0;
-            a.y0[r0 + i] = (T)0;
-        }
-    } else {
-        // resume: the scaled matrix, b~, c~, the scaling, x, the anchors and
-        // the report's set-up fields are still in the workspace; y and the
-        // scalars were saved when the block ended
-        const BInst& r = a.info[inst];
-        eta = r.eta;
-        tol_p = eps * (1.0 + r.b_norm);
-        tol_d = eps * (1.0 + r.c_norm);
-        omega = st.omega;
-        tau = st.tau;
-        sig = st.sig;
-        k = st.k;
-        t = st.t;
-        R0 = st.R0;
-        R_prev = st.R_prev;
-        restarts = st.restarts;
-        for (int i = tid; i < m; i += BS) yL[i] = a.ysave[r0 + i];
+// The instance's sizes and its vectors in LDS
+template <typename T, typename V>
+__device__ __forceinline__ Inst<T, V> inst_of(const BArgs<T, V>& a, int inst, unsigned char* lds) {
+    Inst<T, V> I;
+    I.r0 = uniform(a.row_off[inst]);
+    I.c0 = uniform(a.col_off[inst]);
+    I.m = uniform(a.row_off[inst + 1]) - I.r0;
+    I.n = uniform(a.col_off[inst + 1]) - I.c0;
+    I.z0 = uniform(a.M.a_rowptr[I.r0]);
+    I.nnz = uniform(a.M.a_rowptr[I.r0 + I.m]) - I.z0;
+    I.yl = (T*)lds;
+    I.xl = (T*)(lds + inst_align((I.m + 1) * (int)sizeof(T)));
+    return I;
+}
+
+// The instance's set-up, and its state before the first iteration
+template <typename T, typename V, int BS>
+__device__ void setup_instance(const BArgs<T, V>& a, int inst, unsigned char* lds, double* sh) {
+    Inst<T, V> I = inst_of(a, inst, lds);
+    const InstSetup su = inst_setup<T, V, BS>(I, a.M, a.S, a.d_row, a.d_col, a.pu, a.pav, a.bt, a.ct, a.ruiz, a.pc,
+                                              a.power_iters, a.step_safety, lds, a.lds, sh);
+    if (threadIdx.x == 0) {
+        BInst& r = a.info[inst];
+        r.b_norm = su.b_norm;
+        r.c_norm = su.c_norm;
+        r.sigma_hat = su.sigma_hat;
+        r.eta = su.eta;
+        r.omega0 = su.omega0;
+        BState& st = a.state[inst];
+        st.phase = 1;
+        st.levels = I.levels;
+        st.t = 0;
+        st.k = 0;
+        st.omega = su.omega0;
+        st.tau = su.eta / su.omega0;
+        st.sig = su.eta * su.omega0;
+        st.R0 = NAN;
+        st.R_prev = INFINITY;
+        st.restarts = 0;
     }
+    // initial point (0, 0)
+    for (int p = threadIdx.x; p < I.n; p += BS) {
+        a.x[I.c0 + p] = (T)0;
+        a.x0[I.c0 + p] = (T)0;
+    }
+    for (int p = threadIdx.x; p < I.m; p += BS) {
+        a.ysave[I.r0 + p] = (T)0;
+        a.y0[I.r0 + p] = (T)0;
+    }
+}
+
+// `count` iterations of an instance with no sums, from iteration k of the
+// epoch on.  Each thread loads its register rows first (a loop of their own,
+// so that nothing else competes for the registers: they are read again after
+// each evaluation, a few us in about 60 us).  Float64 arithmetic, stored in
+// T: u = x - x0, v = y - y0 (in LDS), rc = c~ - A~^T y0, rb = b~ - A~ x0:
+// x_hat = x0 + max(u - tau (rc - A~^T v), -x0),
+// y_hat = y0 + v + sigma (rb - A~ (x_bar - x0)).
+template <typename T, typename V, typename Acc, int BS>
+__device__ __forceinline__ void plain_iterations(const BArgs<T, V>& a, const Inst<T, V>& I, unsigned char* lds, int count,
+                                                 int64_t k, double tau, double sig) {
+    typedef RegShape<V> RS;
+    const int tid = opaque(threadIdx.x);
+    const int m = I.m, n = I.n, c0 = I.c0, r0 = I.r0;
+    T *const yL = I.yl, *const xbL = I.xl;
+    const double rho = a.rho, opr = 1.0 + a.rho;
+    RegSide<V, RS::RC, RS::KC> gt;
+    RegSide<V, RS::RR, RS::KR> ga;
+    reg_load<BS, T>(gt, I.AT, lds, n, m);
+    reg_load<BS, T>(ga, I.A, lds, m, n);
+    T ur[RS::RC], x0r[RS::RC], rcr[RS::RC], rbr[RS::RR];
+#pragma unroll
+    for (int r = 0; r < RS::RC; ++r) {
+        const int g = c0 + min(tid + r * BS, n - 1);
+        ur[r] = a.x[g];
+        x0r[r] = a.x0[g];
+        rcr[r] = a.ct[g];
+    }
+#pragma unroll
+    for (int r = 0; r < RS::RR; ++r) rbr[r] = a.bt[r0 + min(tid + r * BS, m - 1)];
+    double wl = 1.0;  // lane l: the Halpern weight of iteration l of each 64
+    for (int it = 0; it < count; ++it) {
+        if (a.halpern && (it & (kWave - 1)) == 0) {
+            const double kl = (double)(k + it + (tid & (kWave - 1)));
+            wl = (kl + 1.0) / (kl + 2.0);
+        }
+        const double w = lane_value(wl, it & (kWave - 1));
+        gt.pin();
+        ga.pin();
+        inst_rows<BS, RS::RC, Acc>(I.levels, n, gt, I.AT, lds, yL, [&](int p, int r, Acc s) {
+            const int g = c0 + p;
+            const double u = (double)(r >= 0 ? ur[r] : a.x[g]), x0 = (double)(r >= 0 ? x0r[r] : a.x0[g]);
+            const double rc = (double)(r >= 0 ? rcr[r] : a.ct[g]);
+            double uh = u - tau * (rc - (double)s);
+            uh = uh < -x0 ? -x0 : uh;
+            xbL[p] = (T)(2.0 * uh - u);  // x_bar - x0
+            const T un = (T)(w * (opr * uh - rho * u));
+            if (r >= 0) ur[r] = un;
+            else a.x[g] = un;
+        });
+        __syncthreads();
+        inst_rows<BS, RS::RR, Acc>(I.levels, m, ga, I.A, lds, xbL, [&](int p, int r, Acc s) {
+            const double rb = (double)(r >= 0 ? rbr[r] : a.bt[r0 + p]);
+            const double v = (double)yL[p];
+            const double vh = v + sig * (rb - (double)s);
+            yL[p] = (T)(w * (opr * vh - rho * v));
+        });
+        __syncthreads();
+    }
+    if (I.levels)
+#pragma unroll
+        for (int r = 0; r < RS::RC; ++r)
+            if (tid + r * BS < n) a.x[c0 + tid + r * BS] = ur[r];
+}
+
+// The iterations of an instance from the state in the workspace (set up, or
+// suspended at the end of a block): the scaled matrix, b~, c~, the scaling, x,
+// the anchors and the report's set-up fields, y and the scalars.
+template <typename T, typename V, typename Acc, int BS>
+__device__ void solve_instance(const BArgs<T, V>& a, int inst, unsigned char* lds, double* sh) {
+    const int tid = threadIdx.x;
+    BState& st = a.state[inst];
+    if (uniform(st.phase) == 2) return;  // finished in an earlier call: its outputs and report stand
+    Inst<T, V> I = inst_of(a, inst, lds);
+    const int r0 = I.r0, c0 = I.c0, m = I.m, n = I.n;
+    T *const yL = I.yl, *const xbL = I.xl;
+    const double eps = uniform(a.eps[inst]);
+    const BInst& in = a.info[inst];
+    const double eta = uniform(in.eta), tol_p = uniform(eps * (1.0 + in.b_norm)),
+                 tol_d = uniform(eps * (1.0 + in.c_norm));
+    double omega = uniform(st.omega), tau = uniform(st.tau), sig = uniform(st.sig), R0 = uniform(st.R0),
+           R_prev = uniform(st.R_prev);
+    int64_t k = uniform64(st.k), t = uniform64(st.t);
+    int restarts = uniform(st.restarts);
+    I.levels = uniform(st.levels) != 0;
+    I.perm_r = a.S.perm_r + r0;
+    I.perm_c = a.S.perm_c + c0;
+    inst_load<T, V, BS>(I, a.M, a.S, lds, a.lds, true);
+    for (int p = tid; p < m; p += BS) yL[p] = a.ysave[r0 + p];
     __syncthreads();
 
+    typedef RegShape<V> RS;
     const double rho = a.rho, opr = 1.0 + a.rho;
     const int E = a.eval_every;
+    const int32_t *arp = a.M.a_rowptr + r0, *trp = a.M.at_rowptr + c0;
     const int64_t t_begin = t;
+    int to_eval = (int)(E - t % E);  // iterations up to and with the next evaluation
+    if (a.max_iter > t && a.max_iter - t < to_eval) to_eval = (int)(a.max_iter - t);
     bool suspended = false;
     int status = -1;
     while (status < 0) {
+        // the iterations that nothing is summed over: all but an epoch's
+        // first and the evaluated one
+        const int plain = k == 0 ? 0 : to_eval - 1;
+        if (plain > 0) {
+            plain_iterations<T, V, Acc, BS>(a, I, lds, plain, k, tau, sig);
+            t += plain;
+            k += plain;
+            to_eval -= plain;
+        }
         ++t;
-        const bool is_eval = (t % E == 0) || (t == a.max_iter);
+        const bool is_eval = --to_eval <= 0;
         const bool first = (k == 0);
         const double w = a.halpern ? (double)(k + 1) / (double)(k + 2) : 1.0;
-        double q[4] = {0.0, 0.0, 0.0, 0.0};
-        // primal step over the columns (rows of A^T); float64 arithmetic,
-        // stored in T.  The next row's bounds and vector entries are loaded
-        // (branch-free, clamped to the last row) while this row is summed.
-        int nb0 = 0, nb1 = 0;
-        T nx = 0, nx0 = 0, nct = 0;
-        if (n > 0) {
-            const int g = c0 + min(tid, n - 1);
-            nb0 = a.at_rowptr[g];
-            nb1 = a.at_rowptr[g + 1];
-            nx = a.x[g];
-            nx0 = a.x0[g];
-            nct = a.ct[g];
-        }
-        for (int j = tid; j < n; j += BS) {
-            const int g = c0 + j;
-            const int b0 = nb0, b1 = nb1;
-            const double u = (double)nx, x0 = (double)nx0, rc = (double)nct;
-            {
-                const int gn = c0 + min(j + BS, n - 1);
-                nb0 = a.at_rowptr[gn];
-                nb1 = a.at_rowptr[gn + 1];
-                nx = a.x[gn];
-                nx0 = a.x0[gn];
-                nct = a.ct[gn];
-            }
-            // u = x - x0, v = y - y0 (in LDS), rc = c~ - A~^T y0:
-            // x_hat = x0 + max(u - tau (rc - A~^T v), -x0)
-            const Acc s = row_dot4<Acc>(a.at_vs, a.at_cl, yL, b0, b1);
+        // the primal and the dual step of plain_iterations, with the sums'
+        // entries stored by column and row
+        const int et = opaque(tid);
+        for (int p = et; p < n; p += BS) {
+            const int g = c0 + p, j = I.column(p);
+            const double u = (double)a.x[g], x0 = (double)a.x0[g], rc = (double)a.ct[g];
+            const Acc s = side_dot<Acc>(I.AT, lds, yL, p, RS::RC * BS, RS::KC);
             double uh = u - tau * (rc - (double)s);
             uh = uh < -x0 ? -x0 : uh;
-            xbL[j] = (T)(2.0 * uh - u);  // x_bar - x0
+            xbL[p] = (T)(2.0 * uh - u);
             a.x[g] = (T)(w * (opr * uh - rho * u));
-            if (first || is_eval) {
-                const double d = u - uh;
-                q[0] += d * d;
-            }
+            a.pu[j] = u - uh;
             if (is_eval) {
-                q[1] += uh * uh;
+                a.rdo[j] = uh;
                 const double xh = x0 + uh;
                 a.xhat[g] = (T)xh;
-                a.xo[g] = a.d_col[g] * xh;
+                a.xo[j] = a.d_col[j] * xh;
             }
         }
         __syncthreads();
-        // dual step over the rows of A, with the same prefetch
-        int mb0 = 0, mb1 = 0;
-        T mbt = 0;
-        if (m > 0) {
-            const int g = r0 + min(tid, m - 1);
-            mb0 = a.a_rowptr[g];
-            mb1 = a.a_rowptr[g + 1];
-            mbt = a.bt[g];
-        }
-        for (int i = tid; i < m; i += BS) {
-            const int g = r0 + i;
-            const int b0 = mb0, b1 = mb1;
-            const double rb = (double)mbt;
-            {
-                const int gn = r0 + min(i + BS, m - 1);
-                mb0 = a.a_rowptr[gn];
-                mb1 = a.a_rowptr[gn + 1];
-                mbt = a.bt[gn];
-            }
-            // rb = b~ - A~ x0: y_hat = y0 + v + sigma (rb - A~ (x_bar - x0))
-            const Acc s = row_dot4<Acc>(a.a_vs, a.a_cl, xbL, b0, b1);
-            const double v = (double)yL[i];
+        for (int p = et; p < m; p += BS) {
+            const int g = r0 + p, i = I.row(p);
+            const double rb = (double)a.bt[g];
+            const Acc s = side_dot<Acc>(I.A, lds, xbL, p, RS::RR * BS, RS::KR);
+            const double v = (double)yL[p];
             const double vh = v + sig * (rb - (double)s);
-            yL[i] = (T)(w * (opr * vh - rho * v));
-            if (first || is_eval) {
-                const double d = v - vh;
-                q[2] += d * d;
-            }
+            yL[p] = (T)(w * (opr * vh - rho * v));
+            a.pav[i] = v - vh;
             if (is_eval) {
-                q[3] += vh * vh;
+                a.rpo[i] = vh;
                 const double yh = (double)a.y0[g] + vh;
                 a.yhat[g] = (T)yh;
-                a.yo[g] = a.d_row[g] * yh;
+                a.yo[i] = a.d_row[i] * yh;
             }
         }
         __syncthreads();
-        if (!(first || is_eval)) {
-            ++k;
-            continue;
-        }
-        wg_reduce<4, 0, BS>(q, nomax, sh);
-        if (first) R0 = sqrt(omega * q[0] + q[2] / omega);
+        double qx[2], qy[2];  // ||u - uh||^2, ||uh||^2 and the same of v
+        inst_sums<BS, 2>(n, sh, qx, [&](int j, double(&s)[2]) {
+            const double d = a.pu[c0 + j];
+            s[0] += d * d;
+            if (is_eval) {
+                const double e = a.rdo[c0 + j];
+                s[1] += e * e;
+            }
+        });
+        inst_sums<BS, 2>(m, sh, qy, [&](int i, double(&s)[2]) {
+            const double d = a.pav[r0 + i];
+            s[0] += d * d;
+            if (is_eval) {
+                const double e = a.rpo[r0 + i];
+                s[1] += e * e;
+            }
+        });
+        if (first) R0 = uniform(sqrt(omega * qx[0] + qy[0] / omega));
         ++k;
         if (!is_eval) continue;
-        const double R = sqrt(omega * q[0] + q[2] / omega);
+        const double R = uniform(sqrt(omega * qx[0] + qy[0] / omega));
         // evaluation on the original block, float64
-        double ev[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, evm[2] = {0.0, 0.0};
-        for (int i = tid; i < m; i += BS) {
+        double rp_inf = 0.0, rd_inf = 0.0;
+        for (int i = et; i < m; i += BS) {
             const int g = r0 + i;
-            double s = 0.0;
-            for (int kz = a.a_rowptr[g]; kz < a.a_rowptr[g + 1]; ++kz) s += a.a_val[kz] * a.xo[a.a_col[kz]];
-            const double rp = a.b[g] - s;
+            const double rp = a.M.b[g] - row_f64<0>(a.M.a_val, a.M.a_col, a.xo, arp[i], arp[i + 1]);
             a.rpo[g] = rp;
-            ev[0] += rp * rp;
-            ev[1] += a.b[g] * a.yo[g];
-            evm[0] = fmax(evm[0], fabs(rp));
+            rp_inf = fmax(rp_inf, fabs(rp));
         }
-        for (int j = tid; j < n; j += BS) {
+        for (int j = et; j < n; j += BS) {
             const int g = c0 + j;
-            double s = 0.0;
-            for (int kz = a.at_rowptr[g]; kz < a.at_rowptr[g + 1]; ++kz) s += a.at_val[kz] * a.yo[a.at_col[kz]];
-            const double gg = a.c[g] - s;
+            const double gg = a.M.c[g] - row_f64<0>(a.M.at_val, a.M.at_col, a.yo, trp[j], trp[j + 1]);
             const double z = gg > 0.0 ? gg : 0.0;
             const double rd = gg - z;
             a.zo[g] = z;
             a.rdo[g] = rd;
-            const double xv = a.xo[g];
-            ev[2] += rd * rd;
-            ev[3] += a.c[g] * xv;
-            ev[4] += xv * z;
-            evm[1] = fmax(evm[1], fabs(rd));
+            rd_inf = fmax(rd_inf, fabs(rd));
         }
-        wg_reduce<5, 2, BS>(ev, evm, sh);
-        const double rp = sqrt(ev[0]), rd = sqrt(ev[2]), pobj = ev[3], dobj = ev[1];
+        rp_inf = inst_max<BS>(rp_inf, sh);
+        rd_inf = inst_max<BS>(rd_inf, sh);
+        double ep[2], ed[3];
+        inst_sums<BS, 2>(m, sh, ep, [&](int i, double(&s)[2]) {
+            const double rp = a.rpo[r0 + i];
+            s[0] += rp * rp;
+            s[1] += a.M.b[r0 + i] * a.yo[r0 + i];
+        });
+        inst_sums<BS, 3>(n, sh, ed, [&](int j, double(&s)[3]) {
+            const double rd = a.rdo[c0 + j], xv = a.xo[c0 + j];
+            s[0] += rd * rd;
+            s[1] += a.M.c[c0 + j] * xv;
+            s[2] += xv * a.zo[c0 + j];
+        });
+        const double rp = sqrt(ep[0]), rd = sqrt(ed[0]), pobj = ed[1], dobj = ep[1];
         const double gap = fabs(pobj - dobj);
-        if (!(isfinite(ev[0]) && isfinite(ev[2]) && isfinite(pobj) && isfinite(dobj))) status = MIPDHG_NUMERICAL;
+        if (!(isfinite(ep[0]) && isfinite(ed[0]) && isfinite(pobj) && isfinite(dobj))) status = MIPDHG_NUMERICAL;
         else if (rp <= tol_p && rd <= tol_d && gap <= eps * (1.0 + fabs(pobj) + fabs(dobj)))
             status = MIPDHG_OPTIMAL;
         else if (t >= a.max_iter) status = MIPDHG_ITER_LIMIT;
         if (tid == 0) {  // the latest evaluation's measures
             BInst& r = a.info[inst];
-            r.rp2 = ev[0];
-            r.rd2 = ev[2];
-            r.pobj = ev[3];
-            r.dobj = ev[1];
-            r.xz = ev[4];
-            r.rp_inf = evm[0];
-            r.rd_inf = evm[1];
+            r.rp2 = ep[0];
+            r.rd2 = ed[0];
+            r.pobj = pobj;
+            r.dobj = dobj;
+            r.xz = ed[2];
+            r.rp_inf = rp_inf;
+            r.rd_inf = rd_inf;
         }
         if (status >= 0) break;
         bool restart = false;
         if (a.restarts)
             restart = (R <= a.beta_suff * R0) || (R <= a.beta_nec * R0 && R > R_prev) ||
                       ((double)k >= a.beta_art * (double)t);
+        to_eval = E;
+        if (a.max_iter - t < to_eval) to_eval = (int)(a.max_iter - t);
         if (restart) {
-            const double dx = sqrt(q[1]), dy = sqrt(q[3]);
+            const double dx = sqrt(qx[1]), dy = sqrt(qy[1]);
             if (dx > 1e-10 && dy > 1e-10) {
-                omega = exp(a.theta * log(dy / dx) + (1.0 - a.theta) * log(omega));
-                tau = eta / omega;
-                sig = eta * omega;
+                omega = uniform(exp(a.theta * log(dy / dx) + (1.0 - a.theta) * log(omega)));
+                tau = uniform(eta / omega);
+                sig = uniform(eta * omega);
             }
             // the anchor moves to (x_hat, y_hat), the state to 0, and the new
             // anchor's residuals are formed in float64 on the caller's
             // matrix: rb = D_r (b - A D_c x0), rc = D_c (c - A^T D_r y0)
-            for (int j = tid; j < n; j += BS) {
-                a.x0[c0 + j] = a.xhat[c0 + j];
-                a.x[c0 + j] = (T)0;
+            // (pu, pav: D_c x0 and D_r y0)
+            for (int p = et; p < n; p += BS) {
+                const T v = a.xhat[c0 + p];
+                a.x0[c0 + p] = v;
+                a.x[c0 + p] = (T)0;
+                const int j = I.column(p);
+                a.pu[j] = a.d_col[j] * (double)v;
             }
-            for (int i = tid; i < m; i += BS) {
-                a.y0[r0 + i] = a.yhat[r0 + i];
-                yL[i] = (T)0;
+            for (int p = et; p < m; p += BS) {
+                const T v = a.yhat[r0 + p];
+                a.y0[r0 + p] = v;
+                yL[p] = (T)0;
+                const int i = I.row(p);
+                a.pav[i] = a.d_row[i] * (double)v;
             }
             __syncthreads();
-            for (int i = tid; i < m; i += BS) {
-                const int g = r0 + i;
-                double sa = 0.0;
-                for (int kz = a.a_rowptr[g]; kz < a.a_rowptr[g + 1]; ++kz) {
-                    const int jc = a.a_col[kz];
-                    sa += a.a_val[kz] * (a.d_col[jc] * (double)a.x0[jc]);
-                }
-                a.bt[g] = (T)(a.d_row[g] * (a.b[g] - sa));
+            for (int p = et; p < m; p += BS) {
+                const int g = I.row(p), i = g - r0;
+                const double sa = row_f64<0>(a.M.a_val, a.M.a_col, a.pu, arp[i], arp[i + 1]);
+                a.bt[r0 + p] = (T)(a.d_row[g] * (a.M.b[g] - sa));
             }
-            for (int j = tid; j < n; j += BS) {
-                const int g = c0 + j;
-                double sa = 0.0;
-                for (int kz = a.at_rowptr[g]; kz < a.at_rowptr[g + 1]; ++kz) {
-                    const int ir = a.at_col[kz];
-                    sa += a.at_val[kz] * (a.d_row[ir] * (double)a.y0[ir]);
-                }
-                a.ct[g] = (T)(a.d_col[g] * (a.c[g] - sa));
+            for (int p = et; p < n; p += BS) {
+                const int g = I.column(p), j = g - c0;
+                const double sa = row_f64<0>(a.M.at_val, a.M.at_col, a.pav, trp[j], trp[j + 1]);
+                a.ct[c0 + p] = (T)(a.d_col[g] * (a.M.c[g] - sa));
             }
             k = 0;
             R_prev = INFINITY;
@@ -342,7 +397,7 @@ __device__ void solve_instance(const BArgs<T, V>& a, int inst, T* yL, T* xbL, do
         }
     }
     if (suspended) {
-        for (int i = tid; i < m; i += BS) a.ysave[r0 + i] = yL[i];
+        for (int p = tid; p < m; p += BS) a.ysave[r0 + p] = yL[p];
         status = MIPDHG_IN_PROGRESS;
     }
     if (tid == 0) {
@@ -364,24 +419,24 @@ __device__ void solve_instance(const BArgs<T, V>& a, int inst, T* yL, T* xbL, do
     __syncthreads();
 }
 
-// Workgroup size of the split's launch of large instances: twice the
-// threads on each instance's rows and columns.
-constexpr int kBatchWide = 512;
-
-template <typename T, typename V, typename Acc, int BS>
-__global__ __launch_bounds__(BS) void k_batched(BArgs<T, V> a) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    T* yL = (T*)smem;
-    T* xbL = yL + a.lds_m;
-    __shared__ double sh[8 * (BS / kWave)];
+// Four waves to a SIMD in every class of launch: at most 128 registers.  The
+// set-up is a launch of its own, so that its code takes no registers from the
+// iterations.
+template <typename T, typename V, typename Acc, int BS, bool SETUP>
+__global__ __launch_bounds__(BS, 4) void k_batched(BArgs<T, V> a) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    __shared__ double sh[BS / kWave > 12 ? BS / kWave : 12];
     __shared__ int next;
     while (true) {
-        if (threadIdx.x == 0) next = atomicAdd(a.counter, 1);
+        if (threadIdx.x == 0) next = atomicAdd(a.counter + (SETUP ? 0 : kClasses), 1);
         __syncthreads();
         const int qi = __builtin_amdgcn_readfirstlane(next);  // uniform: scalar loads of the offsets
         __syncthreads();
         if (qi >= a.B) break;  // uniform: every wave leaves once the queue is empty
-        solve_instance<T, V, Acc, BS>(a, a.order[qi], yL, xbL, sh);
+        const int inst = __builtin_amdgcn_readfirstlane(a.order[qi]);
+        if constexpr (SETUP) setup_instance<T, V, BS>(a, inst, lds, sh);
+        else solve_instance<T, V, Acc, BS>(a, inst, lds, sh);
+        __syncthreads();  // the next instance takes over the LDS
     }
 }
 
@@ -452,7 +507,7 @@ struct BatchWs {
     BState* state;
     double *d_row, *d_col, *pu, *pav, *partials, *red, *eps;
     void *a_vs, *at_vs, *x, *x0, *xhat, *ct, *y0, *yhat, *bt, *ysave;
-    uint16_t *a_cl, *at_cl;
+    uint16_t *a_cl, *at_cl, *perm_r, *perm_c;
     size_t bytes;
 };
 
@@ -482,6 +537,8 @@ static BatchWs carve_batch(void* base, size_t cap, int64_t B, int64_t m, int64_t
     w.at_vs = cv.take<char>(nnz * vs);
     w.a_cl = cv.take<uint16_t>(nnz);
     w.at_cl = cv.take<uint16_t>(nnz);
+    w.perm_r = cv.take<uint16_t>(m);
+    w.perm_c = cv.take<uint16_t>(n);
     w.x = cv.take<char>(n * ts);
     w.x0 = cv.take<char>(n * ts);
     w.xhat = cv.take<char>(n * ts);
@@ -540,6 +597,40 @@ static int lds_bytes_for(int max_m, int max_n, size_t ts) {
     return (int)(((size_t)max_m + (size_t)max_n) * ts + 16);
 }
 
+// Launch classes: workgroups of kClassBs threads.  An instance's results do
+// not depend on its class.  With more instances than compute units the class
+// follows from the LDS the instance needs with both matrices in it, so that
+// every class keeps 16 waves on a compute unit: up to a sixteenth of its LDS
+// one wave, up to a quarter 256 threads, up to a half 512, else 1,024 threads
+// and the whole LDS, from which the matrices' last levels are left out when
+// they do not fit.  With no more instances than compute units nothing is
+// gained by leaving room for others: about one thread per column.
+// Measured on 4,096 LPs of 20 to 2,000 rows, 2.5 times the columns, 4 entries
+// a column (FP32, 256 iterations, call with its host part): one launch of 256
+// threads sized by the largest instance, the matrices in L2, 32.3 ms; these
+// classes 22.9 ms.  48 LPs of 20 to 500 rows in FP64: 256 threads each 2.37
+// ms, by the columns 1.56 ms.
+constexpr int kClassBs[kClasses] = {1024, 512, 256, 64};
+constexpr int kClassLds[kClasses] = {162000, 81000, 40400, 9700};  // shares of 160 KB, less the static part
+
+// One class's launches: as many workgroups as fit, never more than instances
+template <typename T, typename V, typename Acc, int BS>
+static int launch_class(const BArgs<T, V>& a, int cus, hipStream_t s) {
+    auto* ks = k_batched<T, V, Acc, BS, true>;
+    auto* k = k_batched<T, V, Acc, BS, false>;
+    // (the largest class's bytes whatever this launch's: the attribute is the process's)
+    MIP_HIP(hipFuncSetAttribute((const void*)ks, hipFuncAttributeMaxDynamicSharedMemorySize, kClassLds[0]));
+    MIP_HIP(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, kClassLds[0]));
+    int per_cu = 1;
+    MIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, BS, a.lds));
+    const int grid = std::max(1, std::min(a.B, cus * std::max(per_cu, 1)));
+    if (!a.resume)
+        hipLaunchKernelGGL((k_batched<T, V, Acc, BS, true>), dim3(grid), dim3(BS), a.lds, s, a);
+    hipLaunchKernelGGL((k_batched<T, V, Acc, BS, false>), dim3(grid), dim3(BS), a.lds, s, a);
+    MIP_LAUNCH_CHECK();
+    return 0;
+}
+
 template <typename T, typename V, typename Acc>
 static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const double* eps, void* ws, size_t ws_bytes,
                         hipStream_t stream, double* x, double* y, double* z, double* r_p, double* r_d,
@@ -584,28 +675,40 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
     for (int i = 0; i <= B; ++i)
         if (rpa[bt.row_off[i]] != bt.nnz_off[i] || rpat[bt.col_off[i]] != bt.nnz_off[i])
             return set_error("nnz_off does not match the row pointers at instance %d", i), MIPDHG_ERR_BAD_CSR;
-    // largest instances first; with a split, the instances whose vectors
-    // need more than batch_split bytes come first in the order array (the
-    // wide launch), each class largest first
+    int dev = 0, cus = 256;
+    MIP_HIP(hipGetDevice(&dev));
+    MIP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    // the classes' instances one after the other in the order array, each
+    // class largest first; batch_split sends the instances whose vectors fit
+    // its bytes to 256 threads and the others to 1,024
+    std::vector<uint8_t> cls(B);
+    int cl_count[kClasses] = {0, 0, 0, 0}, cl_lds[kClasses] = {0, 0, 0, 0};
+    for (int i = 0; i < B; ++i) {
+        const int mi = bt.row_off[i + 1] - bt.row_off[i], ni = bt.col_off[i + 1] - bt.col_off[i];
+        const int64_t zi = bt.nnz_off[i + 1] - bt.nnz_off[i];
+        auto full = [&](int k) {  // LDS that holds all of it beside the registers of class k's threads
+            typedef RegShape<V> RS;
+            const int64_t zc = zi / std::max(ni, 1), zr = zi / std::max(mi, 1);
+            const int64_t nreg = std::min(ni, RS::RC * kClassBs[k]) * std::min<int64_t>(zc, RS::KC) +
+                                 std::min(mi, RS::RR * kClassBs[k]) * std::min<int64_t>(zr, RS::KR);
+            return inst_full_bytes(mi, ni, zi, sizeof(T), sizeof(V), nreg);
+        };
+        int c;
+        if (o.batch_split > 0) c = lds_bytes_for(mi, ni, sizeof(T)) <= o.batch_split ? 2 : 0;
+        else if (B <= cus) c = ni <= 64 ? 3 : ni <= 512 ? 2 : ni <= 1024 ? 1 : 0;
+        else c = full(3) <= kClassLds[3] ? 3 : full(2) <= kClassLds[2] ? 2 : full(1) <= kClassLds[1] ? 1 : 0;
+        const int64_t cap = B <= cus && o.batch_split == 0 ? kClassLds[0] : kClassLds[c];
+        const int need = (int)std::max<int64_t>(inst_vec_bytes(mi, ni, sizeof(T)), std::min(full(c), cap));
+        cls[i] = (uint8_t)c;
+        ++cl_count[c];
+        cl_lds[c] = std::max(cl_lds[c], need);
+    }
     std::vector<int32_t> order(B);
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int p, int q) {
+        if (cls[p] != cls[q]) return cls[p] < cls[q];
         return bt.nnz_off[p + 1] - bt.nnz_off[p] > bt.nnz_off[q + 1] - bt.nnz_off[q];
     });
-    auto inst_lds = [&](int i) {
-        return lds_bytes_for(bt.row_off[i + 1] - bt.row_off[i], bt.col_off[i + 1] - bt.col_off[i], sizeof(T));
-    };
-    int n_big = B, sm_m = 0, sm_n = 0;  // the wide launch's instance count; the narrow one's largest sizes
-    if (o.batch_split > 0) {
-        std::stable_partition(order.begin(), order.end(), [&](int i) { return inst_lds(i) > o.batch_split; });
-        n_big = 0;
-        for (int i : order)
-            if (inst_lds(i) > o.batch_split) ++n_big;
-        for (int k = n_big; k < B; ++k) {
-            sm_m = std::max(sm_m, bt.row_off[order[k] + 1] - bt.row_off[order[k]]);
-            sm_n = std::max(sm_n, bt.col_off[order[k] + 1] - bt.col_off[order[k]]);
-        }
-    }
     MIP_HIP(hipMemcpyAsync(w.hdr, hdr_running, sizeof(hdr_running), hipMemcpyHostToDevice, stream));
     MIP_HIP(hipMemcpyAsync(w.order, order.data(), B * 4, hipMemcpyHostToDevice, stream));
     MIP_HIP(hipMemcpyAsync(w.row_off, bt.row_off, (B + 1) * 4, hipMemcpyHostToDevice, stream));
@@ -617,23 +720,12 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
         return rc;
     BArgs<T, V> a;
     a.B = B;
-    a.lds_m = max_m;
-    a.lds_n = max_n;
+    a.lds = 0;
     a.order = w.order;
     a.row_off = w.row_off;
     a.col_off = w.col_off;
-    a.a_rowptr = lp.a_rowptr;
-    a.a_col = lp.a_col;
-    a.a_val = lp.a_val;
-    a.at_rowptr = lp.at_rowptr;
-    a.at_col = lp.at_col;
-    a.at_val = lp.at_val;
-    a.b = lp.b;
-    a.c = lp.c;
-    a.a_vs = (V*)w.a_vs;
-    a.at_vs = (V*)w.at_vs;
-    a.a_cl = w.a_cl;
-    a.at_cl = w.at_cl;
+    a.M = InstMat{lp.a_rowptr, lp.a_col, lp.a_val, lp.at_rowptr, lp.at_col, lp.at_val, lp.b, lp.c};
+    a.S = InstStore<V>{(V*)w.a_vs, (V*)w.at_vs, w.a_cl, w.at_cl, w.perm_r, w.perm_c};
     a.x = (T*)w.x;
     a.x0 = (T*)w.x0;
     a.xhat = (T*)w.xhat;
@@ -670,92 +762,69 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
     a.eval_every = o.eval_every;
     a.halpern = o.halpern;
     a.restarts = o.restarts;
-    // persistent grids: as many workgroups as fit, never more than instances
-    int dev = 0, cus = 256;
-    MIP_HIP(hipGetDevice(&dev));
-    MIP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    auto* k_narrow = k_batched<T, V, Acc, kBatchBlock>;
-    auto* k_wide = k_batched<T, V, Acc, kBatchWide>;
-    MIP_HIP(hipFuncSetAttribute((const void*)k_narrow, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-    MIP_HIP(hipFuncSetAttribute((const void*)k_wide, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-    auto grid_for_lds = [&](bool wide, int bytes, int count, int* g) {
-        int per_cu = 1;
-        if (wide) MIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_wide, kBatchWide, bytes));
-        else MIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_narrow, kBatchBlock, bytes));
-        *g = std::max(1, std::min(count, cus * std::max(per_cu, 1)));
-        return 0;
-    };
+    // one persistent launch per class with instances, all at once: the first
+    // on the caller's stream, the others on side streams joined to it
+    // (neither waits on another; each takes the compute units the others
+    // leave)
+    struct Sides {
+        hipStream_t s[kClasses] = {};
+        hipEvent_t fork = nullptr, join[kClasses] = {};
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        ~Sides() {
+            for (int c = 0; c < kClasses; ++c) {
+                if (s[c]) {
+                    (void)hipStreamSynchronize(s[c]);
+                    (void)hipStreamDestroy(s[c]);
+                }
+                if (join[c]) (void)hipEventDestroy(join[c]);
+            }
+            if (fork) (void)hipEventDestroy(fork);
+            if (e0) (void)hipEventDestroy(e0);
+            if (e1) (void)hipEventDestroy(e1);
+        }
+    } side;
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, stream, w.counter, 64);
     const auto t1 = clk::now();
-    hipEvent_t e0, e1;
-    MIP_HIP(hipEventCreate(&e0));
-    MIP_HIP(hipEventCreate(&e1));
+    MIP_HIP(hipEventCreate(&side.e0));
+    MIP_HIP(hipEventCreate(&side.e1));
+    const hipEvent_t e0 = side.e0, e1 = side.e1;
     MIP_HIP(hipEventRecord(e0, stream));
-    if (o.batch_split == 0) {
-        int grid = 1;
-        if ((rc = grid_for_lds(false, lds, B, &grid))) return rc;
-        hipLaunchKernelGGL((k_batched<T, V, Acc, kBatchBlock>), dim3(grid), dim3(kBatchBlock), lds, stream, a);
-        MIP_LAUNCH_CHECK();
-    } else {
-        // the small instances on a side stream at their occupancy, the others
-        // (if any) on the caller's stream in wide workgroups at the largest
-        // instance's occupancy; both persistent launches run at once and share
-        // the CUs
-        struct Side {
-            hipStream_t s = nullptr;
-            hipEvent_t fork = nullptr, join = nullptr;
-            ~Side() {
-                if (fork) (void)hipEventDestroy(fork);
-                if (join) (void)hipEventDestroy(join);
-                if (s) (void)hipStreamDestroy(s);
+    int first = -1, begin = 0;
+    for (int c = 0; c < kClasses; ++c) {
+        if (!cl_count[c]) continue;
+        hipStream_t cs = stream;
+        if (first < 0) {
+            first = c;
+            if (cl_count[c] < B) {
+                MIP_HIP(hipEventCreateWithFlags(&side.fork, hipEventDisableTiming));
+                MIP_HIP(hipEventRecord(side.fork, stream));
             }
-        } side;
-        MIP_HIP(hipStreamCreateWithFlags(&side.s, hipStreamNonBlocking));
-        MIP_HIP(hipEventCreateWithFlags(&side.fork, hipEventDisableTiming));
-        MIP_HIP(hipEventCreateWithFlags(&side.join, hipEventDisableTiming));
-        MIP_HIP(hipEventRecord(side.fork, stream));
-        MIP_HIP(hipStreamWaitEvent(side.s, side.fork, 0));
-        BArgs<T, V> as = a;
-        as.B = B - n_big;
-        as.order = w.order + n_big;
-        as.counter = w.counter + 1;
-        as.lds_m = sm_m;
-        as.lds_n = sm_n;
-        const int lds_sm = lds_bytes_for(sm_m, sm_n, sizeof(T));
-        // grids sized to be resident together: at most one wide workgroup
-        // per CU, the narrow launch in what that leaves of the CU's threads
-        // and LDS (neither launch waits on the other, so this is for speed
-        // only)
-        int max_thr = 2048, cu_lds = 160 * 1024;
-        MIP_HIP(hipDeviceGetAttribute(&max_thr, hipDeviceAttributeMaxThreadsPerMultiProcessor, dev));
-        MIP_HIP(hipDeviceGetAttribute(&cu_lds, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev));
-        const bool shared = n_big > 0 && as.B > 0;
-        if (n_big > 0) {
-            BArgs<T, V> ab = a;
-            ab.B = n_big;
-            int grid = 1;
-            if ((rc = grid_for_lds(true, lds, n_big, &grid))) return rc;
-            if (shared) grid = std::min(grid, cus);
-            hipLaunchKernelGGL((k_batched<T, V, Acc, kBatchWide>), dim3(grid), dim3(kBatchWide), lds, stream, ab);
-            MIP_LAUNCH_CHECK();
+        } else {
+            MIP_HIP(hipStreamCreateWithFlags(&side.s[c], hipStreamNonBlocking));
+            MIP_HIP(hipEventCreateWithFlags(&side.join[c], hipEventDisableTiming));
+            cs = side.s[c];
+            MIP_HIP(hipStreamWaitEvent(cs, side.fork, 0));
         }
-        if (as.B > 0) {
-            int grid = 1;
-            if ((rc = grid_for_lds(false, lds_sm, as.B, &grid))) return rc;
-            if (shared) {
-                const int by_thr = (max_thr - kBatchWide) / kBatchBlock;
-                const int by_lds = lds_sm > 0 ? (cu_lds - lds) / lds_sm : by_thr;
-                const int per_cu = std::max(1, std::min(grid / std::max(cus, 1), std::min(by_thr, by_lds)));
-                grid = std::max(1, std::min(as.B, cus * per_cu));
-            }
-            hipLaunchKernelGGL((k_batched<T, V, Acc, kBatchBlock>), dim3(grid), dim3(kBatchBlock), lds_sm, side.s,
-                               as);
-            MIP_LAUNCH_CHECK();
+        BArgs<T, V> ac = a;
+        ac.B = cl_count[c];
+        ac.order = w.order + begin;
+        ac.counter = w.counter + c;
+        ac.lds = cl_lds[c];
+        begin += cl_count[c];
+        if (c == 0) rc = launch_class<T, V, Acc, kClassBs[0]>(ac, cus, cs);
+        else if (c == 1) rc = launch_class<T, V, Acc, kClassBs[1]>(ac, cus, cs);
+        else if (c == 2) rc = launch_class<T, V, Acc, kClassBs[2]>(ac, cus, cs);
+        else rc = launch_class<T, V, Acc, kClassBs[3]>(ac, cus, cs);
+        if (rc) {
+            (void)hipStreamSynchronize(stream);
+            return rc;
         }
-        MIP_HIP(hipEventRecord(side.join, side.s));
-        MIP_HIP(hipStreamWaitEvent(stream, side.join, 0));
-        MIP_HIP(hipStreamSynchronize(side.s));
     }
+    for (int c = 0; c < kClasses; ++c)
+        if (side.s[c]) {
+            MIP_HIP(hipEventRecord(side.join[c], side.s[c]));
+            MIP_HIP(hipStreamWaitEvent(stream, side.join[c], 0));
+        }
     MIP_HIP(hipEventRecord(e1, stream));
     MIP_HIP(hipMemcpyAsync(w.hdr, hdr_done, sizeof(hdr_done), hipMemcpyHostToDevice, stream));
     std::vector<BInst> res(B);
@@ -763,8 +832,6 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
     MIP_HIP(hipStreamSynchronize(stream));
     float kms = 0.f;
     MIP_HIP(hipEventElapsedTime(&kms, e0, e1));
-    (void)hipEventDestroy(e0);
-    (void)hipEventDestroy(e1);
     const auto t2 = clk::now();
     int worst = MIPDHG_OPTIMAL;
     for (int i = 0; i < B; ++i) worst = std::max(worst, res[i].status);

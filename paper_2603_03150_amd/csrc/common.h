@@ -124,6 +124,43 @@ __device__ __forceinline__ T group_sum(T v) {
     return v;
 }
 
+// group_sum<64> of a double without the shuffles' trips through LDS: the
+// halves and rows are exchanged by lane swaps, and once a sum depends on the
+// lane modulo 2 k only, a rotation of a row by k lanes is the butterfly's
+// exchange.  The same additions in the same order.
+__device__ __forceinline__ double wave_sum(double v) {
+    union U {
+        double d;
+        uint32_t i[2];
+    };
+    U a, b;
+    a.d = v;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const auto r = __builtin_amdgcn_permlane32_swap(a.i[h], a.i[h], false, false);
+        a.i[h] = r[0];
+        b.i[h] = r[1];
+    }
+    a.d = a.d + b.d;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const auto r = __builtin_amdgcn_permlane16_swap(a.i[h], a.i[h], false, false);
+        a.i[h] = r[0];
+        b.i[h] = r[1];
+    }
+    a.d = a.d + b.d;
+#define MIP_ROT_ADD(K)                                                                       \
+    b.i[0] = __builtin_amdgcn_update_dpp(0u, a.i[0], 0x120 + K, 0xf, 0xf, false);            \
+    b.i[1] = __builtin_amdgcn_update_dpp(0u, a.i[1], 0x120 + K, 0xf, 0xf, false);            \
+    a.d = a.d + b.d;
+    MIP_ROT_ADD(8)
+    MIP_ROT_ADD(4)
+    MIP_ROT_ADD(2)
+    MIP_ROT_ADD(1)
+#undef MIP_ROT_ADD
+    return a.d;
+}
+
 template <typename T>
 __device__ __forceinline__ T group_sum_rt(T v, int L) {
     for (int o = L / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, L);

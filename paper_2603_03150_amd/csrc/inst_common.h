@@ -1,6 +1,7 @@
-// Per-instance pieces shared by the batched solve and the unrolled map: a
-// fixed-order workgroup reduction and the instance set-up (norms, scaling,
-// scaled values, power iteration, step and initial primal weight).
+// Per-instance pieces shared by the batched solve and the unrolled map: the
+// instance's scaled matrices laid out for one workgroup, fixed-order sums, and
+// the instance set-up (norms, scaling, scaled values, power iteration, step
+// and initial primal weight).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -32,44 +33,326 @@ __device__ __forceinline__ Acc row_dot4(const V* vals, const uint16_t* cols, con
     return acc;
 }
 
+// The same on the caller's float64 matrix and a float64 vector, the first of
+// its entries being column c0's; MODE 0: sum of a x, 1: sum of |a| x, 2:
+// maximum of |a| x.
+template <int MODE>
+__device__ __forceinline__ double row_f64(const double* vals, const int32_t* cols, const double* x, int s, int e,
+                                          int c0 = 0) {
+    double acc = 0.0;
+    for (int k = s; k < e; k += 4) {
+        double v[4], g[4];
+        int c[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int kk = min(k + q, e - 1);
+            c[q] = cols[kk];
+            v[q] = vals[kk];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g[q] = x[c[q] - c0];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (k + q >= e) continue;
+            if (MODE == 0) acc += v[q] * g[q];
+            else if (MODE == 1) acc += fabs(v[q]) * g[q];
+            else acc = fmax(acc, fabs(v[q]) * g[q]);
+        }
+    }
+    return acc;
+}
+
 // Largest instance dimension the 16-bit local columns address.
 constexpr int kInstMaxDim = 65535;
 
-constexpr int kBatchBlock = 256;
+// Limits of the level layout: rows and columns that the set-up sorts in LDS,
+// and the longest row (a level offset each).  (Byte offsets into a vector of
+// doubles and its extra entry fit 16 bits.)
+constexpr int kLevelMaxDim = 8190;
+constexpr int kLevelMaxLen = 1024;
 
-// Fixed-order workgroup sums (NS) and maxima (NM) over a workgroup of BS
-// threads; every thread gets the result.  sh holds (NS + NM) * BS / 64 doubles.
-template <int NS, int NM, int BS = kBatchBlock>
-__device__ __forceinline__ void wg_reduce(double (&s)[NS > 0 ? NS : 1], double (&mx)[NM > 0 ? NM : 1],
-                                          double* sh) {
-    constexpr int NW = BS / kWave;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+// One scaled matrix of an instance.  In the level layout the rows are taken
+// in the order of decreasing length ("positions"; equal lengths keep their
+// order) and the entries are stored level by level: level k holds the k-th
+// entry of every row longer than k, which are the first positions, so entry
+// (p, k) is at kp[k] + p.  The lanes of a wave, on consecutive positions, read
+// consecutive values and columns whatever the row lengths, with no padding,
+// and every row is still summed in its own order.  The vectors of an instance
+// (and the columns stored here) are by position too.  Thread t holds the
+// first K entries of the rows at positions t, t + BS, ... (R of them) in
+// registers for good (RegSide); the rest of the first K0 levels lies in LDS
+// (entry (p, k) at kl[k] + p), the other levels are streamed from the
+// workspace.  An instance beyond the limits above keeps CSR order
+// (levels == false, positions = rows).  Offsets are bytes in the workgroup's
+// dynamic LDS.
+template <typename V>
+struct Side {
+    bool levels;
+    int K0;
+    int o_kp, o_kl, o_len, o_val, o_col;
+    const V* val;           // the instance's entries in the workspace
+    const uint16_t* col;
+    const int32_t* rowptr;  // of the instance's first row (CSR order)
+    int z0;                 // first entry of the instance
+};
+
+typedef int32_t ii2 __attribute__((ext_vector_type(2)));
+
+// acc + the terms of position p from level k on (k even); len: its row's length
+template <typename Acc, typename V, typename X>
+__device__ __forceinline__ Acc side_rest(const Side<V>& s, const unsigned char* lds, const X* xl, int p, int len, int k,
+                                         Acc acc) {
+    const uint32_t* kp = (const uint32_t*)(lds + s.o_kp);
+    const int32_t* kl = (const int32_t*)(lds + s.o_kl);
+    const V* lv = (const V*)(lds + s.o_val);
+    const uint16_t* lc = (const uint16_t*)(lds + s.o_col);
+    const int kr = min(len, s.K0);
+    for (; k + 4 <= kr; k += 4) {
+        const ii2 oa = *(const ii2*)(kl + k), ob = *(const ii2*)(kl + k + 2);
+        const int o[4] = {oa[0], oa[1], ob[0], ob[1]};
+        int c[4];
+        Acc v[4];
 #pragma unroll
-    for (int q = 0; q < NS; ++q) {
-        const double v = group_sum<kWave>(s[q]);
-        if (lane == 0) sh[q * NW + wave] = v;
+        for (int q = 0; q < 4; ++q) {
+            c[q] = lc[o[q] + p];
+            v[q] = (Acc)ld_val_cached(lv, o[q] + p);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc += v[q] * (Acc)xl[c[q]];
     }
-#pragma unroll
-    for (int q = 0; q < NM; ++q) {
-        double v = mx[q];
-#pragma unroll
-        for (int o = kWave / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
-        if (lane == 0) sh[(NS + q) * NW + wave] = v;
+    for (; k < kr; ++k) {
+        const int e = kl[k] + p;
+        acc += (Acc)ld_val_cached(lv, e) * (Acc)xl[lc[e]];
     }
+    for (; k + 4 <= len; k += 4) {
+        int c[4];
+        Acc v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int e = (int)kp[k + q] + p;
+            c[q] = s.col[e];
+            v[q] = (Acc)ld_val_cached(s.val, e);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc += v[q] * (Acc)xl[c[q]];
+    }
+    for (; k < len; ++k) {
+        const int e = (int)kp[k] + p;
+        acc += (Acc)ld_val_cached(s.val, e) * (Acc)xl[s.col[e]];
+    }
+    return acc;
+}
+
+// The whole row at position p, none of it in registers; the positions below
+// P0 have their first KK levels only in the workspace
+template <typename Acc, typename V, typename X>
+__device__ __forceinline__ Acc side_dot(const Side<V>& s, const unsigned char* lds, const X* xl, int p, int P0, int KK) {
+    if (!s.levels) return row_dot4<Acc>(s.val, s.col, xl, s.rowptr[p] - s.z0, s.rowptr[p + 1] - s.z0);
+    const int len = ((const uint16_t*)(lds + s.o_len))[p];
+    Acc acc = 0;
+    int k = 0;
+    if (p < P0) {
+        const uint32_t* kp = (const uint32_t*)(lds + s.o_kp);
+        const int ke = min(len, KK);
+        for (; k + 4 <= ke; k += 4) {
+            int c[4];
+            Acc v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int e = (int)kp[k + q] + p;
+                c[q] = s.col[e];
+                v[q] = (Acc)ld_val_cached(s.val, e);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc += v[q] * (Acc)xl[c[q]];
+        }
+        for (; k < ke; ++k) {
+            const int e = (int)kp[k] + p;
+            acc += (Acc)ld_val_cached(s.val, e) * (Acc)xl[s.col[e]];
+        }
+        if (len <= KK) return acc;
+    }
+    return side_rest<Acc>(s, lds, xl, p, len, k, acc);
+}
+
+// Rows and entries per row that a thread holds: R rows of K entries, of which
+// the columns are byte offsets into the gathered vector, two to a register.
+// Absent entries are a zero value and the vector's extra zero entry.  Three
+// columns of six and one row of sixteen entries are 51 registers in FP32, of
+// the 128 that four waves to a SIMD leave a thread.
+template <typename V, int R, int K>
+struct RegSide {
+    V v[R][K];
+    uint32_t c[R][K / 2];
+    int len[R];
+    // Called in the loop that uses them: the entries as they are stored stay
+    // in the registers (their conversions and offsets, computed ahead of the
+    // loop, would take twice as many and spill)
+    __device__ __forceinline__ void pin() {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) asm volatile("" : "+v"(v[r][k]));
+#pragma unroll
+            for (int k = 0; k < K / 2; ++k) asm volatile("" : "+v"(c[r][k]));
+        }
+    }
+};
+template <typename V>
+struct RegShape {  // columns (rows of A^T) and rows (of A)
+    static constexpr int RC = 3, KC = sizeof(V) == 8 ? 4 : 6;
+    static constexpr int RR = 1, KR = sizeof(V) == 8 ? 8 : 16;
+};
+
+template <int BS, typename T, typename V, int R, int K>
+__device__ __forceinline__ void reg_load(RegSide<V, R, K>& g, const Side<V>& s, const unsigned char* lds, int dim, int other) {
+    const uint32_t* kp = (const uint32_t*)(lds + s.o_kp);
+    const uint16_t* len = (const uint16_t*)(lds + s.o_len);
+    const bool any = s.levels && len[0] > 0;  // uniform
+    const uint32_t none = ((uint32_t)other * (uint32_t)sizeof(T)) & 0xffffu;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int p = (int)threadIdx.x + r * BS;
+        const int l = any && p < dim ? len[min(p, dim - 1)] : 0;
+        g.len[r] = l;
+        uint32_t c[K];
+        // (branch-free: absent entries load the instance's first one)
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int e = k < l ? (int)kp[k] + p : 0;
+            const V v = any ? s.val[e] : (V)0;
+            const uint32_t cc = any ? (uint32_t)s.col[e] * (uint32_t)sizeof(T) : none;
+            g.v[r][k] = k < l ? v : (V)0;
+            c[k] = k < l ? cc : none;
+        }
+#pragma unroll
+        for (int k = 0; k < K; k += 2) g.c[r][k / 2] = c[k] | (c[k + 1] << 16);
+    }
+}
+
+// The first KE entries of register slot r: the gathers are issued together,
+// the terms added in order
+template <int KE, typename Acc, typename V, typename X, int R, int K>
+__device__ __forceinline__ Acc reg_terms(const RegSide<V, R, K>& g, const X* xl, int r) {
+    X x[KE];
+#pragma unroll
+    for (int k = 0; k < KE; ++k)
+        x[k] = *(const X*)((const unsigned char*)xl + ((k & 1) ? g.c[r][k / 2] >> 16 : g.c[r][k / 2] & 0xffffu));
+    Acc acc = 0;
+#pragma unroll
+    for (int k = 0; k < KE; ++k) acc += (Acc)ld_val_cached(&g.v[r][k], 0) * (Acc)x[k];
+    return acc;
+}
+
+// The row of register slot r.  The wave's longest row is its first lane's, so
+// a wave of short rows issues no more gathers than it needs, in steps.
+template <typename Acc, typename V, typename X, int R, int K>
+__device__ __forceinline__ Acc reg_dot(const RegSide<V, R, K>& g, const Side<V>& s, const unsigned char* lds,
+                                       const X* xl, int r, int p) {
+    const int longest = __builtin_amdgcn_readfirstlane(g.len[r]);
+    if (K > 4 && longest <= 4) return reg_terms<(K > 4 ? 4 : K), Acc>(g, xl, r);
+    if (K > 8 && longest <= 8) return reg_terms<(K > 8 ? 8 : K), Acc>(g, xl, r);
+    if (K > 12 && longest <= 12) return reg_terms<(K > 12 ? 12 : K), Acc>(g, xl, r);
+    Acc acc = reg_terms<K, Acc>(g, xl, r);
+    if (longest > K) acc = side_rest<Acc>(s, lds, xl, p, g.len[r], K, acc);
+    return acc;
+}
+
+// The value of a uniform number, in scalar registers: what is the same for
+// the whole workgroup but comes from LDS or memory would else take a vector
+// register each, and the iterations' matrix entries need those
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ double uniform(double v) {
+    union {
+        double d;
+        int i[2];
+    } u;
+    u.d = v;
+    u.i[0] = __builtin_amdgcn_readfirstlane(u.i[0]);
+    u.i[1] = __builtin_amdgcn_readfirstlane(u.i[1]);
+    return u.d;
+}
+
+__device__ __forceinline__ int64_t uniform64(int64_t v) {
+    const uint32_t lo = (uint32_t)uniform((int)v), hi = (uint32_t)uniform((int)(v >> 32));
+    return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
+// Lane l's value of v (l uniform), in scalar registers
+__device__ __forceinline__ double lane_value(double v, int l) {
+    union {
+        double d;
+        int i[2];
+    } u;
+    u.d = v;
+    u.i[0] = __builtin_amdgcn_readlane(u.i[0], l);
+    u.i[1] = __builtin_amdgcn_readlane(u.i[1], l);
+    return u.d;
+}
+
+// v, computed anew: what depends on it is not moved out of the surrounding
+// loops (addresses formed ahead of the iterations take registers from them)
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// Fixed-order sums over [0, count), whatever the workgroup's size BS (64, or
+// 256 and more): 256 partial sums, i added to the partial i mod 256 in
+// increasing order, then a butterfly over each 64 of them, then the four in
+// order.  f(i, s) adds i's terms and must only read.  Every thread gets the
+// sums; sh holds 4 NS doubles.  Starts with the workgroup in step, and ends
+// with all of f's reads done.
+template <int BS, int NS, class F>
+__device__ __forceinline__ void inst_sums(int count, double* sh, double (&out)[NS], F f) {
     __syncthreads();
+    if constexpr (BS < 256) {
+#pragma unroll 1
+        for (int w = 0; w < 4; ++w) {
+            double s[NS];
 #pragma unroll
-    for (int q = 0; q < NS; ++q) {
-        double v = sh[q * NW];
-        for (int w = 1; w < NW; ++w) v += sh[q * NW + w];
-        s[q] = v;
-    }
+            for (int q = 0; q < NS; ++q) s[q] = 0.0;
+#pragma unroll 2
+            for (int i = opaque(64 * w + (int)threadIdx.x); i < count; i += 256) f(i, s);
 #pragma unroll
-    for (int q = 0; q < NM; ++q) {
-        double v = sh[(NS + q) * NW];
-        for (int w = 1; w < NW; ++w) v = fmax(v, sh[(NS + q) * NW + w]);
-        mx[q] = v;
+            for (int q = 0; q < NS; ++q) {
+                const double v = wave_sum(s[q]);
+                out[q] = uniform(w == 0 ? v : out[q] + v);
+            }
+        }
+        __syncthreads();
+    } else {
+        if (threadIdx.x < 256) {
+            double s[NS];
+#pragma unroll
+            for (int q = 0; q < NS; ++q) s[q] = 0.0;
+#pragma unroll 4
+            for (int i = opaque(threadIdx.x); i < count; i += 256) f(i, s);
+#pragma unroll
+            for (int q = 0; q < NS; ++q) {
+                const double v = wave_sum(s[q]);
+                if ((threadIdx.x & (kWave - 1)) == 0) sh[q * 4 + threadIdx.x / kWave] = v;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NS; ++q) out[q] = uniform(((sh[q * 4] + sh[q * 4 + 1]) + sh[q * 4 + 2]) + sh[q * 4 + 3]);
     }
-    __syncthreads();
+}
+
+// Maximum over the workgroup's threads; sh holds BS / 64 doubles.
+template <int BS>
+__device__ __forceinline__ double inst_max(double v, double* sh) {
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, kWave));
+    if constexpr (BS > kWave) {
+        __syncthreads();
+        if ((threadIdx.x & (kWave - 1)) == 0) sh[threadIdx.x / kWave] = v;
+        __syncthreads();
+        v = sh[0];
+        for (int w = 1; w < BS / kWave; ++w) v = fmax(v, sh[w]);
+    }
+    return uniform(v);
 }
 
 struct InstMat {  // the caller's float64 block-diagonal LP
@@ -84,130 +367,472 @@ struct InstSetup {
     double b_norm, c_norm, sigma_hat, eta, omega0;
 };
 
-// Instance rows [r0, r1), columns [c0, c1), set up by a workgroup of BS
-// threads.  Writes D_r, D_c (float64), the
-// scaled values of the instance's entries of A and A^T (type V) with their
-// instance-local columns (a_cl: col - c0, at_cl: row - r0), b~ and c~ (type T),
-// and returns the norms, sigma_hat, eta and omega_0.  pu, pav are float64
-// scratch vectors indexed like x, y; xl[n] and yl[m] are LDS vectors of the
-// workgroup, free during the set-up.
-template <typename T, typename V, int BS = kBatchBlock>
-__device__ InstSetup inst_setup(const InstMat& M, int r0, int r1, int c0, int c1, double* d_row, double* d_col,
-                                double* pu, double* pav, V* a_vs, V* at_vs, uint16_t* a_cl,
-                                uint16_t* at_cl, T* bt, T* ct, int ruiz, int pc, int power_iters,
-                                double step_safety, T* xl, T* yl, double* sh) {
+// What an instance keeps in the workspace beside its vectors: the scaled
+// values and local columns of A and A^T in side order, and the rows at each
+// position (perm, of rows and columns).
+template <typename V>
+struct InstStore {
+    V *a_vs, *at_vs;
+    uint16_t *a_cl, *at_cl, *perm_r, *perm_c;
+};
+
+// The instance a workgroup holds: sizes, its vectors in LDS (yl of m, xl of n,
+// by position, each followed by a zero) and its two matrices.
+template <typename T, typename V>
+struct Inst {
+    int r0, c0, m, n, z0, nnz;
+    bool levels;
+    const uint16_t *perm_r, *perm_c;
+    T *yl, *xl;
+    Side<V> A, AT;
+    int o_scr;  // LDS scratch of max(m, n) doubles, or -1
+    // the row (column) at position p, in the whole batch
+    __device__ __forceinline__ int row(int p) const { return r0 + (levels ? (int)perm_r[p] : p); }
+    __device__ __forceinline__ int column(int p) const { return c0 + (levels ? (int)perm_c[p] : p); }
+};
+
+__host__ __device__ inline int inst_align(int b) { return (b + 15) & ~15; }
+__host__ __device__ inline int inst_pow2(int v) {
+    int p = 1;
+    while (p < v) p <<= 1;
+    return p;
+}
+// LDS bytes of the vectors, and of the whole instance with its matrices and
+// scratch (the levels' offsets taken at their mean length twice over, which
+// only shapes the launch)
+__host__ __device__ inline int inst_vec_bytes(int m, int n, int ts) {
+    return inst_align((m + 1) * ts) + inst_align((n + 1) * ts);
+}
+// (nreg: the entries that threads hold in registers)
+inline int64_t inst_full_bytes(int64_t m, int64_t n, int64_t nnz, int ts, int vs, int64_t nreg) {
+    const int64_t lens = 2 * (m + n) + 16 * (nnz / (m > 0 ? m : 1) + nnz / (n > 0 ? n : 1)) + 320;
+    const int64_t sort = 4 * (int64_t)inst_pow2((int)(m > n ? m : n)) + 4 * (m + n) + 128;
+    const int64_t left = 2 * nnz > nreg ? 2 * nnz - nreg : 0;
+    const int64_t rest = lens + 8 * (m > n ? m : n) + left * (vs + 2) + 128;
+    return inst_vec_bytes((int)m, (int)n, ts) + (rest > sort ? rest : sort);
+}
+
+// perm <- the positions' rows: rows by decreasing length, equal lengths in
+// order (a bitonic sort of (length, row) keys in LDS, skipped when all
+// lengths are equal)
+template <int BS>
+__device__ void inst_sort(const int32_t* rowptr, int dim, uint32_t* keys, uint16_t* perm, double* sh) {
     const int tid = threadIdx.x;
-    const int m = r1 - r0, n = c1 - c0;
-    double nn[2] = {0.0, 0.0}, nomax[1] = {0.0};
+    double mx = 0.0, mn = 0.0;
+    for (int i = tid; i < dim; i += BS) {
+        const double l = (double)(rowptr[i + 1] - rowptr[i]);
+        mx = fmax(mx, l);
+        mn = fmax(mn, 65536.0 - l);
+    }
+    mx = inst_max<BS>(mx, sh);
+    mn = 65536.0 - inst_max<BS>(mn, sh);
+    if (mx == mn) {  // uniform
+        for (int i = tid; i < dim; i += BS) perm[i] = (uint16_t)i;
+        return;
+    }
+    const int P = inst_pow2(dim);
+    for (int i = tid; i < P; i += BS)
+        keys[i] = i < dim ? ((0xffffu - (uint32_t)(rowptr[i + 1] - rowptr[i])) << 16) | (uint32_t)i : 0xffffffffu;
+    __syncthreads();
+    for (int k = 2; k <= P; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int i = tid; i < P; i += BS) {
+                const int l = i ^ j;
+                if (l > i) {
+                    const uint32_t a = keys[i], b = keys[l];
+                    if ((a > b) == ((i & k) == 0)) {
+                        keys[i] = b;
+                        keys[l] = a;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+    for (int i = tid; i < dim; i += BS) perm[i] = (uint16_t)(keys[i] & 0xffffu);
+    __syncthreads();
+}
+
+// Lengths by position and level offsets of one side in LDS (kp of the
+// workspace, kl of the entries that LDS holds: below level KK those from
+// position P0 on), o: the next free byte (advanced); returns the number of
+// levels.
+template <int BS, typename V>
+__device__ int inst_levels(const int32_t* rowptr, const uint16_t* perm, int dim, int P0, int KK, unsigned char* lds,
+                           int& o, Side<V>& s) {
+    const int tid = threadIdx.x;
+    s.o_len = o;
+    uint16_t* len = (uint16_t*)(lds + s.o_len);
+    o = inst_align(o + 2 * dim);
+    for (int p = tid; p < dim; p += BS) len[p] = (uint16_t)(rowptr[perm[p] + 1] - rowptr[perm[p]]);
+    __syncthreads();
+    const int K = uniform((int)len[0]);
+    s.o_kp = o;
+    uint32_t* kp = (uint32_t*)(lds + s.o_kp);
+    o = inst_align(o + 4 * (K + 4));
+    s.o_kl = o;
+    int32_t* kl = (int32_t*)(lds + s.o_kl);
+    o = inst_align(o + 4 * (K + 4));
+    // rows longer than k, then the running sums
+    for (int p = tid; p < dim; p += BS) {
+        const int lo = p + 1 < dim ? len[p + 1] : 0;
+        for (int k = lo; k < len[p]; ++k) kp[k + 1] = (uint32_t)(p + 1);
+    }
+    if (tid == 0) kp[0] = 0;
+    __syncthreads();
+    if (tid < kWave) {
+        int carry = 0, carry_l = 0;
+        for (int b = 0; b <= K; b += kWave) {
+            const int k = b + tid;
+            int v = k <= K ? (int)kp[k] : 0;
+            int l = k > 0 && k - 1 < KK ? max(v - P0, 0) : v;
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                const int u = __shfl_up(v, d, kWave), ul = __shfl_up(l, d, kWave);
+                if (tid >= d) {
+                    v += u;
+                    l += ul;
+                }
+            }
+            v += carry;
+            l += carry_l;
+            if (k <= K) {
+                kp[k] = (uint32_t)v;
+                kl[k] = l - (k < KK && k < K ? P0 : 0);
+            }
+            carry = __shfl(v, kWave - 1, kWave);
+            carry_l = __shfl(l, kWave - 1, kWave);
+        }
+    }
+    __syncthreads();
+    return K;
+}
+
+// The workgroup's LDS for instance I (sizes and vectors set): the vectors'
+// zero entries, lengths, level offsets, and, as far as `budget` bytes go, the
+// scratch and what the threads' registers leave of the first levels of A^T
+// and A, copied from the workspace if fill; in CSR order only the scratch.
+template <typename T, typename V, int BS>
+__device__ void inst_load(Inst<T, V>& I, const InstMat& M, const InstStore<V>& S, unsigned char* lds, int budget,
+                          bool fill) {
+    typedef RegShape<V> RS;
+    int o = inst_vec_bytes(I.m, I.n, sizeof(T));
+    if (threadIdx.x == 0) {
+        I.yl[I.m] = (T)0;
+        I.xl[I.n] = (T)0;
+    }
+    I.A.levels = I.AT.levels = I.levels;
+    I.A.rowptr = M.a_rowptr + I.r0;
+    I.AT.rowptr = M.at_rowptr + I.c0;
+    I.A.z0 = I.AT.z0 = I.z0;
+    I.A.val = S.a_vs + I.z0;
+    I.AT.val = S.at_vs + I.z0;
+    I.A.col = S.a_cl + I.z0;
+    I.AT.col = S.at_cl + I.z0;
+    I.A.K0 = I.AT.K0 = 0;
+    I.A.o_kp = I.A.o_kl = I.A.o_len = I.A.o_val = I.A.o_col = 0;
+    I.AT.o_kp = I.AT.o_kl = I.AT.o_len = I.AT.o_val = I.AT.o_col = 0;
+    int KA = 0, KT = 0;
+    if (I.levels) {
+        KA = inst_levels<BS>(I.A.rowptr, I.perm_r, I.m, RS::RR * BS, RS::KR, lds, o, I.A);
+        KT = inst_levels<BS>(I.AT.rowptr, I.perm_c, I.n, RS::RC * BS, RS::KC, lds, o, I.AT);
+    }
+    const int scr = 8 * max(I.m, I.n);
+    I.o_scr = -1;
+    int64_t left = 0;  // entries beside those in registers
+    if (I.levels)
+        left = (int64_t)((const int32_t*)(lds + I.A.o_kl))[KA] + ((const int32_t*)(lds + I.AT.o_kl))[KT];
+    left = uniform((int)left);
+    const bool all = o + scr + left * ((int)sizeof(V) + 2) + 96 <= budget;
+    if (all || (o + scr <= budget && 6 * scr <= budget)) {  // otherwise the matrix needs the room more
+        I.o_scr = o;
+        o = inst_align(o + scr);
+    }
+    if (!I.levels) return;
+    auto take = [&](Side<V>& s, int K, int P0, int KK) {
+        // kl[k] + p is level k's entry: its first position in LDS is P0 below level KK
+        const int32_t* kl = (const int32_t*)(lds + s.o_kl);
+        const int room = max(0, budget - o - 32) / ((int)sizeof(V) + 2);
+        auto first = [&](int k) { return kl[k] + (k < KK && k < K ? P0 : 0); };
+        int k0 = K;
+        if (first(K) > room) {  // whole groups of four levels
+            k0 = K & ~3;
+            while (k0 > 0 && first(k0) > room) k0 -= 4;
+        }
+        const int z = uniform(first(k0));
+        s.K0 = uniform(k0);
+        s.o_val = o;
+        o = inst_align(o + z * (int)sizeof(V));
+        s.o_col = o;
+        o = inst_align(o + z * 2);
+    };
+    take(I.AT, KT, RS::RC * BS, RS::KC);
+    take(I.A, KA, RS::RR * BS, RS::KR);
+    if (!fill) return;
+    auto copy = [&](const Side<V>& s, int P0, int KK, int dim) {
+        const uint32_t* kp = (const uint32_t*)(lds + s.o_kp);
+        const int32_t* kl = (const int32_t*)(lds + s.o_kl);
+        V* v = (V*)(lds + s.o_val);
+        uint16_t* c = (uint16_t*)(lds + s.o_col);
+        for (int k = 0; k < s.K0; ++k) {
+            const int cnt = (int)(kp[k + 1] - kp[k]);
+            for (int p = (k < KK ? P0 : 0) + (int)threadIdx.x; p < cnt; p += BS) {
+                v[kl[k] + p] = s.val[kp[k] + p];
+                c[kl[k] + p] = s.col[kp[k] + p];
+            }
+        }
+    };
+    copy(I.AT, RS::RC * BS, RS::KC, I.n);
+    copy(I.A, RS::RR * BS, RS::KR, I.m);
+    __syncthreads();
+}
+
+// f(p, r, sum) for every row at position p of one side, its sum over the
+// gathered vector xl: the rows in registers (slot r), then the others (r = -1).
+// A wave leaves out the slots whose positions all lie past the end.
+template <int BS, int R, typename Acc, typename V, typename X, int K, class F>
+__device__ __forceinline__ void inst_rows(bool levels, int dim, const RegSide<V, R, K>& g, const Side<V>& s,
+                                          const unsigned char* lds, const X* xl, F f) {
+    const int tid = threadIdx.x;
+    const int w0 = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));
+    int p = opaque(tid);
+    if (levels) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (w0 + r * BS >= dim) return;
+            const int pr = tid + r * BS;
+            const Acc a = reg_dot<Acc>(g, s, lds, xl, r, pr);
+            if (pr < dim) f(pr, r, a);
+        }
+        p += R * BS;
+    }
+    for (; p < dim; p += BS) f(p, -1, side_dot<Acc>(s, lds, xl, p, 0, 0));
+}
+
+template <typename V>
+__device__ __forceinline__ void put_scaled(V* out, int64_t k, double v) {
+    if constexpr (sizeof(V) == 2) out[k] = f32_to_bf16_rne((float)v);
+    else out[k] = (V)v;
+}
+
+// Sets up the instance with rows [r0, r1), columns [c0, c1) by a workgroup of
+// BS threads with `budget` bytes of LDS.  Writes D_r, D_c (float64), the scaled
+// values of the instance's entries of A and A^T (type V) with their local
+// columns in side order, b~ and c~ by position (type T), fills I, and returns
+// the norms, sigma_hat, eta and omega_0.  pu[n], pav[m] are float64 scratch
+// vectors of the whole batch.  The results do not depend on BS.
+template <typename T, typename V, int BS>
+__device__ InstSetup inst_setup(Inst<T, V>& I, const InstMat& M, const InstStore<V>& S, double* d_row, double* d_col,
+                                double* pu, double* pav, T* bt, T* ct, int ruiz, int pc, int power_iters,
+                                double step_safety, unsigned char* lds, int budget, double* sh) {
+    const int tid = threadIdx.x;
+    const int r0 = I.r0, c0 = I.c0, m = I.m, n = I.n;
+    const int32_t *arp = M.a_rowptr + r0, *trp = M.at_rowptr + c0;
 
     // norms of b and c
-    for (int i = tid; i < m; i += BS) nn[0] += M.b[r0 + i] * M.b[r0 + i];
-    for (int j = tid; j < n; j += BS) nn[1] += M.c[c0 + j] * M.c[c0 + j];
-    wg_reduce<2, 0, BS>(nn, nomax, sh);
-    const double b_norm = sqrt(nn[0]), c_norm = sqrt(nn[1]);
+    double nb[1], nc[1];
+    inst_sums<BS, 1>(m, sh, nb, [&](int i, double(&s)[1]) { s[0] += M.b[r0 + i] * M.b[r0 + i]; });
+    inst_sums<BS, 1>(n, sh, nc, [&](int j, double(&s)[1]) { s[0] += M.c[c0 + j] * M.c[c0 + j]; });
+    const double b_norm = sqrt(nb[0]), c_norm = sqrt(nc[0]);
+
+    // the layout: levels if every row and column is short enough and the
+    // sort's keys fit
+    double mx = 0.0;
+    for (int i = tid; i < m; i += BS) mx = fmax(mx, (double)(arp[i + 1] - arp[i]));
+    for (int j = tid; j < n; j += BS) mx = fmax(mx, (double)(trp[j + 1] - trp[j]));
+    mx = inst_max<BS>(mx, sh);
+    const int big = max(m, n);
+    const int o_tmp = inst_vec_bytes(m, n, sizeof(T));
+    // (the level offsets of both sides are at most 16 (mx + 4) bytes)
+    const int longest = uniform((int)mx);
+    I.levels = mx <= (double)kLevelMaxLen && big <= kLevelMaxDim &&
+               o_tmp + max(4 * inst_pow2(big) + 64, 2 * (m + n) + 16 * (longest + 4) + 160) + 2 * (m + n) <= budget;
+    if (I.levels) {
+        uint32_t* keys = (uint32_t*)(lds + o_tmp);
+        inst_sort<BS>(arp, m, keys, S.perm_r + r0, sh);
+        __syncthreads();
+        inst_sort<BS>(trp, n, keys, S.perm_c + c0, sh);
+        __syncthreads();
+    }
+    I.perm_r = S.perm_r + r0;
+    I.perm_c = S.perm_c + c0;
 
     // scaling: Ruiz infinity-norm passes, then one Pock-Chambolle pass
-    for (int i = tid; i < m; i += BS) d_row[r0 + i] = 1.0;
-    for (int j = tid; j < n; j += BS) d_col[c0 + j] = 1.0;
-    __syncthreads();
+    // (D_r and D_c of a pass and of the next in LDS where they fit: what bounds
+    // a pass is the latency of a row's range, entries and gathers, one after
+    // the other; in the workspace the gathers are L2 accesses)
     const int passes = ruiz + (pc ? 1 : 0);
-    double* stat_r = pav;
-    double* stat_c = pu;
-    for (int ps = 0; ps < passes; ++ps) {
-        const bool mxm = ps < ruiz;
-        for (int i = tid; i < m; i += BS) {
-            const int g = r0 + i;
-            double acc = 0.0;
-            for (int k = M.a_rowptr[g]; k < M.a_rowptr[g + 1]; ++k) {
-                const double v = fabs(M.a_val[k]) * d_col[M.a_col[k]];
-                acc = mxm ? fmax(acc, v) : acc + v;
+    if (16 * (m + n) <= budget) {
+        double* cur = (double*)lds;
+        double* nxt = cur + m + n;
+        __syncthreads();
+        for (int i = tid; i < m + n; i += BS) cur[i] = 1.0;
+        __syncthreads();
+        for (int ps = 0; ps < passes; ++ps) {
+            const bool mxm = ps < ruiz;
+            auto scale = [&](int i, double acc) {
+                const double s = cur[i] * acc;
+                nxt[i] = s > 0.0 ? cur[i] * (1.0 / sqrt(s)) : cur[i];
+            };
+            for (int i = tid; i < m; i += BS)
+                scale(i, mxm ? row_f64<2>(M.a_val, M.a_col, cur + m, arp[i], arp[i + 1], c0)
+                             : row_f64<1>(M.a_val, M.a_col, cur + m, arp[i], arp[i + 1], c0));
+            for (int j = tid; j < n; j += BS)
+                scale(m + j, mxm ? row_f64<2>(M.at_val, M.at_col, cur, trp[j], trp[j + 1], r0)
+                                 : row_f64<1>(M.at_val, M.at_col, cur, trp[j], trp[j + 1], r0));
+            __syncthreads();
+            double* t = cur;
+            cur = nxt;
+            nxt = t;
+        }
+        for (int i = tid; i < m; i += BS) d_row[r0 + i] = cur[i];
+        for (int j = tid; j < n; j += BS) d_col[c0 + j] = cur[m + j];
+        __syncthreads();
+    } else {
+        for (int i = tid; i < m; i += BS) d_row[r0 + i] = 1.0;
+        for (int j = tid; j < n; j += BS) d_col[c0 + j] = 1.0;
+        __syncthreads();
+        double *stat_r = pav, *stat_c = pu;
+        for (int ps = 0; ps < passes; ++ps) {
+            const bool mxm = ps < ruiz;
+            for (int i = tid; i < m; i += BS) {
+                const double acc = mxm ? row_f64<2>(M.a_val, M.a_col, d_col, arp[i], arp[i + 1])
+                                       : row_f64<1>(M.a_val, M.a_col, d_col, arp[i], arp[i + 1]);
+                stat_r[r0 + i] = d_row[r0 + i] * acc;
             }
-            stat_r[g] = d_row[g] * acc;
+            for (int j = tid; j < n; j += BS) {
+                const double acc = mxm ? row_f64<2>(M.at_val, M.at_col, d_row, trp[j], trp[j + 1])
+                                       : row_f64<1>(M.at_val, M.at_col, d_row, trp[j], trp[j + 1]);
+                stat_c[c0 + j] = d_col[c0 + j] * acc;
+            }
+            __syncthreads();
+            for (int i = tid; i < m; i += BS) {
+                const double s = stat_r[r0 + i];
+                if (s > 0.0) d_row[r0 + i] *= 1.0 / sqrt(s);
+            }
+            for (int j = tid; j < n; j += BS) {
+                const double s = stat_c[c0 + j];
+                if (s > 0.0) d_col[c0 + j] *= 1.0 / sqrt(s);
+            }
+            __syncthreads();
+        }
+    }
+
+    // scaled values in the iteration precision, in side order
+    if (I.levels) {
+        inst_load<T, V, BS>(I, M, S, lds, budget, false);
+        // positions of the rows and columns, in LDS that the sides' copies take over afterwards
+        uint16_t* pos_r = (uint16_t*)(lds + budget - 2 * (m + n));
+        uint16_t* pos_c = pos_r + m;
+        for (int p = tid; p < m; p += BS) pos_r[I.perm_r[p]] = (uint16_t)p;
+        for (int p = tid; p < n; p += BS) pos_c[I.perm_c[p]] = (uint16_t)p;
+        __syncthreads();
+        const uint32_t* kpa = (const uint32_t*)(lds + I.A.o_kp);
+        const uint32_t* kpt = (const uint32_t*)(lds + I.AT.o_kp);
+        for (int p = tid; p < m; p += BS) {
+            const int i = I.perm_r[p], s = arp[i], len = arp[i + 1] - s;
+            const double dr = d_row[r0 + i];
+            for (int k = 0; k < len; ++k) {
+                const int j = M.a_col[s + k];
+                const int64_t e = (int64_t)I.z0 + kpa[k] + p;
+                put_scaled(S.a_vs, e, dr * M.a_val[s + k] * d_col[j]);
+                S.a_cl[e] = pos_c[j - c0];
+            }
+        }
+        for (int p = tid; p < n; p += BS) {
+            const int j = I.perm_c[p], s = trp[j], len = trp[j + 1] - s;
+            const double dc = d_col[c0 + j];
+            for (int k = 0; k < len; ++k) {
+                const int i = M.at_col[s + k];
+                const int64_t e = (int64_t)I.z0 + kpt[k] + p;
+                put_scaled(S.at_vs, e, dc * M.at_val[s + k] * d_row[i]);
+                S.at_cl[e] = pos_r[i - r0];
+            }
+        }
+    } else {
+        for (int i = tid; i < m; i += BS) {
+            const double dr = d_row[r0 + i];
+            for (int k = arp[i]; k < arp[i + 1]; ++k) {
+                const int j = M.a_col[k];
+                put_scaled(S.a_vs, k, dr * M.a_val[k] * d_col[j]);
+                S.a_cl[k] = (uint16_t)(j - c0);
+            }
         }
         for (int j = tid; j < n; j += BS) {
-            const int g = c0 + j;
-            double acc = 0.0;
-            for (int k = M.at_rowptr[g]; k < M.at_rowptr[g + 1]; ++k) {
-                const double v = fabs(M.at_val[k]) * d_row[M.at_col[k]];
-                acc = mxm ? fmax(acc, v) : acc + v;
+            const double dc = d_col[c0 + j];
+            for (int k = trp[j]; k < trp[j + 1]; ++k) {
+                const int i = M.at_col[k];
+                put_scaled(S.at_vs, k, dc * M.at_val[k] * d_row[i]);
+                S.at_cl[k] = (uint16_t)(i - r0);
             }
-            stat_c[g] = d_col[g] * acc;
         }
-        __syncthreads();
-        for (int i = tid; i < m; i += BS) {
-            const double s = stat_r[r0 + i];
-            if (s > 0.0) d_row[r0 + i] *= 1.0 / sqrt(s);
-        }
-        for (int j = tid; j < n; j += BS) {
-            const double s = stat_c[c0 + j];
-            if (s > 0.0) d_col[c0 + j] *= 1.0 / sqrt(s);
-        }
-        __syncthreads();
     }
-    // scaled values in the iteration precision, b~ and c~ (norms in float64)
-    double tn[2] = {0.0, 0.0};
-    for (int i = tid; i < m; i += BS) {
-        const int g = r0 + i;
-        const double dr = d_row[g];
-        for (int k = M.a_rowptr[g]; k < M.a_rowptr[g + 1]; ++k) {
-            const int j = M.a_col[k];
-            const double v = dr * M.a_val[k] * d_col[j];
-            if constexpr (sizeof(V) == 2) a_vs[k] = f32_to_bf16_rne((float)v);
-            else a_vs[k] = (V)v;
-            a_cl[k] = (uint16_t)(j - c0);
-        }
-        const double btv = dr * M.b[g];
-        bt[g] = (T)btv;
-        tn[0] += btv * btv;
+    __syncthreads();
+    inst_load<T, V, BS>(I, M, S, lds, budget, true);
+    // b~ and c~ by position, their norms in float64
+    for (int p = tid; p < m; p += BS) {
+        const int g = I.row(p);
+        bt[r0 + p] = (T)(d_row[g] * M.b[g]);
     }
-    for (int j = tid; j < n; j += BS) {
-        const int g = c0 + j;
-        const double dc = d_col[g];
-        for (int k = M.at_rowptr[g]; k < M.at_rowptr[g + 1]; ++k) {
-            const int i = M.at_col[k];
-            const double v = dc * M.at_val[k] * d_row[i];
-            if constexpr (sizeof(V) == 2) at_vs[k] = f32_to_bf16_rne((float)v);
-            else at_vs[k] = (V)v;
-            at_cl[k] = (uint16_t)(i - r0);
-        }
-        const double ctv = dc * M.c[g];
-        ct[g] = (T)ctv;
-        tn[1] += ctv * ctv;
+    for (int p = tid; p < n; p += BS) {
+        const int g = I.column(p);
+        ct[c0 + p] = (T)(d_col[g] * M.c[g]);
     }
-    wg_reduce<2, 0, BS>(tn, nomax, sh);
-    const double nbt = sqrt(tn[0]), nct = sqrt(tn[1]);
+    inst_sums<BS, 1>(m, sh, nb, [&](int i, double(&s)[1]) {
+        const double v = d_row[r0 + i] * M.b[r0 + i];
+        s[0] += v * v;
+    });
+    inst_sums<BS, 1>(n, sh, nc, [&](int j, double(&s)[1]) {
+        const double v = d_col[c0 + j] * M.c[c0 + j];
+        s[0] += v * v;
+    });
+    const double nbt = sqrt(nb[0]), nct = sqrt(nc[0]);
 
     // power iteration on the scaled iteration copy (the values and 16-bit
     // columns the iterations apply), as in the single-LP solve: vectors in
     // the iterate type, held in LDS (v in xl, A~ v in yl), products and sums
     // in float64.  u = A~^T (A~ v) overwrites v, which it no longer needs.
-    __syncthreads();  // the scaled copies above are read by other threads
-    for (int j = tid; j < n; j += BS) xl[j] = (T)(1.0 / sqrt((double)n));
+    // The float64 entries pass through the scratch to be summed in order.
+    T *xl = I.xl, *yl = I.yl;
+    double* const scr = (double*)(lds + max(I.o_scr, 0));
+    typedef RegShape<V> RS;
+    RegSide<V, RS::RC, RS::KC> gt;
+    RegSide<V, RS::RR, RS::KR> ga;
+    reg_load<BS, T>(gt, I.AT, lds, n, m);
+    reg_load<BS, T>(ga, I.A, lds, m, n);
+    int ir[RS::RR], jc[RS::RC];  // the rows and columns of the register slots
+#pragma unroll
+    for (int r = 0; r < RS::RR; ++r) ir[r] = I.row(min(tid + r * BS, m - 1)) - r0;
+#pragma unroll
+    for (int r = 0; r < RS::RC; ++r) jc[r] = I.column(min(tid + r * BS, n - 1)) - c0;
+    for (int p = tid; p < n; p += BS) xl[p] = (T)(1.0 / sqrt((double)n));
     __syncthreads();
     double h = 0.0, h_m10 = 0.0;
     for (int kk = 0; kk <= power_iters; ++kk) {
-        double s1[1] = {0.0};
-        for (int i = tid; i < m; i += BS) {
-            const int g = r0 + i;
-            const double t = row_dot4<double>(a_vs, a_cl, xl, M.a_rowptr[g], M.a_rowptr[g + 1]);
-            yl[i] = (T)t;
-            s1[0] += t * t;
-        }
-        wg_reduce<1, 0, BS>(s1, nomax, sh);
-        h = sqrt(s1[0]);
+        double s[1];
+        ga.pin();
+        gt.pin();
+        inst_rows<BS, RS::RR, double>(I.levels, m, ga, I.A, lds, xl, [&](int p, int r, double t) {
+            yl[p] = (T)t;
+            const int i = r >= 0 ? ir[r] : I.row(p) - r0;
+            if (I.o_scr >= 0) scr[i] = t;
+            else pav[r0 + i] = t;
+        });
+        if (I.o_scr >= 0) inst_sums<BS, 1>(m, sh, s, [&](int i, double(&q)[1]) { q[0] += scr[i] * scr[i]; });
+        else inst_sums<BS, 1>(m, sh, s, [&](int i, double(&q)[1]) { q[0] += pav[r0 + i] * pav[r0 + i]; });
+        h = sqrt(s[0]);
         if (kk == power_iters - 10) h_m10 = h;
         if (kk == power_iters) break;
-        double s2[1] = {0.0};
-        for (int j = tid; j < n; j += BS) {
-            const int g = c0 + j;
-            const double t = row_dot4<double>(at_vs, at_cl, yl, M.at_rowptr[g], M.at_rowptr[g + 1]);
-            xl[j] = (T)t;
-            s2[0] += t * t;
-        }
-        wg_reduce<1, 0, BS>(s2, nomax, sh);
-        const double nu = sqrt(s2[0]);
+        inst_rows<BS, RS::RC, double>(I.levels, n, gt, I.AT, lds, yl, [&](int p, int r, double t) {
+            xl[p] = (T)t;
+            const int j = r >= 0 ? jc[r] : I.column(p) - c0;
+            if (I.o_scr >= 0) scr[j] = t;
+            else pu[c0 + j] = t;
+        });
+        if (I.o_scr >= 0) inst_sums<BS, 1>(n, sh, s, [&](int j, double(&q)[1]) { q[0] += scr[j] * scr[j]; });
+        else inst_sums<BS, 1>(n, sh, s, [&](int j, double(&q)[1]) { q[0] += pu[c0 + j] * pu[c0 + j]; });
+        const double nu = sqrt(s[0]);
         if (nu != 0.0)
-            for (int j = tid; j < n; j += BS) xl[j] = (T)((double)xl[j] / nu);
+            for (int p = tid; p < n; p += BS) xl[p] = (T)((double)xl[p] / nu);
         __syncthreads();
     }
     const double sigma_hat = h;

@@ -24,7 +24,13 @@
 //                       lam_y -= A~ lam_g
 // with the seed D_c * grad(x_K) on the last x_hat.  dL/dc = D_c lam_c~ and
 // dL/db = D_r lam_b~.  Both passes run one workgroup per instance in one
-// persistent launch, with the two gathered vectors in LDS.
+// persistent launch, with the two gathered vectors in LDS and, between the
+// iterations that checkpoint or may restart, the matrices and the state in
+// the threads' registers as in the batched solve: an iteration is bound by the
+// latency of its gathers and two barriers (the reverse sweep: three).
+// Measured at 256 instances of 500 x 1,500, 5 entries a column, FP32, K = 400:
+// with 256 threads reading the matrices and the state from L2, 4.9 ms forward
+// and 9.3 ms backward; so, 0.86 (set-up) + 1.75 and 3.55 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -41,14 +47,15 @@ namespace mip {
 template <typename T, typename V>
 struct UArgs {
     int32_t B, K, ckpt, E, nseg, nep, W;
-    int32_t lds_m, lds_n, replay;
+    int32_t lds, replay;  // lds: bytes of dynamic LDS per workgroup
     int32_t N, Mrows;
     const int32_t *row_off, *col_off, *word_off;
     InstMat M;
-    // tape: scaling, scaled values, schedule, checkpoints
+    // tape: scaling, scaled values, schedule, checkpoints; the instance
+    // vectors, masks and checkpoints by position (see Side)
     double *d_row, *d_col, *pu, *pav;
-    V *a_vs, *at_vs;
-    uint16_t *a_cl, *at_cl;  // instance-local columns of A, A^T
+    InstStore<V> S;
+    int32_t* levels;  // per instance: the matrices' layout
     T *bt, *ct;
     double *eta, *omega0, *taus, *sigmas;
     int8_t* restart;
@@ -69,184 +76,250 @@ struct UArgs {
     int32_t ruiz, pc, power_iters, halpern, restarts;
 };
 
-template <typename T, typename V>
-struct UInst {
-    int inst, r0, r1, c0, c1, m, n;
-};
-
-// One forward iteration t of instance u with step (tau, sig) and Halpern
-// weight from k.  With masks != nullptr the projection masks are stored.
-// Returns q = (||x-x^||^2, ||x^-x0||^2, ||y-y^||^2, ||y^-y0||^2) partials of
-// this thread when `want_q`.
-template <typename T, typename V, typename Acc>
-__device__ __forceinline__ void u_iterate(const UArgs<T, V>& a, const UInst<T, V>& u, T* yL, T* xbL, int64_t k,
+// One forward iteration of instance I (number i) with step (tau, sig) and
+// Halpern weight from k.  want_q: the sums' entries x - x^, x^ - x0 (by column)
+// and y - y^, y^ - y0 (by row) go to pu, xK and pav, lbt; keep_hat: x^, y^ are
+// kept; last: x_K is written; maskrow (or NULL): the projection masks.
+template <typename T, typename V, typename Acc, int BS>
+__device__ __forceinline__ void u_iterate(const UArgs<T, V>& a, const Inst<T, V>& I, const unsigned char* lds, int64_t k,
                                           double tau, double sig, bool want_q, bool keep_hat, bool last,
-                                          uint64_t* maskrow, double (&q)[4]) {
-    const int tid = threadIdx.x;
+                                          uint64_t* maskrow) {
+    typedef RegShape<V> RS;
+    const int tid = opaque(threadIdx.x);
+    const int n = I.n, m = I.m, c0 = I.c0, r0 = I.r0;
     const double w = a.halpern ? (double)(k + 1) / (double)(k + 2) : 1.0;
     const double omw = 1.0 - w, rho = a.rho, opr = 1.0 + a.rho;
-    // the next row's bounds and vector entries are loaded (branch-free,
-    // clamped to the last row) while this row is summed
-    int nb0 = 0, nb1 = 0;
-    T nx = 0, nx0 = 0, nct = 0;
-    if (u.n > 0) {
-        const int g = u.c0 + min(tid, u.n - 1);
-        nb0 = a.M.at_rowptr[g];
-        nb1 = a.M.at_rowptr[g + 1];
-        nx = a.x[g];
-        nx0 = a.x0[g];
-        nct = a.ct[g];
-    }
-    for (int j = tid; j < u.n; j += kBatchBlock) {
-        const int g = u.c0 + j;
-        const int b0 = nb0, b1 = nb1;
-        const double o = (double)nx, an = (double)nx0, ctg = (double)nct;
-        {
-            const int gn = u.c0 + min(j + kBatchBlock, u.n - 1);
-            nb0 = a.M.at_rowptr[gn];
-            nb1 = a.M.at_rowptr[gn + 1];
-            nx = a.x[gn];
-            nx0 = a.x0[gn];
-            nct = a.ct[gn];
-        }
-        const Acc s = row_dot4<Acc>(a.at_vs, a.at_cl, yL, b0, b1);
+    for (int p = tid; p < n; p += BS) {
+        const int g = c0 + p;
+        const double o = (double)a.x[g], an = (double)a.x0[g], ctg = (double)a.ct[g];
+        const Acc s = side_dot<Acc>(I.AT, lds, I.yl, p, RS::RC * BS, RS::KC);
         const double v = o - tau * (ctg - (double)s);
         const double hh = v < 0.0 ? 0.0 : v;
         if (maskrow) {
             const unsigned long long bits = __ballot(v > 0.0);
-            if ((tid & (kWave - 1)) == 0) maskrow[j >> 6] = bits;
+            if ((tid & (kWave - 1)) == 0) maskrow[p >> 6] = bits;
         }
-        xbL[j] = (T)(2.0 * hh - o);
+        I.xl[p] = (T)(2.0 * hh - o);
         a.x[g] = (T)(w * (opr * hh - rho * o) + omw * an);
-        if (want_q) {
-            const double d = o - hh, e = hh - an;
-            q[0] += d * d;
-            q[1] += e * e;
+        if (want_q || last) {
+            const int j = I.column(p);
+            if (last) a.xK[j] = a.d_col[j] * hh;
+            if (want_q) {
+                a.pu[j] = o - hh;
+                a.xK[j] = hh - an;  // (the last iteration wants no sums)
+            }
         }
         if (keep_hat) a.xhat[g] = (T)hh;
-        if (last) a.xK[g] = a.d_col[g] * hh;
     }
     __syncthreads();
-    int mb0 = 0, mb1 = 0;
-    T my0 = 0, mbt = 0;
-    if (u.m > 0) {
-        const int g = u.r0 + min(tid, u.m - 1);
-        mb0 = a.M.a_rowptr[g];
-        mb1 = a.M.a_rowptr[g + 1];
-        my0 = a.y0[g];
-        mbt = a.bt[g];
-    }
-    for (int i = tid; i < u.m; i += kBatchBlock) {
-        const int g = u.r0 + i;
-        const int b0 = mb0, b1 = mb1;
-        const double an = (double)my0, btg = (double)mbt;
-        {
-            const int gn = u.r0 + min(i + kBatchBlock, u.m - 1);
-            mb0 = a.M.a_rowptr[gn];
-            mb1 = a.M.a_rowptr[gn + 1];
-            my0 = a.y0[gn];
-            mbt = a.bt[gn];
-        }
-        const Acc s = row_dot4<Acc>(a.a_vs, a.a_cl, xbL, b0, b1);
-        const double o = (double)yL[i];
+    for (int p = tid; p < m; p += BS) {
+        const int g = r0 + p;
+        const double an = (double)a.y0[g], btg = (double)a.bt[g];
+        const Acc s = side_dot<Acc>(I.A, lds, I.xl, p, RS::RR * BS, RS::KR);
+        const double o = (double)I.yl[p];
         const double hh = o + sig * (btg - (double)s);
-        yL[i] = (T)(w * (opr * hh - rho * o) + omw * an);
+        I.yl[p] = (T)(w * (opr * hh - rho * o) + omw * an);
         if (want_q) {
-            const double d = o - hh, e = hh - an;
-            q[2] += d * d;
-            q[3] += e * e;
+            const int i = I.row(p);
+            a.pav[i] = o - hh;
+            a.lbt[i] = hh - an;
         }
         if (keep_hat) a.yhat[g] = (T)hh;
     }
     __syncthreads();
 }
 
-// state and anchor <- projected point (a restart)
-template <typename T, typename V>
-__device__ __forceinline__ void u_restart(const UArgs<T, V>& a, const UInst<T, V>& u, T* yL) {
-    for (int j = threadIdx.x; j < u.n; j += kBatchBlock) {
-        const T v = a.xhat[u.c0 + j];
-        a.x[u.c0 + j] = v;
-        a.x0[u.c0 + j] = v;
+// `count` such iterations with none of these extras (but the masks, W words
+// from one iteration's to the next), from iteration k of the epoch on: the
+// threads' rows and their vectors' entries stay in registers.
+template <typename T, typename V, typename Acc, int BS>
+__device__ __forceinline__ void u_plain(const UArgs<T, V>& a, const Inst<T, V>& I, const unsigned char* lds, int count,
+                                        int64_t k, double tau, double sig, uint64_t* maskrow) {
+    typedef RegShape<V> RS;
+    const int tid = opaque(threadIdx.x);
+    const int m = I.m, n = I.n, c0 = I.c0, r0 = I.r0, W = a.W;
+    T *const yL = I.yl, *const xbL = I.xl;
+    const double rho = a.rho, opr = 1.0 + a.rho;
+    RegSide<V, RS::RC, RS::KC> gt;
+    RegSide<V, RS::RR, RS::KR> ga;
+    reg_load<BS, T>(gt, I.AT, lds, n, m);
+    reg_load<BS, T>(ga, I.A, lds, m, n);
+    T xr[RS::RC], x0r[RS::RC], ctr[RS::RC], y0r[RS::RR], btr[RS::RR];
+#pragma unroll
+    for (int r = 0; r < RS::RC; ++r) {
+        const int g = c0 + min(tid + r * BS, n - 1);
+        xr[r] = a.x[g];
+        x0r[r] = a.x0[g];
+        ctr[r] = a.ct[g];
     }
-    for (int i = threadIdx.x; i < u.m; i += kBatchBlock) {
-        const T v = a.yhat[u.r0 + i];
-        yL[i] = v;
-        a.y0[u.r0 + i] = v;
+#pragma unroll
+    for (int r = 0; r < RS::RR; ++r) {
+        const int g = r0 + min(tid + r * BS, m - 1);
+        y0r[r] = a.y0[g];
+        btr[r] = a.bt[g];
+    }
+    double wl = 1.0;  // lane l: the Halpern weight of iteration l of each 64
+    for (int it = 0; it < count; ++it) {
+        if (a.halpern && (it & (kWave - 1)) == 0) {
+            const double kl = (double)(k + it + (tid & (kWave - 1)));
+            wl = (kl + 1.0) / (kl + 2.0);
+        }
+        const double w = lane_value(wl, it & (kWave - 1)), omw = 1.0 - w;
+        gt.pin();
+        ga.pin();
+        inst_rows<BS, RS::RC, Acc>(I.levels, n, gt, I.AT, lds, yL, [&](int p, int r, Acc s) {
+            const int g = c0 + p;
+            const double o = (double)(r >= 0 ? xr[r] : a.x[g]), an = (double)(r >= 0 ? x0r[r] : a.x0[g]);
+            const double ctg = (double)(r >= 0 ? ctr[r] : a.ct[g]);
+            const double v = o - tau * (ctg - (double)s);
+            const double hh = v < 0.0 ? 0.0 : v;
+            if (maskrow) {
+                const unsigned long long bits = __ballot(v > 0.0);
+                if ((tid & (kWave - 1)) == 0) maskrow[p >> 6] = bits;
+            }
+            xbL[p] = (T)(2.0 * hh - o);
+            const T xn = (T)(w * (opr * hh - rho * o) + omw * an);
+            if (r >= 0) xr[r] = xn;
+            else a.x[g] = xn;
+        });
+        __syncthreads();
+        inst_rows<BS, RS::RR, Acc>(I.levels, m, ga, I.A, lds, xbL, [&](int p, int r, Acc s) {
+            const int g = r0 + p;
+            const double an = (double)(r >= 0 ? y0r[r] : a.y0[g]), btg = (double)(r >= 0 ? btr[r] : a.bt[g]);
+            const double o = (double)yL[p];
+            const double hh = o + sig * (btg - (double)s);
+            yL[p] = (T)(w * (opr * hh - rho * o) + omw * an);
+        });
+        __syncthreads();
+        if (maskrow) maskrow += W;
+    }
+    if (I.levels)
+#pragma unroll
+        for (int r = 0; r < RS::RC; ++r)
+            if (tid + r * BS < n) a.x[c0 + tid + r * BS] = xr[r];
+}
+
+// state and anchor <- projected point (a restart)
+template <typename T, typename V, int BS>
+__device__ __forceinline__ void u_restart(const UArgs<T, V>& a, const Inst<T, V>& I) {
+    for (int p = opaque(threadIdx.x); p < I.n; p += BS) {
+        const T v = a.xhat[I.c0 + p];
+        a.x[I.c0 + p] = v;
+        a.x0[I.c0 + p] = v;
+    }
+    for (int p = opaque(threadIdx.x); p < I.m; p += BS) {
+        const T v = a.yhat[I.r0 + p];
+        I.yl[p] = v;
+        a.y0[I.r0 + p] = v;
     }
     __syncthreads();
 }
 
-template <typename T, typename V, typename Acc>
-__device__ void forward_instance(const UArgs<T, V>& a, const UInst<T, V>& u, T* yL, T* xbL, double* sh) {
-    const int tid = threadIdx.x, i = u.inst, B = a.B;
-    const InstSetup su = inst_setup<T, V>(a.M, u.r0, u.r1, u.c0, u.c1, a.d_row, a.d_col, a.pu, a.pav,
-                                          a.a_vs, a.at_vs, a.a_cl, a.at_cl, a.bt, a.ct, a.ruiz, a.pc,
-                                          a.power_iters, a.step_safety, xbL, yL, sh);
-    double omega = su.omega0;
+// Set-up of instance i: layout, scaling, scaled matrices and (if no schedule is
+// replayed) the first step sizes.  A kernel of its own, so that the registers
+// it wants are not taken from the iterations.
+template <typename T, typename V, int BS>
+__device__ void prepare_instance(const UArgs<T, V>& a, Inst<T, V>& I, int i, unsigned char* lds, double* sh) {
+    const InstSetup su = inst_setup<T, V, BS>(I, a.M, a.S, a.d_row, a.d_col, a.pu, a.pav, a.bt, a.ct, a.ruiz, a.pc,
+                                              a.power_iters, a.step_safety, lds, a.lds, sh);
+    if (threadIdx.x != 0) return;
+    a.levels[i] = I.levels;
+    if (a.replay) return;
+    a.eta[i] = su.eta;
+    a.omega0[i] = su.omega0;
+    a.taus[i] = su.eta / su.omega0;
+    a.sigmas[i] = su.eta * su.omega0;
+}
+
+// the layout and the matrices that prepare_instance left
+template <typename T, typename V, int BS>
+__device__ __forceinline__ void reload_instance(const UArgs<T, V>& a, Inst<T, V>& I, int i, unsigned char* lds) {
+    I.levels = uniform(a.levels[i]) != 0;
+    I.perm_r = a.S.perm_r + I.r0;
+    I.perm_c = a.S.perm_c + I.c0;
+    inst_load<T, V, BS>(I, a.M, a.S, lds, a.lds, true);
+}
+
+template <typename T, typename V, typename Acc, int BS>
+__device__ void forward_instance(const UArgs<T, V>& a, Inst<T, V>& I, int i, unsigned char* lds, double* sh) {
+    const int tid = threadIdx.x, B = a.B;
+    const int m = I.m, n = I.n, r0 = I.r0, c0 = I.c0;
+    reload_instance<T, V, BS>(a, I, i, lds);
+    const double eta = uniform(a.eta[i]);  // (unused in a replay)
+    double omega = uniform(a.omega0[i]);
     int epoch = 0;
-    double tau, sig;
-    if (a.replay) {
-        tau = a.taus[i];
-        sig = a.sigmas[i];
-    } else {
-        tau = su.eta / omega;
-        sig = su.eta * omega;
-        if (tid == 0) {
-            a.eta[i] = su.eta;
-            a.omega0[i] = su.omega0;
-            a.taus[i] = tau;
-            a.sigmas[i] = sig;
-        }
+    double tau = uniform(a.taus[i]), sig = uniform(a.sigmas[i]);
+    for (int p = tid; p < n; p += BS) {
+        a.x[c0 + p] = (T)0;
+        a.x0[c0 + p] = (T)0;
     }
-    for (int j = tid; j < u.n; j += kBatchBlock) {
-        a.x[u.c0 + j] = (T)0;
-        a.x0[u.c0 + j] = (T)0;
-    }
-    for (int r = tid; r < u.m; r += kBatchBlock) {
-        yL[r] = (T)0;
-        a.y0[u.r0 + r] = (T)0;
+    for (int p = tid; p < m; p += BS) {
+        I.yl[p] = (T)0;
+        a.y0[r0 + p] = (T)0;
     }
     __syncthreads();
     int64_t k = 0;
     double R0 = NAN, R_prev = INFINITY;
-    double nomax[1] = {0.0};
-    for (int t = 1; t <= a.K; ++t) {
+    for (int t = 1; t <= a.K;) {
         if ((t - 1) % a.ckpt == 0) {  // checkpoint of the state before iteration t
             const int seg = (t - 1) / a.ckpt;
-            for (int j = tid; j < u.n; j += kBatchBlock) {
-                a.cp_x[(int64_t)seg * a.N + u.c0 + j] = a.x[u.c0 + j];
-                a.cp_x0[(int64_t)seg * a.N + u.c0 + j] = a.x0[u.c0 + j];
+            for (int p = opaque(tid); p < n; p += BS) {
+                a.cp_x[(int64_t)seg * a.N + c0 + p] = a.x[c0 + p];
+                a.cp_x0[(int64_t)seg * a.N + c0 + p] = a.x0[c0 + p];
             }
-            for (int r = tid; r < u.m; r += kBatchBlock) {
-                a.cp_y[(int64_t)seg * a.Mrows + u.r0 + r] = yL[r];
-                a.cp_y0[(int64_t)seg * a.Mrows + u.r0 + r] = a.y0[u.r0 + r];
+            for (int p = opaque(tid); p < m; p += BS) {
+                a.cp_y[(int64_t)seg * a.Mrows + r0 + p] = I.yl[p];
+                a.cp_y0[(int64_t)seg * a.Mrows + r0 + p] = a.y0[r0 + p];
             }
             if (tid == 0) {
                 a.cp_k[seg * B + i] = (int32_t)k;
                 a.cp_ep[seg * B + i] = epoch;
             }
         }
+        // plain iterations up to the next checkpoint, evaluation or the end
+        if (k != 0 || a.replay) {
+            const int to_cp = a.ckpt - (t - 1) % a.ckpt, to_ev = a.E - (t - 1) % a.E - 1, to_end = a.K - t;
+            const int plain = min(to_cp, min(to_ev, to_end));
+            if (plain > 0) {
+                u_plain<T, V, Acc, BS>(a, I, lds, plain, k, tau, sig, nullptr);
+                t += plain;
+                k += plain;
+                if (plain == to_cp) continue;
+            }
+        }
         const bool at_eval = (t % a.E == 0) && t < a.K;
         const bool first = k == 0;
-        const bool need_q = !a.replay && (first || at_eval);
-        double q[4] = {0.0, 0.0, 0.0, 0.0};
-        u_iterate<T, V, Acc>(a, u, yL, xbL, k, tau, sig, need_q, at_eval, t == a.K, nullptr, q);
-        if (need_q) wg_reduce<4, 0>(q, nomax, sh);
-        if (!a.replay && first) R0 = sqrt(omega * q[0] + q[2] / omega);
+        const bool need_q = !a.replay && (first || at_eval) && t < a.K;
+        u_iterate<T, V, Acc, BS>(a, I, lds, k, tau, sig, need_q, at_eval, t == a.K, nullptr);
+        double qx[2] = {0.0, 0.0}, qy[2] = {0.0, 0.0};  // ||x - x^||^2, ||x^ - x0||^2 and the same of y
+        if (need_q) {
+            inst_sums<BS, 2>(n, sh, qx, [&](int j, double(&s)[2]) {
+                const double d = a.pu[c0 + j], e = a.xK[c0 + j];
+                s[0] += d * d;
+                s[1] += e * e;
+            });
+            inst_sums<BS, 2>(m, sh, qy, [&](int r, double(&s)[2]) {
+                const double d = a.pav[r0 + r], e = a.lbt[r0 + r];
+                s[0] += d * d;
+                s[1] += e * e;
+            });
+            __syncthreads();
+        }
+        if (!a.replay && first) R0 = uniform(sqrt(omega * qx[0] + qy[0] / omega));
         ++k;
+        const int te = t++;
         if (!at_eval) continue;
         bool restart;
         if (a.replay) {
-            restart = a.restart[(int64_t)(t - 1) * B + i] != 0;
+            restart = a.restart[(int64_t)(te - 1) * B + i] != 0;
         } else {
-            const double R = sqrt(omega * q[0] + q[2] / omega);
+            const double R = uniform(sqrt(omega * qx[0] + qy[0] / omega));
             restart = a.restarts && ((R <= a.beta_suff * R0) || (R <= a.beta_nec * R0 && R > R_prev) ||
-                                     ((double)k >= a.beta_art * (double)t));
+                                     ((double)k >= a.beta_art * (double)te));
             if (restart) {
-                const double dx = sqrt(q[1]), dy = sqrt(q[3]);
+                const double dx = sqrt(qx[1]), dy = sqrt(qy[1]);
                 if (dx > 1e-10 && dy > 1e-10)
-                    omega = exp(a.theta * log(dy / dx) + (1.0 - a.theta) * log(omega));
+                    omega = uniform(exp(a.theta * log(dy / dx) + (1.0 - a.theta) * log(omega)));
                 R_prev = INFINITY;
             } else {
                 R_prev = R;
@@ -255,151 +328,251 @@ __device__ void forward_instance(const UArgs<T, V>& a, const UInst<T, V>& u, T* 
         if (restart) {
             ++epoch;
             if (a.replay) {
-                tau = a.taus[(int64_t)epoch * B + i];
-                sig = a.sigmas[(int64_t)epoch * B + i];
+                tau = uniform(a.taus[(int64_t)epoch * B + i]);
+                sig = uniform(a.sigmas[(int64_t)epoch * B + i]);
             } else {
-                tau = su.eta / omega;
-                sig = su.eta * omega;
+                tau = uniform(eta / omega);
+                sig = uniform(eta * omega);
                 if (tid == 0) {
-                    a.restart[(int64_t)(t - 1) * B + i] = 1;
+                    a.restart[(int64_t)(te - 1) * B + i] = 1;
                     a.taus[(int64_t)epoch * B + i] = tau;
                     a.sigmas[(int64_t)epoch * B + i] = sig;
                 }
             }
-            u_restart<T, V>(a, u, yL);
+            u_restart<T, V, BS>(a, I);
             k = 0;
         }
     }
 }
 
-template <typename T, typename V, typename Acc>
-__device__ void backward_instance(const UArgs<T, V>& a, const UInst<T, V>& u, T* yL, T* xbL) {
-    const int tid = threadIdx.x, i = u.inst, B = a.B;
-    for (int j = tid; j < u.n; j += kBatchBlock) {
-        const int g = u.c0 + j;
+// The reverse sweep over iterations te, ..., tb + 1 of a segment, its adjoint
+// state in the workspace before and after, in the threads' registers between;
+// yL holds lam_yhat, xbL holds lam_g.  The iterations' numbers (k, tau, sigma,
+// restart) are loaded 64 at a time, one to a lane.
+template <typename T, typename V, typename Acc, int BS>
+__device__ __forceinline__ void u_reverse(const UArgs<T, V>& a, const Inst<T, V>& I, const unsigned char* lds, int i,
+                                          int tb, int te) {
+    typedef RegShape<V> RS;
+    const int tid = opaque(threadIdx.x), lane = tid & (kWave - 1);
+    const int m = I.m, n = I.n, c0 = I.c0, r0 = I.r0, B = a.B;
+    T *const lyhL = I.yl, *const lgL = I.xl;
+    const double rho = a.rho, opr = 1.0 + a.rho;
+    RegSide<V, RS::RC, RS::KC> gt;
+    RegSide<V, RS::RR, RS::KR> ga;
+    reg_load<BS, T>(gt, I.AT, lds, n, m);
+    reg_load<BS, T>(ga, I.A, lds, m, n);
+    T lxr[RS::RC], lx0r[RS::RC], lyr[RS::RR], ly0r[RS::RR];
+    double lcr[RS::RC], lbr[RS::RR];
+#pragma unroll
+    for (int r = 0; r < RS::RC; ++r) {
+        const int g = c0 + min(tid + r * BS, n - 1);
+        lxr[r] = a.lx[g];
+        lx0r[r] = a.lx0[g];
+        lcr[r] = a.lct[g];
+    }
+#pragma unroll
+    for (int r = 0; r < RS::RR; ++r) {
+        const int g = r0 + min(tid + r * BS, m - 1);
+        lyr[r] = a.ly[g];
+        ly0r[r] = a.ly0[g];
+        lbr[r] = a.lbt[g];
+    }
+    int kl = 0, rl = 0;
+    double wl = 1.0, tl = 0.0, sl = 0.0;
+    for (int t = te; t > tb; --t) {
+        const int back = te - t;
+        if ((back & (kWave - 1)) == 0) {
+            const int it = max(t - tb - 1 - lane, 0);
+            kl = a.kbuf[(int64_t)it * B + i];
+            tl = a.tbuf[(int64_t)it * B + i];
+            sl = a.sbuf[(int64_t)it * B + i];
+            rl = a.restart[(int64_t)(tb + it) * B + i];
+            wl = a.halpern ? ((double)kl + 1.0) / ((double)kl + 2.0) : 1.0;
+        }
+        const int src = back & (kWave - 1);
+        const bool rs = __builtin_amdgcn_readlane(rl, src) != 0;
+        const double w = lane_value(wl, src), omw = 1.0 - w;
+        const double tau = lane_value(tl, src), sig = lane_value(sl, src);
+        gt.pin();
+        ga.pin();
+        // (R1) rows: adjoint of y_hat, of the previous y (partial) and anchor
+        auto rows1 = [&](int p, T& lyT, T& ly0T, double& lb) {
+            const double ly = (double)lyT, ly0 = (double)ly0T;
+            const double lyh = rs ? ly + ly0 : w * opr * ly;
+            lyhL[p] = (T)lyh;
+            lyT = (T)((rs ? 0.0 : -w * rho * ly) + lyh);
+            ly0T = (T)(rs ? 0.0 : ly0 + omw * ly);
+            lb += sig * lyh;
+        };
+        int p = opaque(tid);
+        if (I.levels) {
+#pragma unroll
+            for (int r = 0; r < RS::RR; ++r)
+                if (tid + r * BS < m) rows1(tid + r * BS, lyr[r], ly0r[r], lbr[r]);
+            p += RS::RR * BS;
+        }
+        for (; p < m; p += BS) rows1(p, a.ly[r0 + p], a.ly0[r0 + p], a.lbt[r0 + p]);
+        __syncthreads();
+        // (C) columns: lam_xbar = -sigma A~^T lam_yhat, then extrapolation,
+        // projection and primal step
+        const uint64_t* mrow = a.masks + (int64_t)(t - tb - 1) * a.W + a.word_off[i];
+        inst_rows<BS, RS::RC, Acc>(I.levels, n, gt, I.AT, lds, lyhL, [&](int p, int r, Acc s) {
+            const int g = c0 + p;
+            const double lxbar = -sig * (double)s;
+            const double lx = (double)(r >= 0 ? lxr[r] : a.lx[g]), lx0 = (double)(r >= 0 ? lx0r[r] : a.lx0[g]);
+            double lxh = (rs ? lx + lx0 : w * opr * lx) + 2.0 * lxbar;
+            if (t == a.K) {
+                const int j = I.column(p);
+                lxh += a.d_col[j] * a.gx[j];
+            }
+            const bool on = (mrow[p >> 6] >> (p & 63)) & 1ull;
+            const double lv = on ? lxh : 0.0;
+            const double lg = -tau * lv;
+            const T nx = (T)((rs ? 0.0 : -w * rho * lx) - lxbar + lv), nx0 = (T)(rs ? 0.0 : lx0 + omw * lx);
+            if (r >= 0) {
+                lxr[r] = nx;
+                lx0r[r] = nx0;
+                lcr[r] += lg;
+            } else {
+                a.lx[g] = nx;
+                a.lx0[g] = nx0;
+                a.lct[g] += lg;
+            }
+            lgL[p] = (T)lg;
+        });
+        __syncthreads();
+        // (R2) rows: lam_y -= A~ lam_g
+        inst_rows<BS, RS::RR, Acc>(I.levels, m, ga, I.A, lds, lgL, [&](int p, int r, Acc s) {
+            if (r >= 0) lyr[r] = (T)((double)lyr[r] - (double)s);
+            else a.ly[r0 + p] = (T)((double)a.ly[r0 + p] - (double)s);
+        });
+        // (the next iteration's rows write lyhL, read by nobody since the last
+        // barrier, and its columns lgL only after the next one)
+    }
+    __syncthreads();
+    if (I.levels) {
+#pragma unroll
+        for (int r = 0; r < RS::RC; ++r)
+            if (tid + r * BS < n) {
+                const int g = c0 + tid + r * BS;
+                a.lx[g] = lxr[r];
+                a.lx0[g] = lx0r[r];
+                a.lct[g] = lcr[r];
+            }
+#pragma unroll
+        for (int r = 0; r < RS::RR; ++r)
+            if (tid + r * BS < m) {
+                const int g = r0 + tid + r * BS;
+                a.ly[g] = lyr[r];
+                a.ly0[g] = ly0r[r];
+                a.lbt[g] = lbr[r];
+            }
+    }
+}
+
+template <typename T, typename V, typename Acc, int BS>
+__device__ void backward_instance(const UArgs<T, V>& a, Inst<T, V>& I, int i, unsigned char* lds) {
+    const int tid = threadIdx.x, B = a.B;
+    const int m = I.m, n = I.n, r0 = I.r0, c0 = I.c0;
+    reload_instance<T, V, BS>(a, I, i, lds);
+    for (int p = tid; p < n; p += BS) {
+        const int g = c0 + p;
         a.lx[g] = (T)0;
         a.lx0[g] = (T)0;
         a.lct[g] = 0.0;
     }
-    for (int r = tid; r < u.m; r += kBatchBlock) {
-        const int g = u.r0 + r;
+    for (int p = tid; p < m; p += BS) {
+        const int g = r0 + p;
         a.ly[g] = (T)0;
         a.ly0[g] = (T)0;
         a.lbt[g] = 0.0;
     }
-    const double rho = a.rho, opr = 1.0 + a.rho;
-    double qd[4];
     for (int seg = a.nseg - 1; seg >= 0; --seg) {
         const int tb = seg * a.ckpt, te = min(a.K, tb + a.ckpt);
         // restore the checkpoint and recompute the segment, keeping masks
-        for (int j = tid; j < u.n; j += kBatchBlock) {
-            a.x[u.c0 + j] = a.cp_x[(int64_t)seg * a.N + u.c0 + j];
-            a.x0[u.c0 + j] = a.cp_x0[(int64_t)seg * a.N + u.c0 + j];
+        for (int p = opaque(tid); p < n; p += BS) {
+            a.x[c0 + p] = a.cp_x[(int64_t)seg * a.N + c0 + p];
+            a.x0[c0 + p] = a.cp_x0[(int64_t)seg * a.N + c0 + p];
         }
-        for (int r = tid; r < u.m; r += kBatchBlock) {
-            yL[r] = a.cp_y[(int64_t)seg * a.Mrows + u.r0 + r];
-            a.y0[u.r0 + r] = a.cp_y0[(int64_t)seg * a.Mrows + u.r0 + r];
+        for (int p = opaque(tid); p < m; p += BS) {
+            I.yl[p] = a.cp_y[(int64_t)seg * a.Mrows + r0 + p];
+            a.y0[r0 + p] = a.cp_y0[(int64_t)seg * a.Mrows + r0 + p];
         }
-        int64_t k = a.cp_k[seg * B + i];
-        int epoch = a.cp_ep[seg * B + i];
+        int64_t k = uniform(a.cp_k[seg * B + i]);
+        int epoch = uniform(a.cp_ep[seg * B + i]);
         __syncthreads();
-        for (int t = tb + 1; t <= te; ++t) {
-            const int it = t - tb - 1;
-            const double tau = a.taus[(int64_t)epoch * B + i], sig = a.sigmas[(int64_t)epoch * B + i];
-            if (tid == 0) {
-                a.kbuf[(int64_t)it * B + i] = (int32_t)k;
-                a.tbuf[(int64_t)it * B + i] = tau;
-                a.sbuf[(int64_t)it * B + i] = sig;
+        for (int t = tb + 1; t <= te;) {
+            const double tau = uniform(a.taus[(int64_t)epoch * B + i]), sig = uniform(a.sigmas[(int64_t)epoch * B + i]);
+            // the iterations up to the next one that may restart, or te
+            const int to_ev = a.E - (t - 1) % a.E - 1;
+            const int plain = min(to_ev, te - t + 1);
+            auto note = [&](int it0, int cnt) {
+                for (int q = tid; q < cnt; q += BS) {
+                    a.kbuf[(int64_t)(it0 + q) * B + i] = (int32_t)(k + q);
+                    a.tbuf[(int64_t)(it0 + q) * B + i] = tau;
+                    a.sbuf[(int64_t)(it0 + q) * B + i] = sig;
+                }
+            };
+            uint64_t* const masks = a.masks + (int64_t)(t - tb - 1) * a.W + a.word_off[i];
+            if (plain > 0) {
+                note(t - tb - 1, plain);
+                u_plain<T, V, Acc, BS>(a, I, lds, plain, k, tau, sig, masks);
+                t += plain;
+                k += plain;
+                continue;
             }
+            note(t - tb - 1, 1);
             const bool rs = a.restart[(int64_t)(t - 1) * B + i] != 0;
-            u_iterate<T, V, Acc>(a, u, yL, xbL, k, tau, sig, false, rs, false,
-                            a.masks + (int64_t)it * a.W + a.word_off[i], qd);
+            u_iterate<T, V, Acc, BS>(a, I, lds, k, tau, sig, false, rs, false, masks);
+            ++t;
             ++k;
             if (rs) {
-                u_restart<T, V>(a, u, yL);
+                u_restart<T, V, BS>(a, I);
                 k = 0;
                 ++epoch;
             }
         }
-        __syncthreads();  // kbuf / tbuf / sbuf written by thread 0 are read by all
-        // reverse sweep over the segment; yL holds lam_yhat, xbL holds lam_g
-        T* lyhL = yL;
-        T* lgL = xbL;
-        for (int t = te; t > tb; --t) {
-            const int it = t - tb - 1;
-            const bool rs = a.restart[(int64_t)(t - 1) * B + i] != 0;
-            const int64_t kt = a.kbuf[(int64_t)it * B + i];
-            const double w = a.halpern ? (double)(kt + 1) / (double)(kt + 2) : 1.0;
-            const double omw = 1.0 - w;
-            const double tau = a.tbuf[(int64_t)it * B + i], sig = a.sbuf[(int64_t)it * B + i];
-            // (R1) rows: adjoint of y_hat, of the previous y (partial) and anchor
-            for (int r = tid; r < u.m; r += kBatchBlock) {
-                const int g = u.r0 + r;
-                const double ly = (double)a.ly[g], ly0 = (double)a.ly0[g];
-                const double lyh = rs ? ly + ly0 : w * opr * ly;
-                lyhL[r] = (T)lyh;
-                a.ly[g] = (T)((rs ? 0.0 : -w * rho * ly) + lyh);
-                a.ly0[g] = (T)(rs ? 0.0 : ly0 + omw * ly);
-                a.lbt[g] += sig * lyh;
-            }
-            __syncthreads();
-            // (C) columns: lam_xbar = -sigma A~^T lam_yhat, then extrapolation,
-            // projection and primal step
-            const uint64_t* mrow = a.masks + (int64_t)it * a.W + a.word_off[i];
-            for (int j = tid; j < u.n; j += kBatchBlock) {
-                const int g = u.c0 + j;
-                const Acc s =
-                    row_dot4<Acc>(a.at_vs, a.at_cl, lyhL, a.M.at_rowptr[g], a.M.at_rowptr[g + 1]);
-                const double lxbar = -sig * (double)s;
-                const double lx = (double)a.lx[g], lx0 = (double)a.lx0[g];
-                double lxh = (rs ? lx + lx0 : w * opr * lx) + 2.0 * lxbar;
-                if (t == a.K) lxh += a.d_col[g] * a.gx[g];
-                const bool on = (mrow[j >> 6] >> (j & 63)) & 1ull;
-                const double lv = on ? lxh : 0.0;
-                const double lg = -tau * lv;
-                a.lx[g] = (T)((rs ? 0.0 : -w * rho * lx) - lxbar + lv);
-                a.lx0[g] = (T)(rs ? 0.0 : lx0 + omw * lx);
-                a.lct[g] += lg;
-                lgL[j] = (T)lg;
-            }
-            __syncthreads();
-            // (R2) rows: lam_y -= A~ lam_g
-            for (int r = tid; r < u.m; r += kBatchBlock) {
-                const int g = u.r0 + r;
-                const Acc s = row_dot4<Acc>(a.a_vs, a.a_cl, lgL, a.M.a_rowptr[g], a.M.a_rowptr[g + 1]);
-                a.ly[g] = (T)((double)a.ly[g] - (double)s);
-            }
-            __syncthreads();
-        }
+        __syncthreads();  // the iterations' numbers and masks are read by all
+        u_reverse<T, V, Acc, BS>(a, I, lds, i, tb, te);
+        __syncthreads();
     }
-    for (int j = tid; j < u.n; j += kBatchBlock) a.gc[u.c0 + j] = a.d_col[u.c0 + j] * a.lct[u.c0 + j];
-    for (int r = tid; r < u.m; r += kBatchBlock) a.gb[u.r0 + r] = a.d_row[u.r0 + r] * a.lbt[u.r0 + r];
+    for (int p = opaque(tid); p < n; p += BS) {
+        const int j = I.column(p);
+        a.gc[j] = a.d_col[j] * a.lct[c0 + p];
+    }
+    for (int p = opaque(tid); p < m; p += BS) {
+        const int r = I.row(p);
+        a.gb[r] = a.d_row[r] * a.lbt[r0 + p];
+    }
     __syncthreads();
 }
 
-template <typename T, typename V, typename Acc, bool BACKWARD>
-__global__ __launch_bounds__(kBatchBlock) void k_unrolled(UArgs<T, V> a) {
-    extern __shared__ __align__(16) unsigned char smem[];
-    T* yL = (T*)smem;
-    T* xbL = yL + a.lds_m;
-    __shared__ double sh[8 * (kBatchBlock / kWave)];
+enum { kPrepare = 0, kForward = 1, kBackward = 2 };
+
+template <typename T, typename V, typename Acc, int BS, int PHASE>
+__global__ __launch_bounds__(BS, 4) void k_unrolled(UArgs<T, V> a) {
+    extern __shared__ __align__(16) unsigned char lds[];
+    __shared__ double sh[BS / kWave > 12 ? BS / kWave : 12];
     __shared__ int next;
     while (true) {
-        if (threadIdx.x == 0) next = atomicAdd(a.counter, 1);
+        if (threadIdx.x == 0) next = atomicAdd(a.counter + PHASE, 1);
         __syncthreads();
-        const int qi = next;
+        const int qi = __builtin_amdgcn_readfirstlane(next);
         __syncthreads();
         if (qi >= a.B) break;
-        UInst<T, V> u;
-        u.inst = qi;
-        u.r0 = a.row_off[qi];
-        u.r1 = a.row_off[qi + 1];
-        u.c0 = a.col_off[qi];
-        u.c1 = a.col_off[qi + 1];
-        u.m = u.r1 - u.r0;
-        u.n = u.c1 - u.c0;
-        if (BACKWARD) backward_instance<T, V, Acc>(a, u, yL, xbL);
-        else forward_instance<T, V, Acc>(a, u, yL, xbL, sh);
+        Inst<T, V> I;
+        I.r0 = uniform(a.row_off[qi]);
+        I.c0 = uniform(a.col_off[qi]);
+        I.m = uniform(a.row_off[qi + 1]) - I.r0;
+        I.n = uniform(a.col_off[qi + 1]) - I.c0;
+        I.z0 = uniform(a.M.a_rowptr[I.r0]);
+        I.nnz = uniform(a.M.a_rowptr[I.r0 + I.m]) - I.z0;
+        I.yl = (T*)lds;
+        I.xl = (T*)(lds + inst_align((I.m + 1) * (int)sizeof(T)));
+        if (PHASE == kPrepare) prepare_instance<T, V, BS>(a, I, qi, lds, sh);
+        else if (PHASE == kBackward) backward_instance<T, V, Acc, BS>(a, I, qi, lds);
+        else forward_instance<T, V, Acc, BS>(a, I, qi, lds, sh);
+        __syncthreads();  // the next instance takes over the LDS
     }
 }
 
@@ -415,7 +588,8 @@ struct TapeLayout {
     int32_t *row_off, *col_off, *word_off, *counter;
     double *d_row, *d_col, *pu, *pav, *eta, *omega0, *taus, *sigmas;
     void *a_vs, *at_vs, *bt, *ct;
-    uint16_t *a_cl, *at_cl;
+    uint16_t *a_cl, *at_cl, *perm_r, *perm_c;
+    int32_t* levels;
     int8_t* restart;
     void *cp_x, *cp_x0, *cp_y, *cp_y0;
     int32_t *cp_k, *cp_ep;
@@ -458,6 +632,9 @@ static TapeLayout carve_tape(void* base, size_t cap, const mipdhg_batch& bt, int
     t.at_vs = cv.take<char>(nnz * vs);
     t.a_cl = cv.take<uint16_t>(nnz);
     t.at_cl = cv.take<uint16_t>(nnz);
+    t.perm_r = cv.take<uint16_t>(m);
+    t.perm_c = cv.take<uint16_t>(n);
+    t.levels = cv.take<int32_t>(B);
     t.bt = cv.take<char>(m * ts);
     t.ct = cv.take<char>(n * ts);
     t.restart = cv.take<int8_t>((size_t)K * B);
@@ -516,6 +693,24 @@ static int check_unrolled(const mipdhg_batch* bt, const mipdhg_options* o, int K
     return 0;
 }
 
+template <typename T, typename V, typename Acc, int BS, int PHASE>
+static int launch_phase(const UArgs<T, V>& a, int cus, hipStream_t s) {
+    int per_cu = 1;
+    MIP_HIP(hipFuncSetAttribute((const void*)k_unrolled<T, V, Acc, BS, PHASE>,
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 162000));
+    MIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_unrolled<T, V, Acc, BS, PHASE>, BS, a.lds));
+    const int grid = std::max(1, std::min(a.B, cus * std::max(per_cu, 1)));
+    hipLaunchKernelGGL((k_unrolled<T, V, Acc, BS, PHASE>), dim3(grid), dim3(BS), a.lds, s, a);
+    MIP_LAUNCH_CHECK();
+    return 0;
+}
+template <typename T, typename V, typename Acc, int BS>
+static int launch_unrolled(const UArgs<T, V>& a, int cus, bool backward, hipStream_t s) {
+    if (backward) return launch_phase<T, V, Acc, BS, kBackward>(a, cus, s);
+    if (int rc = launch_phase<T, V, Acc, BS, kPrepare>(a, cus, s)) return rc;
+    return launch_phase<T, V, Acc, BS, kForward>(a, cus, s);
+}
+
 template <typename T, typename V, typename Acc>
 static int unrolled_impl(const mipdhg_batch& bt, const mipdhg_options& o, int K, int ckpt, void* tape,
                          size_t tape_bytes, hipStream_t stream, bool backward, int replay, const double* gx,
@@ -530,7 +725,7 @@ static int unrolled_impl(const mipdhg_batch& bt, const mipdhg_options& o, int K,
         max_m = std::max(max_m, bt.row_off[i + 1] - bt.row_off[i]);
         max_n = std::max(max_n, bt.col_off[i + 1] - bt.col_off[i]);
     }
-    const int lds = (int)(((size_t)max_m + (size_t)max_n) * sizeof(T) + 16);
+    const int lds = (int)(((size_t)max_m + (size_t)max_n) * sizeof(T) + 16);  // the vectors'
     if (lds > 150 * 1024 || max_m > kInstMaxDim || max_n > kInstMaxDim)
         return set_error("instance too large for LDS (%d bytes)", lds), MIPDHG_ERR_UNSUPPORTED;
     const mipdhg_lp& lp = bt.whole;
@@ -569,8 +764,6 @@ static int unrolled_impl(const mipdhg_batch& bt, const mipdhg_options& o, int K,
     a.nseg = t.nseg;
     a.nep = t.nep;
     a.W = t.W;
-    a.lds_m = max_m;
-    a.lds_n = max_n;
     a.replay = replay;
     a.N = lp.n;
     a.Mrows = lp.m;
@@ -582,10 +775,8 @@ static int unrolled_impl(const mipdhg_batch& bt, const mipdhg_options& o, int K,
     a.d_col = t.d_col;
     a.pu = t.pu;
     a.pav = t.pav;
-    a.a_vs = (V*)t.a_vs;
-    a.at_vs = (V*)t.at_vs;
-    a.a_cl = t.a_cl;
-    a.at_cl = t.at_cl;
+    a.S = InstStore<V>{(V*)t.a_vs, (V*)t.at_vs, t.a_cl, t.at_cl, t.perm_r, t.perm_c};
+    a.levels = t.levels;
     a.bt = (T*)t.bt;
     a.ct = (T*)t.ct;
     a.eta = t.eta;
@@ -630,24 +821,36 @@ static int unrolled_impl(const mipdhg_batch& bt, const mipdhg_options& o, int K,
     a.power_iters = o.power_iters;
     a.halpern = o.halpern;
     a.restarts = o.restarts;
-    int dev = 0, cus = 256, per_cu = 1;
+    int dev = 0, cus = 256;
     MIP_HIP(hipGetDevice(&dev));
     MIP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    if (backward) {
-        MIP_HIP(hipFuncSetAttribute((const void*)k_unrolled<T, V, Acc, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    lds));
-        MIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_unrolled<T, V, Acc, true>, kBatchBlock, lds));
-    } else {
-        MIP_HIP(hipFuncSetAttribute((const void*)k_unrolled<T, V, Acc, false>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, lds));
-        MIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_unrolled<T, V, Acc, false>, kBatchBlock, lds));
-    }
-    const int grid = std::max(1, std::min(B, cus * std::max(per_cu, 1)));
+    // One launch of workgroups shaped for the largest instance: with no more
+    // instances than compute units about one thread per column and all the
+    // LDS the instance can use; with more, as many waves as keep 16 on a
+    // compute unit (see kClassBs in batched.hip).
+    int64_t full[3] = {0, 0, 0};
+    const int bs[3] = {1024, 256, 64};
+    const int64_t share[3] = {162000, 40400, 9700};
+    for (int c = 0; c < 3; ++c)
+        for (int i = 0; i < B; ++i) {
+            typedef RegShape<V> RS;
+            const int mi = bt.row_off[i + 1] - bt.row_off[i], ni = bt.col_off[i + 1] - bt.col_off[i];
+            const int64_t zi = bt.nnz_off[i + 1] - bt.nnz_off[i];
+            const int64_t nreg = std::min(ni, RS::RC * bs[c]) * std::min<int64_t>(zi / ni, RS::KC) +
+                                 std::min(mi, RS::RR * bs[c]) * std::min<int64_t>(zi / mi, RS::KR);
+            full[c] = std::max(full[c], inst_full_bytes(mi, ni, zi, sizeof(T), sizeof(V), nreg));
+        }
+    int c;
+    if (B <= cus) c = max_n <= 64 ? 2 : max_n <= 512 ? 1 : 0;
+    else c = full[2] <= share[2] ? 2 : full[1] <= share[1] ? 1 : 0;
+    a.lds = (int)std::max<int64_t>(inst_vec_bytes(max_m, max_n, sizeof(T)),
+                                   std::min(full[c], B <= cus ? share[0] : share[c]));
     hipLaunchKernelGGL(k_zero_bytes, dim3(1), dim3(64), 0, stream, (uint8_t*)t.counter, (int64_t)256);
-    if (backward)
-        hipLaunchKernelGGL((k_unrolled<T, V, Acc, true>), dim3(grid), dim3(kBatchBlock), lds, stream, a);
-    else
-        hipLaunchKernelGGL((k_unrolled<T, V, Acc, false>), dim3(grid), dim3(kBatchBlock), lds, stream, a);
+    int rc;
+    if (c == 0) rc = launch_unrolled<T, V, Acc, 1024>(a, cus, backward, stream);
+    else if (c == 1) rc = launch_unrolled<T, V, Acc, 256>(a, cus, backward, stream);
+    else rc = launch_unrolled<T, V, Acc, 64>(a, cus, backward, stream);
+    if (rc) return rc;
     MIP_LAUNCH_CHECK();
     MIP_HIP(hipStreamSynchronize(stream));
     return 0;

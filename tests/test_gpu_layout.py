@@ -1,0 +1,114 @@
+"""The layouts and workgroup classes of instances held by one workgroup.
+
+Shapes at the edges: one row or column, columns and rows without entries,
+sizes beside multiples of a wave and of three, a row and a column too long for
+the level layout, more rows than it takes, and more entries than LDS holds.
+FP64 is compared with the oracle at the tolerances of the other per-iterate
+tests (1e-10 over at most 150 iterations, 1e-8 for gradients).  An instance's
+bits must not depend on the workgroup that held it: alone, in a batch of more
+instances than compute units (other classes), and under a launch split.
+"""
+import numpy as np
+import pytest
+
+import lpgen
+import oracle
+from oracle.pdhg import OracleOptions
+
+pytestmark = pytest.mark.gpu
+
+P = pytest.importorskip("paper_2603_03150_amd")
+torch = pytest.importorskip("torch")
+
+
+def _np(t):
+    return t.detach().cpu().numpy()
+
+
+def _rel(a, b):
+    return float(np.linalg.norm(a - b)) / max(1.0, float(np.linalg.norm(b)))
+
+
+def _planted(name, m, counts, extra=None):
+    """counts[j] distinct uniform rows in column j; extra(j) more of them."""
+    rng = lpgen.rng_for(77, len(name), m, len(counts))
+    cols = []
+    for j, k in enumerate(counts):
+        rows = set(rng.choice(m, size=min(int(k), m), replace=False).tolist())
+        if extra is not None:
+            rows |= set(extra(j))
+        cols.append(sorted(rows))
+    cnt = np.array([len(r) for r in cols], dtype=np.int64)
+    rows = np.array([i for r in cols for i in r], dtype=np.int64)
+    return lpgen.planted_from_columns(m, cnt, rows, rng.standard_normal(rows.size), rng, name=name)
+
+
+def _shape(name):
+    rng = lpgen.rng_for(78, len(name))
+    if name == "one":
+        return _planted(name, 1, [1])
+    if name == "one_row":
+        return _planted(name, 1, [1] * 65)
+    if name == "ragged_63":  # columns and rows without entries
+        return _planted(name, 63, rng.integers(0, 4, size=64))
+    if name == "ragged_193":  # past three columns to a thread of one wave
+        return _planted(name, 65, rng.integers(0, 8, size=193))
+    if name == "wide_3073":  # past three columns to a thread of 1,024
+        return _planted(name, 1025, rng.integers(1, 6, size=3073))
+    if name == "long_row":  # 1,100 entries: CSR order
+        return _planted(name, 70, [3] * 1100, extra=lambda j: [0])
+    if name == "long_column":
+        return _planted(name, 1030, [4] * 2000, extra=lambda j: range(1030) if j == 7 else [])
+    if name == "many_rows":  # more rows than the level layout takes
+        return _planted(name, 8300, [60] * 300)
+    if name == "partial":  # a matrix that LDS holds in part
+        return _planted(name, 300, [24] * 2500)
+    raise ValueError(name)
+
+
+NAMES = ["one", "one_row", "ragged_63", "ragged_193", "wide_3073", "long_row", "long_column", "many_rows", "partial"]
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_batched_shape_matches_oracle_and_bits_do_not_depend_on_the_class(name):
+    lp, T = _shape(name), 70
+    alone = P.solve_batched(P.DeviceBatch.from_lps([lp]), 1e-14, "fp64", max_iter=T)
+    ref = oracle.solve(lp.A, lp.AT, lp.b, lp.c, 1e-14, opts=OracleOptions(max_iter=T))
+    assert alone.infos[0]["iters"] == ref.iters and alone.infos[0]["restarts"] == ref.restarts
+    assert _rel(_np(alone.x), ref.meas.x) <= 1e-10
+    assert _rel(_np(alone.y), ref.meas.y) <= 1e-10
+    fill = [lpgen.cfg4_instance(2000 + i, m) for i, m in enumerate([20, 90, 300] * 100)]
+    batch = P.DeviceBatch.from_lps([lp] + fill)
+    for prec in ("fp64", "fp32", "fp32acc32", "bf16"):
+        one = P.solve_batched(P.DeviceBatch.from_lps([lp]), 1e-14, prec, max_iter=T)
+        for split in (0, 1000):
+            many = P.solve_batched(batch, 1e-14, prec, max_iter=T, batch_split=split).split(batch, 0)
+            assert np.array_equal(_np(one.x), _np(many["x"])), (prec, split)
+            assert np.array_equal(_np(one.y), _np(many["y"])), (prec, split)
+
+
+@pytest.mark.parametrize("name", NAMES)
+def test_unrolled_shape_matches_oracle_and_bits_do_not_depend_on_the_class(name):
+    lp, K = _shape(name), 65
+    w = lpgen.rng_for(79, len(name)).standard_normal(lp.c.size)
+
+    def run(lps, prec):
+        batch = P.DeviceBatch.from_lps(lps)
+        umap = P.UnrolledMap(batch, K=K, ckpt_every=32, precision=prec)
+        c, b = batch.lp.c.clone(), batch.lp.b.clone()
+        xK, tape = umap.forward_raw(c, b)
+        g = torch.zeros_like(c)
+        g[:w.size] = torch.tensor(w, device="cuda")
+        gc, gb = umap.backward_raw(c, b, tape, g)
+        n, m = lp.c.size, lp.b.size
+        return _np(xK)[:n], _np(gc)[:n], _np(gb)[:m]
+
+    xK, gc, gb = run([lp], "fp64")
+    rc, rb, rx, _ = oracle.unrolled_grad(lp.A, lp.b, lp.c, K, w, OracleOptions())
+    assert _rel(xK, rx) <= 1e-10
+    assert _rel(gc, rc) <= 1e-8
+    assert _rel(gb, rb) <= 1e-8
+    fill = [lpgen.cfg4_instance(2000 + i, m) for i, m in enumerate([20, 90, 300] * 100)]
+    for prec in ("fp64", "fp32", "bf16"):
+        for a, b in zip(run([lp], prec), run([lp] + fill, prec)):
+            assert np.array_equal(a, b), prec
