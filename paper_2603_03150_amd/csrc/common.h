@@ -124,6 +124,18 @@ __device__ __forceinline__ T group_sum(T v) {
     return v;
 }
 
+// Lane l's value of v (l uniform), in scalar registers
+__device__ __forceinline__ double lane_value(double v, int l) {
+    union {
+        double d;
+        int i[2];
+    } u;
+    u.d = v;
+    u.i[0] = __builtin_amdgcn_readlane(u.i[0], l);
+    u.i[1] = __builtin_amdgcn_readlane(u.i[1], l);
+    return u.d;
+}
+
 // group_sum<64> of a double without the shuffles' trips through LDS: the
 // halves and rows are exchanged by lane swaps, and once a sum depends on the
 // lane modulo 2 k only, a rotation of a row by k lanes is the butterfly's

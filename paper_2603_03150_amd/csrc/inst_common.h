@@ -278,18 +278,6 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
     return (int64_t)((uint64_t)hi << 32 | lo);
 }
 
-// Lane l's value of v (l uniform), in scalar registers
-__device__ __forceinline__ double lane_value(double v, int l) {
-    union {
-        double d;
-        int i[2];
-    } u;
-    u.d = v;
-    u.i[0] = __builtin_amdgcn_readlane(u.i[0], l);
-    u.i[1] = __builtin_amdgcn_readlane(u.i[1], l);
-    return u.d;
-}
-
 // v, computed anew: what depends on it is not moved out of the surrounding
 // loops (addresses formed ahead of the iterations take registers from them)
 __device__ __forceinline__ int opaque(int v) {

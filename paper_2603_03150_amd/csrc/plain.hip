@@ -562,6 +562,317 @@ __global__ __launch_bounds__(kBlock) void k_iter_persist(IterArgs<T, V> a, TileP
 }
 
 // ---------------------------------------------------------------------------
+// small LPs: one workgroup holds the scaled matrix, both ways, in its LDS
+// ---------------------------------------------------------------------------
+// The iterations of a block between its first and its last (which record the
+// restart norms and the point), and the power iteration, as one launch each.
+// What bounds a small LP's step is not its data but the launches: two tiles of
+// work to a launch take 6.4 us, while on one compute unit with everything on
+// chip an iteration is two barriers and the instructions its 16 waves issue.
+// 200 rows of 12 and 500 columns of 5 entries, FP64: 13 us an iteration by
+// launches; so 2.3 us with one lane to a row and all entries read from LDS, 2.1
+// with up to eight lanes, 1.24 with each lane's first four entries in registers
+// (and 256 iterations with their set-up 6.5 -> 1.77 ms).
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallRows = 2;  // rows (and columns) a thread holds
+
+struct SmallMat {  // one side of the scaled copy, as the tile kernels read it
+    TilePlan tp;
+    const int32_t* col;
+    int32_t dim;
+};
+
+struct SmallLds {
+    int vy, vx, av, atv, ac, atc, bytes;
+};
+__host__ __device__ inline SmallLds small_lds(int64_t m, int64_t n, int64_t nnz, int ts, int vs) {
+    auto up = [](int64_t b) { return (int)((b + 15) & ~(int64_t)15); };
+    SmallLds L;
+    L.vy = 0;
+    L.vx = L.vy + up((m + 1) * ts);
+    L.av = L.vx + up((n + 1) * ts);
+    L.atv = L.av + up(nnz * vs);
+    L.ac = L.atv + up(nnz * vs);
+    L.atc = L.ac + up(nnz * 2);
+    L.bytes = L.atc + up(nnz * 2);
+    return L;
+}
+
+// The side's entries into LDS in row order (from the sorted layout by slot)
+template <typename V>
+__device__ __forceinline__ void small_fill(const SmallMat& s, const V* val, V* lv, uint16_t* lc) {
+    for (int t = 0; t < s.tp.ntiles; ++t) {
+        const int4 d = s.tp.desc[t];
+        const int b = d.z, nz = d.w - d.z;
+        const bool sorted = s.tp.slot && nz <= s.tp.tile_nnz;
+        for (int j = threadIdx.x; j < nz; j += kSmallBlock) {
+            const int e = b + (sorted ? (int)s.tp.slot[b + j] : j);
+            lv[e] = val[b + j];
+            lc[e] = (uint16_t)s.col[b + j];
+        }
+    }
+}
+
+// Lanes to a row (a power of two, as its logarithm): as many as give every
+// thread work, at most eight; with one, the longest row's chain of gathers is
+// the iteration's time.
+__device__ __forceinline__ int small_lanes(int dim) {
+    int lg = 0;
+    while (lg < 3 && (dim << (lg + 1)) <= kSmallBlock) ++lg;
+    return lg;
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_other(double v) {
+    union {
+        double d;
+        int i[2];
+    } u;
+    u.d = v;
+    u.i[0] = __builtin_amdgcn_update_dpp(u.i[0], u.i[0], CTRL, 0xf, 0xf, false);
+    u.i[1] = __builtin_amdgcn_update_dpp(u.i[1], u.i[1], CTRL, 0xf, 0xf, false);
+    return u.d;
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_other(float v) {
+    return __int_as_float(
+        __builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xf, 0xf, false));
+}
+
+// One side's rows as the lanes of a workgroup hold them: 2^lg lanes to a row,
+// lane l of them with every 2^lg-th entry from the l-th on; its first
+// kSmallRegs entries of each row are in registers (absent ones a zero value
+// and the vector's extra zero entry), the others are read from LDS eight at a
+// time.  The lanes' sums are added pairwise and all of them get the result.
+constexpr int kSmallRegs = 4;
+template <typename V>
+struct SmallSide {
+    V v[kSmallRows][kSmallRegs];
+    int c[kSmallRows][kSmallRegs];
+    int k[kSmallRows], e[kSmallRows];  // what is left: entries k, k + 2^lg, ... below e
+    int lg;
+    __device__ __forceinline__ int row() const { return (int)threadIdx.x >> lg; }
+    __device__ __forceinline__ bool first() const { return (threadIdx.x & ((1u << lg) - 1)) == 0; }
+    __device__ __forceinline__ void load(const SmallMat& s, const V* lv, const uint16_t* lc, int other) {
+        const int step = 1 << lg;
+#pragma unroll
+        for (int r = 0; r < kSmallRows; ++r) {
+            const int i = row() + r * kSmallBlock;
+            k[r] = e[r] = 0;
+            if (i < s.dim) {
+                k[r] = s.tp.rowptr[i] + ((int)threadIdx.x & (step - 1));
+                e[r] = s.tp.rowptr[i + 1];
+            }
+#pragma unroll
+            for (int q = 0; q < kSmallRegs; ++q) {
+                const bool in = k[r] < e[r];
+                v[r][q] = in ? lv[k[r]] : (V)0;
+                c[r][q] = in ? (int)lc[k[r]] : other;
+                k[r] += step;
+            }
+        }
+    }
+    template <typename Acc, typename X>
+    __device__ __forceinline__ Acc dot(const V* lv, const uint16_t* lc, const X* xl, int r) const {
+        Acc acc = 0;
+        Acc x[8];
+#pragma unroll
+        for (int q = 0; q < kSmallRegs; ++q) x[q] = (Acc)xl[c[r][q]];
+#pragma unroll
+        for (int q = 0; q < kSmallRegs; ++q) acc += (Acc)ld_val_cached(&v[r][q], 0) * x[q];
+        const int step = 1 << lg;
+        for (int kk = k[r]; kk < e[r]; kk += 8 * step) {
+            int cc[8];
+            Acc vv[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int at = min(kk + q * step, e[r] - 1);
+                cc[q] = lc[at];
+                vv[q] = (Acc)ld_val_cached(lv, at);
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) x[q] = (Acc)xl[cc[q]];
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                if (kk + q * step < e[r]) acc += vv[q] * x[q];
+        }
+        if (lg > 0) acc += dpp_other<0xB1>(acc);   // quad_perm [1, 0, 3, 2]
+        if (lg > 1) acc += dpp_other<0x4E>(acc);   // quad_perm [2, 3, 0, 1]
+        if (lg > 2) acc += dpp_other<0x141>(acc);  // row_half_mirror
+        return acc;
+    }
+};
+
+// `count` iterations from a.it on, none of them a block's first or last: the
+// arithmetic of IterEpi, the state in registers and LDS
+template <typename T, typename V, typename Acc, bool GENP, bool GEND>
+__global__ __launch_bounds__(kSmallBlock) void k_small_iters(IterArgs<T, V> p, IterArgs<T, V> d, SmallMat ma,
+                                                             SmallMat mat, int count) {
+    const Ctrl* ctrl = p.ctrl;
+    if (ctrl->status != ST_RUNNING) return;
+    extern __shared__ __align__(16) unsigned char smem_t[];
+    const int tid = threadIdx.x, m = ma.dim, n = mat.dim;
+    const SmallLds L = small_lds(m, n, ma.tp.rowptr[m], sizeof(T), sizeof(V));
+    T* const vy = (T*)(smem_t + L.vy);
+    T* const vx = (T*)(smem_t + L.vx);
+    V* const av = (V*)(smem_t + L.av);
+    V* const atv = (V*)(smem_t + L.atv);
+    uint16_t* const ac = (uint16_t*)(smem_t + L.ac);
+    uint16_t* const atc = (uint16_t*)(smem_t + L.atc);
+    SmallSide<V> sa, st;
+    sa.lg = small_lanes(m);
+    st.lg = small_lanes(n);
+    const int it0 = sa.row(), jt = st.row();
+    const bool first_r = sa.first(), first_c = st.first();
+    small_fill(ma, d.val, av, ac);
+    small_fill(mat, p.val, atv, atc);
+    T u[kSmallRows], an[kSmallRows], rc[kSmallRows], lo[kSmallRows], hi[kSmallRows], rb[kSmallRows], ay[kSmallRows];
+    int sense[kSmallRows];
+#pragma unroll
+    for (int r = 0; r < kSmallRows; ++r) {
+        const int j = min(jt + r * kSmallBlock, n - 1), i = min(it0 + r * kSmallBlock, m - 1);
+        u[r] = p.state[j];
+        an[r] = p.anchor[j];
+        rc[r] = p.rhs[j];
+        lo[r] = GENP ? p.lo[j] : (T)0;
+        hi[r] = GENP ? p.hi[j] : (T)0;
+        rb[r] = d.rhs[i];
+        ay[r] = GEND ? d.anchor[i] : (T)0;
+        sense[r] = GEND ? d.sense[i] : 0;
+    }
+    for (int i = tid; i < m; i += kSmallBlock) vy[i] = d.state[i];
+    const double tau = ctrl->tau, sig = ctrl->sigma, rho = p.rho, opr = 1.0 + p.rho;
+    const int64_t k0 = ctrl->k_base + p.it;
+    if (tid == 0) {
+        vy[m] = (T)0;
+        vx[n] = (T)0;
+    }
+    __syncthreads();
+    sa.load(ma, av, ac, n);
+    st.load(mat, atv, atc, m);
+    double wl = 1.0;  // lane l: the Halpern weight of iteration l of each 64
+    for (int it = 0; it < count; ++it) {
+        if (p.halpern && (it & (kWave - 1)) == 0) {
+            const double kl = (double)(k0 + it + (tid & (kWave - 1)));
+            wl = (kl + 1.0) / (kl + 2.0);
+        }
+        const double w = lane_value(wl, it & (kWave - 1));
+#pragma unroll
+        for (int r = 0; r < kSmallRows; ++r) {
+            const int j = jt + r * kSmallBlock;
+            if (j >= n) break;
+            const Acc sum = st.template dot<Acc>(atv, atc, vy, r);
+            const double o = (double)u[r], a0 = (double)an[r];
+            double dh = o - tau * ((double)rc[r] - (double)sum);
+            if (GENP) {
+                const double l = (double)lo[r] - a0, h = (double)hi[r] - a0;
+                dh = dh < l ? l : (dh > h ? h : dh);
+            } else {
+                dh = dh < -a0 ? -a0 : dh;
+            }
+            if (first_c) vx[j] = (T)(2.0 * dh - o);
+            u[r] = (T)(w * (opr * dh - rho * o));
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kSmallRows; ++r) {
+            const int i = it0 + r * kSmallBlock;
+            if (i >= m) break;
+            const Acc sum = sa.template dot<Acc>(av, ac, vx, r);
+            const double o = (double)vy[i], a0 = (double)ay[r];
+            double dh = o + sig * ((double)rb[r] - (double)sum);
+            if (GEND) {
+                if (sense[r] == MIPDHG_SENSE_GE) dh = dh < -a0 ? -a0 : dh;
+                else if (sense[r] == MIPDHG_SENSE_LE) dh = dh > -a0 ? -a0 : dh;
+            }
+            if (first_r) vy[i] = (T)(w * (opr * dh - rho * o));
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < kSmallRows; ++r) {
+        const int j = jt + r * kSmallBlock;
+        if (first_c && j < n) p.state_out[j] = u[r];
+    }
+    for (int i = tid; i < m; i += kSmallBlock) d.state_out[i] = vy[i];
+}
+
+// The whole power iteration: hist[k] = ||A~ v_k||^2 for k = 0, ..., iters,
+// v_0 constant, the vectors rounded to T and the sums in float64 as in
+// k_spmv_copy and k_normalize (the norms are added up in another order)
+template <typename T, typename V>
+__global__ __launch_bounds__(kSmallBlock) void k_small_power(SmallMat ma, SmallMat mat, const V* a_val,
+                                                             const V* at_val, int iters, double v0, double* hist) {
+    extern __shared__ __align__(16) unsigned char smem_t[];
+    __shared__ double part[2][kSmallBlock / kWave];
+    const int tid = threadIdx.x, m = ma.dim, n = mat.dim;
+    const SmallLds L = small_lds(m, n, ma.tp.rowptr[m], sizeof(T), sizeof(V));
+    T* const vy = (T*)(smem_t + L.vy);
+    T* const vx = (T*)(smem_t + L.vx);
+    V* const av = (V*)(smem_t + L.av);
+    V* const atv = (V*)(smem_t + L.atv);
+    uint16_t* const ac = (uint16_t*)(smem_t + L.ac);
+    uint16_t* const atc = (uint16_t*)(smem_t + L.atc);
+    SmallSide<V> sa, st;
+    sa.lg = small_lanes(m);
+    st.lg = small_lanes(n);
+    const int it0 = sa.row(), jt = st.row();
+    const bool first_r = sa.first(), first_c = st.first();
+    small_fill(ma, a_val, av, ac);
+    small_fill(mat, at_val, atv, atc);
+    for (int j = tid; j < n; j += kSmallBlock) vx[j] = (T)v0;
+    // (each buffer of partial sums is written again only two barriers later)
+    auto total = [&](double v, int buf) {
+        v = wave_sum(v);
+        if ((tid & (kWave - 1)) == 0) part[buf][tid / kWave] = v;
+        __syncthreads();
+        double t = part[buf][0];
+        for (int w = 1; w < kSmallBlock / kWave; ++w) t += part[buf][w];
+        return t;
+    };
+    if (tid == 0) {
+        vy[m] = (T)0;
+        vx[n] = (T)0;
+    }
+    __syncthreads();
+    sa.load(ma, av, ac, n);
+    st.load(mat, atv, atc, m);
+    for (int k = 0; k <= iters; ++k) {
+        double q = 0.0;
+#pragma unroll
+        for (int r = 0; r < kSmallRows; ++r) {
+            const int i = it0 + r * kSmallBlock;
+            if (i >= m) break;
+            const double t = sa.template dot<double>(av, ac, vx, r);
+            if (first_r) {
+                vy[i] = (T)t;
+                q += t * t;
+            }
+        }
+        q = total(q, 0);
+        if (tid == 0) hist[k] = q;
+        if (k == iters) break;
+        T un[kSmallRows];
+        q = 0.0;
+#pragma unroll
+        for (int r = 0; r < kSmallRows; ++r) {
+            un[r] = (T)0;
+            if (jt + r * kSmallBlock >= n) break;
+            const double t = st.template dot<double>(atv, atc, vy, r);
+            un[r] = (T)t;
+            if (first_c) q += t * t;
+        }
+        const double nrm = sqrt(total(q, 1));
+        if (nrm != 0.0) {
+#pragma unroll
+            for (int r = 0; r < kSmallRows; ++r)
+                if (first_c && jt + r * kSmallBlock < n) vx[jt + r * kSmallBlock] = (T)((double)un[r] / nrm);
+        }
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------------------
 // dual step on the panel layout (panel.h)
 // ---------------------------------------------------------------------------
 typedef float pf4 __attribute__((ext_vector_type(4)));
@@ -1938,6 +2249,54 @@ struct Solver {
         }
     }
     bool adaptive() const { return o.step_rule == 1; }
+    // Small LPs run a block's middle iterations and the power iteration in one
+    // workgroup: both copies of the matrix fit its LDS, no thread has more
+    // than kSmallRows rows or columns, and no row is so long that its lanes
+    // take more than the tile kernels' 13 us for an iteration (192 entries in
+    // one lane at 0.15 us to eight of them, 3.6 us).  The adaptive step, the
+    // average of an epoch's points and the panel layouts keep their kernels.
+    static constexpr int kSmallRowLen = 192;
+    static constexpr int kSmallLdsMax = 155 * 1024;
+    int64_t longest = 0;  // of the rows of A and of A^T
+    SmallLds small_layout() const { return small_lds(lp.m, lp.n, lp.nnz, sizeof(T), sizeof(V)); }
+    bool small() const {
+        const int64_t cap = (int64_t)kSmallRows * kSmallBlock;
+        return !adaptive() && !o.restart_avg && !panel() && lp.m <= cap && lp.n <= cap && longest <= kSmallRowLen &&
+               lp.nnz <= kSmallLdsMax && small_layout().bytes <= kSmallLdsMax;
+    }
+    SmallMat small_side(bool a) const {
+        SmallMat s{a ? ta : tat, a ? (sorted() ? w.col_a : lp.a_col) : (sorted() ? w.col_at : lp.at_col),
+                   a ? lp.m : lp.n};
+        s.tp.slot = sorted() ? (a ? w.slot_a : w.slot_at) : nullptr;
+        return s;
+    }
+    int allow_small_lds() {
+        const void* ks[] = {(const void*)k_small_iters<T, V, Acc, false, false>,
+                            (const void*)k_small_iters<T, V, Acc, true, false>,
+                            (const void*)k_small_iters<T, V, Acc, false, true>,
+                            (const void*)k_small_iters<T, V, Acc, true, true>, (const void*)k_small_power<T, V>};
+        for (const void* k : ks)
+            MIP_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLdsMax));
+        return 0;
+    }
+    int launch_small(int it, int count) {
+        IterArgs<T, V> p, d;
+        fill_iter(p, true, it, 0);
+        fill_iter(d, false, it, 0);
+        const SmallMat ma = small_side(true), mat = small_side(false);
+        const int lds = small_layout().bytes;
+        const bool gp = gen_primal(), gd = gen_dual();
+#define MIP_SMALL(GP, GD)                                                                                         \
+    hipLaunchKernelGGL((k_small_iters<T, V, Acc, GP, GD>), dim3(1), dim3(kSmallBlock), lds, stream, p, d, ma, mat, \
+                       count)
+        if (gp && gd) MIP_SMALL(true, true);
+        else if (gp) MIP_SMALL(true, false);
+        else if (gd) MIP_SMALL(false, true);
+        else MIP_SMALL(false, false);
+#undef MIP_SMALL
+        MIP_LAUNCH_CHECK();
+        return 0;
+    }
     // One of the tile kernels: one workgroup per tile or persistent, 8 or 16
     // products in flight per thread, row-major or sorted layout.
     template <bool PRIMAL>
@@ -2199,6 +2558,10 @@ struct Solver {
     int enqueue_block(int nit, int64_t t_first, bool trace) {
         int rc;
         for (int it = 0; it < nit; ++it) {
+            if (it == 1 && nit > 2 && small() && !trace && !timing) {
+                if ((rc = launch_small(1, nit - 2))) return rc;
+                it = nit - 1;
+            }
             const bool last = it == nit - 1;
             const int flags = (it == 0 ? F_FIRST : 0) | (last ? (F_EVAL | F_HAT) : 0) | (trace ? F_HAT : 0);
             if (timing) MIP_HIP(hipEventRecord(tev[3 * it], stream));
@@ -2321,6 +2684,9 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
         S.tat = make_tile_plan(lp.at_rowptr, w.tiles_at, (int32_t)(tat.size() / 4), lp.n, tnz_t, trows_t, srow_t);
         if ((rc = S.allow_tile_lds())) return rc;
         if ((rc = S.plan_persistent())) return rc;
+        for (int64_t i = 0; i < m; ++i) S.longest = std::max<int64_t>(S.longest, rpa[i + 1] - rpa[i]);
+        for (int64_t j = 0; j < n; ++j) S.longest = std::max<int64_t>(S.longest, rpat[j + 1] - rpat[j]);
+        if (S.small() && (rc = S.allow_small_lds())) return rc;
         MIP_HIP(hipStreamSynchronize(stream));  // host vectors go out of scope
     }
     const int gta = S.ta.ntiles, gtat = S.tat.ntiles;
@@ -2422,7 +2788,12 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
 
     // --- power iteration for sigma_hat = ||D_r A D_c||_2 (not for the
     // adaptive step, which starts from the largest scaled entry instead)
-    if (!S.adaptive()) {
+    if (S.small()) {
+        hipLaunchKernelGGL((k_small_power<T, V>), dim3(1), dim3(kSmallBlock), S.small_layout().bytes, stream,
+                           S.small_side(true), S.small_side(false), (const V*)w.a_vs, (const V*)w.at_vs,
+                           o.power_iters, 1.0 / sqrt((double)n), w.hist);
+        MIP_LAUNCH_CHECK();
+    } else if (!S.adaptive()) {
         const double v0 = 1.0 / sqrt((double)n);
         hipLaunchKernelGGL((k_fill_t<T>), dim3(grid_for(n)), dim3(kBlock), 0, stream, (T*)w.pv, n, (T)v0);
         // on the scaled iteration copies (tile plans with their layout)

@@ -112,3 +112,46 @@ def test_unrolled_shape_matches_oracle_and_bits_do_not_depend_on_the_class(name)
     for prec in ("fp64", "fp32", "bf16"):
         for a, b in zip(run([lp], prec), run([lp] + fill, prec)):
             assert np.array_equal(a, b), prec
+
+
+def _small(name):
+    rng = lpgen.rng_for(80, len(name))
+    if name == "one":
+        return _planted(name, 1, [1])
+    if name == "empty_rows_and_columns":
+        return _planted(name, 40, rng.integers(0, 3, size=64))
+    if name == "lanes_8":  # a row to eight lanes up to 128 of them, with long rows
+        return _planted(name, 128, rng.integers(3, 9, size=130))
+    if name == "lanes_4":
+        return _planted(name, 129, [4] * 257)
+    if name == "lanes_2":
+        return _planted(name, 257, [4] * 513)
+    if name == "two_rows":  # more columns than threads
+        return _planted(name, 513, [3] * 1025)
+    if name == "rows_2048":
+        return _planted(name, 2048, [2] * 2048)
+    if name == "rows_2049":  # past the one workgroup's rows
+        return _planted(name, 2049, [2] * 1500)
+    if name == "row_192":
+        return _planted(name, 30, [2] * 191 + [0], extra=lambda j: [5])
+    if name == "row_193":  # past its longest row
+        return _planted(name, 30, [2] * 193, extra=lambda j: [5])
+    raise ValueError(name)
+
+
+@pytest.mark.parametrize("general", [False, True])
+@pytest.mark.parametrize("name", ["one", "empty_rows_and_columns", "lanes_8", "lanes_4", "lanes_2", "two_rows",
+                                  "rows_2048", "rows_2049", "row_192", "row_193"])
+def test_small_lp_in_one_workgroup_matches_oracle(name, general):
+    lp = _small(name)
+    kw = {}
+    if general:
+        lp = lpgen.general_from_matrix(lp.A, lp.AT, lpgen.rng_for(81, len(name)))
+        kw = dict(lo=lp.lo, hi=lp.hi, sense=lp.sense)
+    for T in (1, 2, 3, 64, 66, 67, 130):  # blocks of 64 with and without iterations between the first and last
+        sol = P.solve(P.DeviceLP.from_lp(lp), 1e-14, "fp64", max_iter=T)
+        ref = oracle.solve(lp.A, lp.AT, lp.b, lp.c, 1e-14, opts=OracleOptions(max_iter=T), **kw)
+        assert sol.info["iters"] == ref.iters and sol.info["restarts"] == ref.restarts, T
+        assert abs(sol.info["sigma_hat"] - ref.sigma_hat) <= 1e-12 * ref.sigma_hat
+        assert _rel(_np(sol.x), ref.meas.x) <= 1e-10, T
+        assert _rel(_np(sol.y), ref.meas.y) <= 1e-10, T
