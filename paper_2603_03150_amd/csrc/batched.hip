@@ -444,68 +444,13 @@ __global__ void k_zero_i32(int32_t* p, int n) {
     for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
 }
 
-// block-diagonal structure: every entry of instance i's rows lies in its columns
-__global__ void k_check_blockdiag(const int32_t* rowptr, const int32_t* col, const int32_t* row_off,
-                                  const int32_t* col_off, int B, int32_t nrows, int32_t* flags) {
-    for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < nrows;
-         r += (int64_t)gridDim.x * blockDim.x) {
-        int lo = 0, hi = B;  // instance: row_off[lo] <= r < row_off[lo+1]
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) / 2;
-            if (row_off[mid] <= r) lo = mid;
-            else hi = mid;
-        }
-        const int c0 = col_off[lo], c1 = col_off[lo + 1];
-        for (int k = rowptr[r]; k < rowptr[r + 1]; ++k)
-            if (col[k] < c0 || col[k] >= c1) {
-                atomicOr(flags, 8);
-                break;
-            }
-    }
-}
-
-int validate_blockdiag(const mipdhg_batch& bt, const std::vector<int32_t>& rpa, const std::vector<int32_t>& rpat,
-                       int32_t* tiles_a, int32_t* tiles_at, const int32_t* row_off_dev, const int32_t* col_off_dev,
-                       int32_t* flags, double* partials, double* red, hipStream_t stream) {
-    const mipdhg_lp& lp = bt.whole;
-    const std::vector<int32_t> ta = make_tile_desc(rpa, lp.m, kTileNnzDefault, kTileRowsDefault),
-                               tat = make_tile_desc(rpat, lp.n, kTileNnzDefault, kTileRowsDefault);
-    if (!tile_desc_ok(ta, rpa, lp.m, kTileNnzDefault, kTileRowsDefault) ||
-        !tile_desc_ok(tat, rpat, lp.n, kTileNnzDefault, kTileRowsDefault))
-        return set_error("internal: tile plan does not cover the rows"), MIPDHG_ERR_UNSUPPORTED;
-    MIP_HIP(hipMemcpyAsync(tiles_a, ta.data(), ta.size() * 4, hipMemcpyHostToDevice, stream));
-    MIP_HIP(hipMemcpyAsync(tiles_at, tat.data(), tat.size() * 4, hipMemcpyHostToDevice, stream));
-    const TilePlan pa = make_tile_plan(lp.a_rowptr, tiles_a, (int32_t)(ta.size() / 4), lp.m, kTileNnzDefault,
-                                       kTileRowsDefault, kShortRowDefault);
-    const TilePlan pat = make_tile_plan(lp.at_rowptr, tiles_at, (int32_t)(tat.size() / 4), lp.n, kTileNnzDefault,
-                                        kTileRowsDefault, kShortRowDefault);
-    int rc;
-    if ((rc = allow_validate_lds((int)std::max(tile_lds_bytes(pa, 8), tile_lds_bytes(pat, 8))))) return rc;
-    if ((rc = validate_device(lp, pa, pat, flags, partials, red, stream))) return rc;
-    MIP_HIP(hipMemsetAsync(flags, 0, 4, stream));
-    hipLaunchKernelGGL(k_check_blockdiag, dim3(grid_for(lp.m)), dim3(kBlock), 0, stream, lp.a_rowptr, lp.a_col,
-                       row_off_dev, col_off_dev, bt.count, lp.m, flags);
-    hipLaunchKernelGGL(k_check_blockdiag, dim3(grid_for(lp.n)), dim3(kBlock), 0, stream, lp.at_rowptr, lp.at_col,
-                       col_off_dev, row_off_dev, bt.count, lp.n, flags);
-    MIP_LAUNCH_CHECK();
-    int32_t f = 0;
-    MIP_HIP(hipMemcpyAsync(&f, flags, 4, hipMemcpyDeviceToHost, stream));
-    MIP_HIP(hipStreamSynchronize(stream));
-    if (f & 8) return set_error("an entry lies outside its instance's diagonal block"), MIPDHG_ERR_BAD_CSR;
-    return 0;
-}
-
-int64_t blockdiag_tile_slots(int64_t m, int64_t n, int64_t nnz) {
-    return std::max(max_tiles(m, nnz, kTileNnzDefault, kTileRowsDefault),
-                    max_tiles(n, nnz, kTileNnzDefault, kTileRowsDefault));
-}
-
 struct BatchWs {
     uint64_t* hdr;  // {marker, fingerprint} of the state the workspace holds
-    int32_t *order, *row_off, *col_off, *counter, *flags, *tiles_a, *tiles_at;
+    int32_t *order, *row_off, *col_off, *counter, *flags;
+    int64_t* nnz_off;
     BInst* info;
     BState* state;
-    double *d_row, *d_col, *pu, *pav, *partials, *red, *eps;
+    double *d_row, *d_col, *pu, *pav, *partials, *eps;
     void *a_vs, *at_vs, *x, *x0, *xhat, *ct, *y0, *yhat, *bt, *ysave;
     uint16_t *a_cl, *at_cl, *perm_r, *perm_c;
     size_t bytes;
@@ -522,8 +467,7 @@ static BatchWs carve_batch(void* base, size_t cap, int64_t B, int64_t m, int64_t
     w.col_off = cv.take<int32_t>(B + 1);
     w.counter = cv.take<int32_t>(64);
     w.flags = cv.take<int32_t>(64);
-    w.tiles_a = cv.take<int32_t>(4 * max_tiles(m, nnz, kTileNnzDefault, kTileRowsDefault));
-    w.tiles_at = cv.take<int32_t>(4 * max_tiles(n, nnz, kTileNnzDefault, kTileRowsDefault));
+    w.nnz_off = cv.take<int64_t>(B + 1);
     w.info = cv.take<BInst>(B);
     w.state = cv.take<BState>(B);
     w.eps = cv.take<double>(B);
@@ -531,8 +475,7 @@ static BatchWs carve_batch(void* base, size_t cap, int64_t B, int64_t m, int64_t
     w.d_col = cv.take<double>(n);
     w.pu = cv.take<double>(n);
     w.pav = cv.take<double>(m);
-    w.partials = cv.take<double>((size_t)std::max(max_tiles(m, nnz, kTileNnzDefault, kTileRowsDefault), max_tiles(n, nnz, kTileNnzDefault, kTileRowsDefault)) + 16);
-    w.red = cv.take<double>(16);
+    w.partials = cv.take<double>(4 * kCheckGrid);
     w.a_vs = cv.take<char>(nnz * vs);
     w.at_vs = cv.take<char>(nnz * vs);
     w.a_cl = cv.take<uint16_t>(nnz);
@@ -664,17 +607,6 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
     if (lds > 150 * 1024 || max_m > kInstMaxDim || max_n > kInstMaxDim)
         return set_error("largest instance needs %d bytes of LDS (limit 150 KiB): m + n too large", lds),
                MIPDHG_ERR_UNSUPPORTED;
-    // host checks of the row pointers against the instance offsets
-    std::vector<int32_t> rpa(lp.m + 1), rpat(lp.n + 1);
-    MIP_HIP(hipMemcpyAsync(rpa.data(), lp.a_rowptr, (lp.m + 1) * 4, hipMemcpyDeviceToHost, stream));
-    MIP_HIP(hipMemcpyAsync(rpat.data(), lp.at_rowptr, (lp.n + 1) * 4, hipMemcpyDeviceToHost, stream));
-    MIP_HIP(hipStreamSynchronize(stream));
-    int rc;
-    if ((rc = check_rowptr(rpa, lp.m, lp.nnz, "A"))) return rc;
-    if ((rc = check_rowptr(rpat, lp.n, lp.nnz, "A^T"))) return rc;
-    for (int i = 0; i <= B; ++i)
-        if (rpa[bt.row_off[i]] != bt.nnz_off[i] || rpat[bt.col_off[i]] != bt.nnz_off[i])
-            return set_error("nnz_off does not match the row pointers at instance %d", i), MIPDHG_ERR_BAD_CSR;
     int dev = 0, cus = 256;
     MIP_HIP(hipGetDevice(&dev));
     MIP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -714,9 +646,9 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
     MIP_HIP(hipMemcpyAsync(w.row_off, bt.row_off, (B + 1) * 4, hipMemcpyHostToDevice, stream));
     MIP_HIP(hipMemcpyAsync(w.eps, eps, (size_t)B * 8, hipMemcpyHostToDevice, stream));
     MIP_HIP(hipMemcpyAsync(w.col_off, bt.col_off, (B + 1) * 4, hipMemcpyHostToDevice, stream));
-    if (o.validate && !o.resume &&
-        (rc = validate_blockdiag(bt, rpa, rpat, w.tiles_a, w.tiles_at, w.row_off, w.col_off, w.flags, w.partials,
-                                 w.red, stream)))
+    // the row pointers against the instance offsets and, unless this resumes
+    // a validated call's state, the entries
+    if (int rc = check_blocks(bt, o.validate && !o.resume, w.row_off, w.col_off, w.nnz_off, w.flags, w.partials, stream))
         return rc;
     BArgs<T, V> a;
     a.B = B;
@@ -811,11 +743,14 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
         ac.counter = w.counter + c;
         ac.lds = cl_lds[c];
         begin += cl_count[c];
+        int rc;
         if (c == 0) rc = launch_class<T, V, Acc, kClassBs[0]>(ac, cus, cs);
         else if (c == 1) rc = launch_class<T, V, Acc, kClassBs[1]>(ac, cus, cs);
         else if (c == 2) rc = launch_class<T, V, Acc, kClassBs[2]>(ac, cus, cs);
         else rc = launch_class<T, V, Acc, kClassBs[3]>(ac, cus, cs);
-        if (rc) {
+        if (rc) {  // the launches before it still use the workspace
+            for (int q = 0; q < kClasses; ++q)
+                if (side.s[q]) (void)hipStreamSynchronize(side.s[q]);
             (void)hipStreamSynchronize(stream);
             return rc;
         }

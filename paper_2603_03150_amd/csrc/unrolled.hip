@@ -599,8 +599,9 @@ struct TapeLayout {
     double *tbuf, *sbuf;
     void *lx, *lx0, *ly, *ly0;
     double *lct, *lbt;
-    int32_t *vtiles_a, *vtiles_at, *vflags;  // input validation (forward)
-    double *vpartials, *vred;
+    int64_t* nnz_off;  // input validation (forward)
+    int32_t* vflags;
+    double* vpartials;
     int32_t W, nseg, nep;
     size_t bytes;
 };
@@ -659,12 +660,9 @@ static TapeLayout carve_tape(void* base, size_t cap, const mipdhg_batch& bt, int
     t.ly0 = cv.take<char>(m * ts);
     t.lct = cv.take<double>(n);
     t.lbt = cv.take<double>(m);
-    const int64_t vs_slots = blockdiag_tile_slots(m, n, nnz);
-    t.vtiles_a = cv.take<int32_t>(4 * vs_slots);
-    t.vtiles_at = cv.take<int32_t>(4 * vs_slots);
+    t.nnz_off = cv.take<int64_t>(B + 1);
     t.vflags = cv.take<int32_t>(64);
-    t.vpartials = cv.take<double>((size_t)vs_slots + 16);
-    t.vred = cv.take<double>(16);
+    t.vpartials = cv.take<double>(4 * kCheckGrid);
     t.bytes = (cv.off + 255) & ~size_t(255);
     return t;
 }
@@ -730,25 +728,14 @@ static int unrolled_impl(const mipdhg_batch& bt, const mipdhg_options& o, int K,
         return set_error("instance too large for LDS (%d bytes)", lds), MIPDHG_ERR_UNSUPPORTED;
     const mipdhg_lp& lp = bt.whole;
     if (!backward) {
-        std::vector<int32_t> rpa(lp.m + 1), rpat(lp.n + 1);
-        MIP_HIP(hipMemcpyAsync(rpa.data(), lp.a_rowptr, (lp.m + 1) * 4, hipMemcpyDeviceToHost, stream));
-        MIP_HIP(hipMemcpyAsync(rpat.data(), lp.at_rowptr, (lp.n + 1) * 4, hipMemcpyDeviceToHost, stream));
-        MIP_HIP(hipStreamSynchronize(stream));
-        int rc;
-        if ((rc = check_rowptr(rpa, lp.m, lp.nnz, "A"))) return rc;
-        if ((rc = check_rowptr(rpat, lp.n, lp.nnz, "A^T"))) return rc;
-        for (int i = 0; i <= B; ++i)
-            if (rpa[bt.row_off[i]] != bt.nnz_off[i] || rpat[bt.col_off[i]] != bt.nnz_off[i])
-                return set_error("nnz_off does not match the row pointers at instance %d", i), MIPDHG_ERR_BAD_CSR;
         std::vector<int32_t> wo(B + 1, 0);
         for (int i = 0; i < B; ++i) wo[i + 1] = wo[i] + (bt.col_off[i + 1] - bt.col_off[i] + 63) / 64;
         MIP_HIP(hipMemcpyAsync(t.row_off, bt.row_off, (B + 1) * 4, hipMemcpyHostToDevice, stream));
         MIP_HIP(hipMemcpyAsync(t.col_off, bt.col_off, (B + 1) * 4, hipMemcpyHostToDevice, stream));
         MIP_HIP(hipMemcpyAsync(t.word_off, wo.data(), (B + 1) * 4, hipMemcpyHostToDevice, stream));
-        // column ranges, finiteness, A^T against A, and the block-diagonal
+        // row pointers, column ranges, finiteness, A^T against A, and the block-diagonal
         // structure, before any kernel indexes with the columns
-        if (o.validate && (rc = validate_blockdiag(bt, rpa, rpat, t.vtiles_a, t.vtiles_at, t.row_off, t.col_off,
-                                                   t.vflags, t.vpartials, t.vred, stream)))
+        if (int rc = check_blocks(bt, o.validate, t.row_off, t.col_off, t.nnz_off, t.vflags, t.vpartials, stream))
             return rc;
         if (!replay)
             hipLaunchKernelGGL(k_zero_bytes, dim3(grid_for((int64_t)K * B)), dim3(kBlock), 0, stream,

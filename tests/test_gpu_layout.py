@@ -155,3 +155,44 @@ def test_small_lp_in_one_workgroup_matches_oracle(name, general):
         assert abs(sol.info["sigma_hat"] - ref.sigma_hat) <= 1e-12 * ref.sigma_hat
         assert _rel(_np(sol.x), ref.meas.x) <= 1e-10, T
         assert _rel(_np(sol.y), ref.meas.y) <= 1e-10, T
+
+
+# What the device check of a batch finds, each on a batch with more rows than
+# a chunk's LDS holds, most of them without entries.
+@pytest.mark.parametrize("what,code,text", [
+    ("nothing", 0, ""),
+    ("decreasing", -2, "A row pointer decreases at row 2"),
+    ("decreasing_t", -2, "A^T row pointer decreases at row 2"),
+    ("end", -2, "must start at 0 and end at nnz"),
+    ("nnz_off", -2, "nnz_off does not match the row pointers at instance 1"),
+    ("column", -2, "column index out of range"),
+    ("nan", -7, "NaN or Inf"),
+    ("inf_b", -7, "NaN or Inf"),
+    ("transpose", -3, "does not match"),
+])
+def test_batch_check_finds(what, code, text):
+    lps = [_planted("sparse", 5000, [2] * 60), lpgen.cfg4_instance(1, 40), _planted("sparse2", 4000, [3] * 30)]
+    batch = P.DeviceBatch.from_lps(lps)
+    lp = batch.lp
+    if what == "decreasing":
+        lp.a_rowptr[2], lp.a_rowptr[3] = 50, 10
+    elif what == "decreasing_t":
+        lp.at_rowptr[2], lp.at_rowptr[3] = 50, 10
+    elif what == "end":
+        lp.a_rowptr[-1] += 1
+    elif what == "nnz_off":
+        batch.nnz_off[1] += 1
+    elif what == "column":
+        lp.at_col[7] = -1
+    elif what == "nan":
+        lp.at_val[100] = float("nan")
+    elif what == "inf_b":
+        lp.b[3] = float("inf")
+    elif what == "transpose":
+        lp.a_val[100] *= 1.0 + 1e-6
+    if code == 0:
+        assert P.solve_batched(batch, 1e-14, "fp32", max_iter=3).infos[0]["iters"] == 3
+        return
+    with pytest.raises(P.MipdhgError) as e:
+        P.solve_batched(batch, 1e-4, "fp32", max_iter=3)
+    assert e.value.code == code and text in str(e.value), str(e.value)
