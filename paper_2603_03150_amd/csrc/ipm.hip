@@ -49,10 +49,15 @@ __global__ __launch_bounds__(kBlock) void k_ipm_spmv(const int32_t* rp, const in
 }
 
 // scaled values (d_row[i] a_ij) d_col[j]; trans: the rows are A's columns
+// (a wave to a row: with one thread its longest row's entries came one after
+// the other, 93 us on 1,000 x 4,000 and 203 us on 4,000 x 16,000 power-law LPs;
+// so 4.8 and 9.8 us (the two sides' mean))
 __global__ void k_ipm_scale_vals(const int32_t* rp, const int32_t* col, const double* val, int32_t nrows,
                                  const double* d_row, const double* d_col, int trans, double* out) {
-    for (int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; r < nrows; r += (int64_t)gridDim.x * blockDim.x)
-        for (int k = rp[r]; k < rp[r + 1]; ++k) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t waves = (int64_t)gridDim.x * blockDim.x / kWave;
+    for (int64_t r = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave; r < nrows; r += waves)
+        for (int k = rp[r] + lane; k < rp[r + 1]; k += kWave) {
             const int32_t c = col[k];
             const double dr = d_row ? d_row[trans ? c : r] : 1.0, dc = d_col ? d_col[trans ? r : c] : 1.0;
             out[k] = (dr * val[k]) * dc;
@@ -659,9 +664,9 @@ __global__ __launch_bounds__(kBlock) void k_ipm_ratio(const double* x, const dou
 
 // sum (x + ap dx)(z + ad dz)
 __global__ __launch_bounds__(kBlock) void k_ipm_mu_at(const double* x, const double* dx, const double* z,
-                                                      const double* dz, int64_t n, const double* steps,
+                                                      const double* dz, int64_t n, const double* bounds,
                                                       double* part) {
-    const double ap = steps[0], ad = steps[1];
+    const double ap = fmin(1.0, bounds[0]), ad = fmin(1.0, bounds[1]);
     double v[1] = {0.0};
     for (int64_t j = blockIdx.x * (int64_t)kBlock + threadIdx.x; j < n; j += (int64_t)gridDim.x * kBlock)
         v[0] += (x[j] + ap * dx[j]) * (z[j] + ad * dz[j]);
@@ -704,8 +709,7 @@ __global__ __launch_bounds__(kBlock) void k_ipm_final(const double* part, int G,
 
 // v += a s .* dv for up to three (vector, direction, step slot) triples
 __global__ void k_ipm_step(double* x, const double* dx, int64_t n, double* y, const double* dy, int64_t m, double* z,
-                           const double* dz, const double* steps) {
-    const double ap = steps[0], ad = steps[1];
+                           const double* dz, double ap, double ad) {
     for (int64_t j = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x) {
         x[j] = x[j] + ap * dx[j];
         z[j] = z[j] + ad * dz[j];
@@ -849,13 +853,20 @@ struct Ipm {
         MIP_LAUNCH_CHECK();
         return 0;
     }
+    // Scalars stay on the device until the host decides with them: the sums of
+    // the partials go to slots of w.scal, and one copy brings several.  (A copy
+    // with its wait is about 20 us of an idle device; a Newton step has three,
+    // where fetching each sum by itself and sending the steps back took seven.)
     template <int W>
-    int reduce(int64_t len, int G, int minmask, double* host) {
-        hipLaunchKernelGGL((k_ipm_final<W>), dim3(1), dim3(kBlock), 0, s, (const double*)w.part, G, minmask, w.scal);
+    int reduce(int G, int minmask, int slot, int64_t skip = 0) {
+        hipLaunchKernelGGL((k_ipm_final<W>), dim3(1), dim3(kBlock), 0, s, (const double*)(w.part + skip), G, minmask,
+                           w.scal + slot);
         MIP_LAUNCH_CHECK();
-        MIP_HIP(hipMemcpyAsync(host, w.scal, W * sizeof(double), hipMemcpyDeviceToHost, s));
+        return 0;
+    }
+    int fetch(double* host, int slot, int count) {
+        MIP_HIP(hipMemcpyAsync(host, w.scal + slot, count * sizeof(double), hipMemcpyDeviceToHost, s));
         MIP_HIP(hipStreamSynchronize(s));
-        (void)len;
         return 0;
     }
 
@@ -871,49 +882,35 @@ struct Ipm {
         if ((rc = spmv_a(w.ct, nullptr, 1.0, nullptr, w.y))) return rc;
         if ((rc = solve(w.y))) return rc;
         if ((rc = spmv_at(w.y, w.ct, -1.0, nullptr, w.z))) return rc;
-        const int G = red_grid(n);
-        double hx[3], hz[3];
-        hipLaunchKernelGGL(k_ipm_summin, dim3(G), dim3(kBlock), 0, s, (const double*)w.x, (const double*)nullptr, n,
-                           w.part);
-        MIP_LAUNCH_CHECK();
-        if ((rc = finish_summin(G, hx))) return rc;
-        hipLaunchKernelGGL(k_ipm_summin, dim3(G), dim3(kBlock), 0, s, (const double*)w.z, (const double*)nullptr, n,
-                           w.part);
-        MIP_LAUNCH_CHECK();
-        if ((rc = finish_summin(G, hz))) return rc;
-        const double sx = std::max(-1.5 * hx[1], 0.0), sz = std::max(-1.5 * hz[1], 0.0);
+        double h[6];  // {sum, sum of products, min} of x and of z
+        if ((rc = summin(w.x, nullptr, 0)) || (rc = summin(w.z, nullptr, 3)) || (rc = fetch(h, 0, 6))) return rc;
+        const double sx = std::max(-1.5 * h[2], 0.0), sz = std::max(-1.5 * h[5], 0.0);
         hipLaunchKernelGGL(k_ipm_shift, dim3(grid_for(n)), dim3(kBlock), 0, s, w.x, n, sx);
         hipLaunchKernelGGL(k_ipm_shift, dim3(grid_for(n)), dim3(kBlock), 0, s, w.z, n, sz);
         MIP_LAUNCH_CHECK();
         // x^T z, sum x, sum z of the shifted vectors
-        hipLaunchKernelGGL(k_ipm_summin, dim3(G), dim3(kBlock), 0, s, (const double*)w.x, (const double*)w.z, n,
-                           w.part);
-        MIP_LAUNCH_CHECK();
-        if ((rc = finish_summin(G, hx))) return rc;
-        hipLaunchKernelGGL(k_ipm_summin, dim3(G), dim3(kBlock), 0, s, (const double*)w.z, (const double*)nullptr, n,
-                           w.part);
-        MIP_LAUNCH_CHECK();
-        if ((rc = finish_summin(G, hz))) return rc;
-        const double xz = hx[2];
-        hipLaunchKernelGGL(k_ipm_shift, dim3(grid_for(n)), dim3(kBlock), 0, s, w.x, n, 0.5 * xz / hz[0]);
-        hipLaunchKernelGGL(k_ipm_shift, dim3(grid_for(n)), dim3(kBlock), 0, s, w.z, n, 0.5 * xz / hx[0]);
+        if ((rc = summin(w.x, w.z, 0)) || (rc = summin(w.z, nullptr, 3)) || (rc = fetch(h, 0, 6))) return rc;
+        const double xz = h[1];
+        hipLaunchKernelGGL(k_ipm_shift, dim3(grid_for(n)), dim3(kBlock), 0, s, w.x, n, 0.5 * xz / h[3]);
+        hipLaunchKernelGGL(k_ipm_shift, dim3(grid_for(n)), dim3(kBlock), 0, s, w.z, n, 0.5 * xz / h[0]);
         MIP_LAUNCH_CHECK();
         return 0;
     }
-    // {sum a, min a, sum a b} from k_ipm_summin's partials
-    int finish_summin(int G, double* h) {
-        double s2[2], s1[1];
-        hipLaunchKernelGGL((k_ipm_final<2>), dim3(1), dim3(kBlock), 0, s, (const double*)w.part, G, 0, w.scal);
-        hipLaunchKernelGGL((k_ipm_final<1>), dim3(1), dim3(kBlock), 0, s, (const double*)(w.part + 2 * G), G, 1,
-                           w.scal + 2);
+    // {sum a, sum a b, min a} into three slots
+    int summin(const double* a, const double* b, int slot) {
+        const int G = red_grid(n);
+        hipLaunchKernelGGL(k_ipm_summin, dim3(G), dim3(kBlock), 0, s, a, b, n, w.part);
         MIP_LAUNCH_CHECK();
-        MIP_HIP(hipMemcpyAsync(s2, w.scal, 2 * 8, hipMemcpyDeviceToHost, s));
-        MIP_HIP(hipMemcpyAsync(s1, w.scal + 2, 8, hipMemcpyDeviceToHost, s));
-        MIP_HIP(hipStreamSynchronize(s));
-        h[0] = s2[0];
-        h[1] = s1[0];
-        h[2] = s2[1];
-        return 0;
+        int rc;
+        if ((rc = reduce<2>(G, 0, slot))) return rc;
+        return reduce<1>(G, 1, slot + 2, 2 * (int64_t)G);
+    }
+    // {sum a^2, sum b c, sum c d} into three slots
+    int sums3(const double* a, const double* b, const double* c, const double* d, int64_t len, int slot) {
+        const int G = red_grid(len);
+        hipLaunchKernelGGL(k_ipm_sums3, dim3(G), dim3(kBlock), 0, s, a, b, c, d, len, w.part);
+        MIP_LAUNCH_CHECK();
+        return reduce<3>(G, 0, slot);
     }
 
     // the relative measures (rp, rd, gap) and c~^T x, b~^T y, x^T z; r_b, r_c left in the workspace
@@ -921,17 +918,11 @@ struct Ipm {
         int rc;
         if ((rc = spmv_a(w.x, w.bt, -1.0, nullptr, w.rb))) return rc;
         if ((rc = spmv_at(w.y, w.ct, -1.0, w.z, w.rc))) return rc;
-        double hn[3], hm[3];
-        int G = red_grid(n);
-        hipLaunchKernelGGL(k_ipm_sums3, dim3(G), dim3(kBlock), 0, s, (const double*)w.rc, (const double*)w.ct,
-                           (const double*)w.x, (const double*)w.z, n, w.part);
-        MIP_LAUNCH_CHECK();
-        if ((rc = reduce<3>(n, G, 0, hn))) return rc;
-        G = red_grid(m);
-        hipLaunchKernelGGL(k_ipm_sums3, dim3(G), dim3(kBlock), 0, s, (const double*)w.rb, (const double*)w.bt,
-                           (const double*)w.y, (const double*)nullptr, m, w.part);
-        MIP_LAUNCH_CHECK();
-        if ((rc = reduce<3>(m, G, 0, hm))) return rc;
+        double h[6];
+        if ((rc = sums3(w.rc, w.ct, w.x, w.z, n, 0)) || (rc = sums3(w.rb, w.bt, w.y, nullptr, m, 3)) ||
+            (rc = fetch(h, 0, 6)))
+            return rc;
+        const double *hn = h, *hm = h + 3;
         rel[0] = sqrt(hm[0]) / (1.0 + bnorm);
         rel[1] = sqrt(hn[0]) / (1.0 + cnorm);
         *px = hn[1];
@@ -957,13 +948,13 @@ struct Ipm {
         MIP_LAUNCH_CHECK();
         return 0;
     }
-    // steps to the boundary of (x, dx) and (z, dz)
-    int boundary(const double* dx, const double* dz, double* h) {
+    // steps to the boundary of (x, dx) and (z, dz) into two slots
+    int boundary(const double* dx, const double* dz, int slot) {
         const int G = red_grid(n);
         hipLaunchKernelGGL(k_ipm_ratio, dim3(G), dim3(kBlock), 0, s, (const double*)w.x, dx, (const double*)w.z, dz,
                            n, w.part);
         MIP_LAUNCH_CHECK();
-        return reduce<2>(n, G, 3, h);
+        return reduce<2>(G, 3, slot);
     }
 
     // the iteration from the point in (x, y, z); fills info
@@ -974,6 +965,9 @@ struct Ipm {
         for (int k = 0;; ++k) {
             double rel[3], px, dyv, xz;
             if ((rc = measures(rel, &px, &dyv, &xz))) return rc;
+            info->pobj = px;
+            info->dobj = dyv;
+            info->mu = xz / (double)n;
             info->rel_rp = rel[0];
             info->rel_rd = rel[1];
             info->rel_gap = rel[2];
@@ -993,32 +987,26 @@ struct Ipm {
             if ((rc = factor(w.d))) return rc;
             // predictor
             if ((rc = direction(0, 0.0, w.dxa, w.dya, w.dza))) return rc;
-            double st[2];
-            if ((rc = boundary(w.dxa, w.dza, st))) return rc;
-            double steps[2] = {std::min(1.0, st[0]), std::min(1.0, st[1])};
-            MIP_HIP(hipMemcpyAsync(w.scal + 8, steps, 16, hipMemcpyHostToDevice, s));
-            MIP_HIP(hipStreamSynchronize(s));
+            if ((rc = boundary(w.dxa, w.dza, 0))) return rc;
             const int G = red_grid(n);
             hipLaunchKernelGGL(k_ipm_mu_at, dim3(G), dim3(kBlock), 0, s, (const double*)w.x, (const double*)w.dxa,
-                               (const double*)w.z, (const double*)w.dza, n, (const double*)(w.scal + 8), w.part);
+                               (const double*)w.z, (const double*)w.dza, n, (const double*)w.scal, w.part);
             MIP_LAUNCH_CHECK();
             double mua[1];
-            if ((rc = reduce<1>(n, G, 0, mua))) return rc;
+            if ((rc = reduce<1>(G, 0, 2)) || (rc = fetch(mua, 2, 1))) return rc;
             const double sigma = std::pow((mua[0] / (double)n) / mu, 3.0);
             // corrector, with the same factor
             if ((rc = direction(1, sigma * mu, w.dx, w.dy, w.dz))) return rc;
-            if ((rc = boundary(w.dx, w.dz, st))) return rc;
-            steps[0] = std::min(1.0, o.step_frac * st[0]);
-            steps[1] = std::min(1.0, o.step_frac * st[1]);
+            double st[2];
+            if ((rc = boundary(w.dx, w.dz, 0)) || (rc = fetch(st, 0, 2))) return rc;
+            const double steps[2] = {std::min(1.0, o.step_frac * st[0]), std::min(1.0, o.step_frac * st[1])};
             if (k == 0) {
                 info->first_step_p = steps[0];
                 info->first_step_d = steps[1];
             }
-            MIP_HIP(hipMemcpyAsync(w.scal + 8, steps, 16, hipMemcpyHostToDevice, s));
-            MIP_HIP(hipStreamSynchronize(s));
             hipLaunchKernelGGL(k_ipm_step, dim3(grid_for(std::max(m, n))), dim3(kBlock), 0, s, w.x,
                                (const double*)w.dx, n, w.y, (const double*)w.dy, m, w.z, (const double*)w.dz,
-                               (const double*)(w.scal + 8));
+                               steps[0], steps[1]);
             MIP_LAUNCH_CHECK();
             info->iters = k + 1;
         }
@@ -1073,31 +1061,25 @@ int ipm_setup(Ipm& P, const double* d_row, const double* d_col) {
         }
     const IpmWs& w = P.w;
     if ((rc = P.allow_lds())) return rc;
-    hipLaunchKernelGGL(k_ipm_scale_vals, dim3(grid_for(lp.m)), dim3(kBlock), 0, s, lp.a_rowptr, lp.a_col, lp.a_val,
+    hipLaunchKernelGGL(k_ipm_scale_vals, dim3(grid_for((int64_t)lp.m * kWave)), dim3(kBlock), 0, s, lp.a_rowptr, lp.a_col, lp.a_val,
                        lp.m, d_row, d_col, 0, w.av);
-    hipLaunchKernelGGL(k_ipm_scale_vals, dim3(grid_for(lp.n)), dim3(kBlock), 0, s, lp.at_rowptr, lp.at_col, lp.at_val,
+    hipLaunchKernelGGL(k_ipm_scale_vals, dim3(grid_for((int64_t)lp.n * kWave)), dim3(kBlock), 0, s, lp.at_rowptr, lp.at_col, lp.at_val,
                        lp.n, d_row, d_col, 1, w.atv);
     hipLaunchKernelGGL(k_ipm_vscale, dim3(grid_for(lp.m)), dim3(kBlock), 0, s, lp.b, d_row, 0, (int64_t)lp.m, w.bt);
     hipLaunchKernelGGL(k_ipm_vscale, dim3(grid_for(lp.n)), dim3(kBlock), 0, s, lp.c, d_col, 0, (int64_t)lp.n, w.ct);
     hipLaunchKernelGGL(k_zero_flag, dim3(1), dim3(32), 0, s, w.flag);
     MIP_LAUNCH_CHECK();
-    double hb[3], hc[3];
-    int G = red_grid(lp.m);
-    hipLaunchKernelGGL(k_ipm_sums3, dim3(G), dim3(kBlock), 0, s, (const double*)w.bt, (const double*)w.bt,
-                       (const double*)w.bt, (const double*)nullptr, (int64_t)lp.m, w.part);
-    MIP_LAUNCH_CHECK();
-    if ((rc = P.reduce<3>(lp.m, G, 0, hb))) return rc;
-    G = red_grid(lp.n);
-    hipLaunchKernelGGL(k_ipm_sums3, dim3(G), dim3(kBlock), 0, s, (const double*)w.ct, (const double*)w.ct,
-                       (const double*)w.ct, (const double*)nullptr, (int64_t)lp.n, w.part);
-    MIP_LAUNCH_CHECK();
-    if ((rc = P.reduce<3>(lp.n, G, 0, hc))) return rc;
-    P.bnorm = sqrt(hb[0]);
-    P.cnorm = sqrt(hc[0]);
+    double h[6];
+    if ((rc = P.sums3(w.bt, w.bt, w.bt, nullptr, lp.m, 0)) || (rc = P.sums3(w.ct, w.ct, w.ct, nullptr, lp.n, 3)) ||
+        (rc = P.fetch(h, 0, 6)))
+        return rc;
+    P.bnorm = sqrt(h[0]);
+    P.cnorm = sqrt(h[3]);
     return 0;
 }
 
-// the point in the workspace, unscaled into the outputs; objectives and pivots into info
+// the point in the workspace, unscaled into the outputs; pivots into info (its
+// measures are those that ended run())
 int ipm_finish(Ipm& P, const double* d_row, const double* d_col, double* x, double* y, double* z,
                mipdhg_ipm_info* info) {
     hipStream_t s = P.s;
@@ -1106,15 +1088,9 @@ int ipm_finish(Ipm& P, const double* d_row, const double* d_col, double* x, doub
     hipLaunchKernelGGL(k_ipm_vscale, dim3(grid_for(P.m)), dim3(kBlock), 0, s, (const double*)w.y, d_row, 0, P.m, y);
     hipLaunchKernelGGL(k_ipm_vscale, dim3(grid_for(P.n)), dim3(kBlock), 0, s, (const double*)w.z, d_col, 1, P.n, z);
     MIP_LAUNCH_CHECK();
-    double rel[3], px, dy, xz;
-    int rc = P.measures(rel, &px, &dy, &xz);
-    if (rc) return rc;
     int32_t piv = 0;
     MIP_HIP(hipMemcpyAsync(&piv, w.flag, 4, hipMemcpyDeviceToHost, s));
     MIP_HIP(hipStreamSynchronize(s));
-    info->pobj = px;
-    info->dobj = dy;
-    info->mu = xz / (double)P.n;
     info->pivots_replaced = piv;
     return 0;
 }
