@@ -57,28 +57,35 @@ __global__ __launch_bounds__(kBlock) void k_sumsq(const double* v, int64_t n, do
     block_reduce_store<1, 0>(s, mx, partials + blockIdx.x);
 }
 
+// Fixed-order sum of column q of G partial rows of width W by a workgroup, in
+// its first thread; sh: kBlock doubles
+__device__ __forceinline__ double reduce_column(const double* partials, int G, int W, int q, double* sh) {
+    double s = 0.0;
+    int g = threadIdx.x;
+    for (; g + 7 * kBlock < G; g += 8 * kBlock) {  // 8 loads in flight, added in the same order
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = partials[(int64_t)(g + u * kBlock) * W + q];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += x[u];
+    }
+    for (; g < G; g += kBlock) s += partials[(int64_t)g * W + q];
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    for (int st = kBlock / 2; st > 0; st >>= 1) {
+        if (threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
+        __syncthreads();
+    }
+    return sh[0];
+}
+
 // out[q] = fixed-order sum over G partial rows of width W (one workgroup)
 __global__ __launch_bounds__(kBlock) void k_reduce_rows(const double* partials, int G, int W,
                                                         double* out) {
     __shared__ double sh[kBlock];
     for (int q = 0; q < W; ++q) {
-        double s = 0.0;
-        int g = threadIdx.x;
-        for (; g + 7 * kBlock < G; g += 8 * kBlock) {  // 8 loads in flight, added in the same order
-            double x[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) x[u] = partials[(int64_t)(g + u * kBlock) * W + q];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) s += x[u];
-        }
-        for (; g < G; g += kBlock) s += partials[(int64_t)g * W + q];
-        sh[threadIdx.x] = s;
-        __syncthreads();
-        for (int st = kBlock / 2; st > 0; st >>= 1) {
-            if (threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) out[q] = sh[0];
+        const double s = reduce_column(partials, G, W, q, sh);
+        if (threadIdx.x == 0) out[q] = s;
         __syncthreads();
     }
 }
@@ -275,22 +282,21 @@ __global__ __launch_bounds__(kBlock) void k_spmv_copy(TilePlan p, const int32_t*
     block_reduce_store<1, 0>(s, mx, partials + blockIdx.x);
 }
 
-// v = u / sqrt(sum of G partials), identical sum order in every workgroup
+// v = u / sqrt(sum of G partials), identical sum order in every workgroup; the
+// last workgroup of the grid sums A~ v's partials into hist instead (as a
+// launch of its own that was 4.1 us of each power iteration)
 template <typename X>
-__global__ __launch_bounds__(kBlock) void k_normalize(const X* u, X* v, int64_t n,
-                                                      const double* partials, int G) {
+__global__ __launch_bounds__(kBlock) void k_normalize(const X* u, X* v, int64_t n, const double* partials, int G,
+                                                      const double* av_partials, int Ga, double* hist) {
     __shared__ double sh[kBlock];
-    double s = 0.0;
-    for (int g = threadIdx.x; g < G; g += kBlock) s += partials[g];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int st = kBlock / 2; st > 0; st >>= 1) {
-        if (threadIdx.x < st) sh[threadIdx.x] += sh[threadIdx.x + st];
-        __syncthreads();
+    if (blockIdx.x == gridDim.x - 1) {
+        const double s = reduce_column(av_partials, Ga, 1, 0, sh);
+        if (threadIdx.x == 0) *hist = s;
+        return;
     }
-    const double nrm = sqrt(sh[0]);
+    const double nrm = sqrt(reduce_column(partials, G, 1, 0, sh));
     if (nrm == 0.0) return;  // u = 0: keep v
-    for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock)
+    for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n; i += (int64_t)(gridDim.x - 1) * kBlock)
         v[i] = (X)((double)u[i] / nrm);
 }
 
@@ -2821,13 +2827,16 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
         for (int k = 0; k <= o.power_iters; ++k) {
             // av = A~ v, hist[k] = ||av||^2
             spmv(pa, ca, w.a_vs, w.pv, w.pav, w.psetup);
-            hipLaunchKernelGGL(k_reduce_rows, dim3(1), dim3(kBlock), 0, stream, (const double*)w.psetup, gta, 1,
-                               w.hist + k);
-            if (k == o.power_iters) break;
+            if (k == o.power_iters) {
+                hipLaunchKernelGGL(k_reduce_rows, dim3(1), dim3(kBlock), 0, stream, (const double*)w.psetup, gta, 1,
+                                   w.hist + k);
+                break;
+            }
             // u = A~^T av, v = u / ||u||
             spmv(pat, cat, w.at_vs, w.pav, w.pu, w.psetup + G);
-            hipLaunchKernelGGL((k_normalize<T>), dim3(grid_for(n, 1024)), dim3(kBlock), 0, stream, (const T*)w.pu,
-                               (T*)w.pv, n, (const double*)(w.psetup + G), gtat);
+            hipLaunchKernelGGL((k_normalize<T>), dim3(grid_for(n, 1024) + 1), dim3(kBlock), 0, stream, (const T*)w.pu,
+                               (T*)w.pv, n, (const double*)(w.psetup + G), gtat, (const double*)w.psetup, gta,
+                               w.hist + k);
             MIP_LAUNCH_CHECK();
         }
         MIP_LAUNCH_CHECK();
