@@ -578,7 +578,8 @@ __global__ __launch_bounds__(kBlock) void k_iter_persist(IterArgs<T, V> a, TileP
 // 200 rows of 12 and 500 columns of 5 entries, FP64: 13 us an iteration by
 // launches; so 2.3 us with one lane to a row and all entries read from LDS, 2.1
 // with up to eight lanes, 1.24 with each lane's first four entries in registers
-// (and 256 iterations with their set-up 6.5 -> 1.77 ms).
+// (and 256 iterations with their set-up 6.5 -> 1.77 ms, with the scaling by one
+// launch and without the sort 1.43 ms).
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallRows = 2;  // rows (and columns) a thread holds
 
@@ -876,6 +877,64 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_power(SmallMat ma, SmallM
         }
         __syncthreads();
     }
+}
+
+// All scaling passes (Ruiz's infinity norms, then 1-norms), D and the float64
+// matrix in LDS: D_r and D_c of a pass and of the next.  Four launches a pass
+// were 160 us of kernels and their gaps at 200 x 500, this is 32 us.
+__host__ __device__ inline SmallLds small_scale_lds(int64_t m, int64_t n, int64_t nnz) {
+    return small_lds(m, n, nnz, 16, 8);  // two doubles to a row and to a column
+}
+__global__ __launch_bounds__(kSmallBlock) void k_small_scale(SmallMat ma, SmallMat mat, const double* a_val,
+                                                             const double* at_val, int ruiz, int passes,
+                                                             double* d_row, double* d_col) {
+    extern __shared__ __align__(16) unsigned char smem_t[];
+    const int tid = threadIdx.x, m = ma.dim, n = mat.dim;
+    const SmallLds L = small_scale_lds(m, n, ma.tp.rowptr[m]);
+    double* dr = (double*)(smem_t + L.vy);
+    double* dc = (double*)(smem_t + L.vx);
+    double *dr2 = dr + m, *dc2 = dc + n;
+    double* const av = (double*)(smem_t + L.av);
+    double* const atv = (double*)(smem_t + L.atv);
+    uint16_t* const ac = (uint16_t*)(smem_t + L.ac);
+    uint16_t* const atc = (uint16_t*)(smem_t + L.atc);
+    small_fill(ma, a_val, av, ac);
+    small_fill(mat, at_val, atv, atc);
+    for (int i = tid; i < m; i += kSmallBlock) dr[i] = 1.0;
+    for (int j = tid; j < n; j += kSmallBlock) dc[j] = 1.0;
+    __syncthreads();
+    auto side = [&](const SmallMat& s, const double* lv, const uint16_t* lc, const double* self, const double* other,
+                    double* out, bool mx) {
+        const int lg = small_lanes(s.dim), step = 1 << lg;
+        for (int i = tid >> lg; i < s.dim; i += kSmallBlock >> lg) {
+            double a = 0.0;
+            const int e = s.tp.rowptr[i + 1];
+#pragma unroll 4
+            for (int k = s.tp.rowptr[i] + (tid & (step - 1)); k < e; k += step) {
+                const double t = fabs(lv[k]) * other[lc[k]];
+                a = mx ? fmax(a, t) : a + t;
+            }
+            auto join = [&](double b) { a = mx ? fmax(a, b) : a + b; };
+            if (lg > 0) join(dpp_other<0xB1>(a));
+            if (lg > 1) join(dpp_other<0x4E>(a));
+            if (lg > 2) join(dpp_other<0x141>(a));
+            const double st = self[i] * a;
+            if ((tid & (step - 1)) == 0) out[i] = st > 0.0 ? self[i] * (1.0 / sqrt(st)) : self[i];
+        }
+    };
+    for (int ps = 0; ps < passes; ++ps) {
+        side(ma, av, ac, dr, dc, dr2, ps < ruiz);
+        side(mat, atv, atc, dc, dr, dc2, ps < ruiz);
+        __syncthreads();
+        double* t = dr;
+        dr = dr2;
+        dr2 = t;
+        t = dc;
+        dc = dc2;
+        dc2 = t;
+    }
+    for (int i = tid; i < m; i += kSmallBlock) d_row[i] = dr[i];
+    for (int j = tid; j < n; j += kSmallBlock) d_col[j] = dc[j];
 }
 
 // ---------------------------------------------------------------------------
@@ -2160,7 +2219,9 @@ struct Solver {
                    MIPDHG_ERR_UNSUPPORTED;
         return 0;
     }
-    bool sorted() const { return sorted_layout(o, lp.m, lp.n); }
+    // (a small LP's gathers hit the caches in any order, and the sort by one
+    // workgroup a side is 71 us)
+    bool sorted() const { return sorted_layout(o, lp.m, lp.n) && !small(); }
     // spmv_kind 3: the dual step on A's panel layout, the primal on A^T's tiles
     bool panel() const { return o.spmv_kind == 3 || o.spmv_kind == 4; }
     bool rowpanel() const { return o.spmv_kind == 4; }
@@ -2263,7 +2324,7 @@ struct Solver {
     // average of an epoch's points and the panel layouts keep their kernels.
     static constexpr int kSmallRowLen = 192;
     static constexpr int kSmallLdsMax = 155 * 1024;
-    int64_t longest = 0;  // of the rows of A and of A^T
+    int64_t longest = kSmallRowLen + 1;  // of the rows of A and of A^T, once they are known
     SmallLds small_layout() const { return small_lds(lp.m, lp.n, lp.nnz, sizeof(T), sizeof(V)); }
     bool small() const {
         const int64_t cap = (int64_t)kSmallRows * kSmallBlock;
@@ -2280,7 +2341,8 @@ struct Solver {
         const void* ks[] = {(const void*)k_small_iters<T, V, Acc, false, false>,
                             (const void*)k_small_iters<T, V, Acc, true, false>,
                             (const void*)k_small_iters<T, V, Acc, false, true>,
-                            (const void*)k_small_iters<T, V, Acc, true, true>, (const void*)k_small_power<T, V>};
+                            (const void*)k_small_iters<T, V, Acc, true, true>, (const void*)k_small_power<T, V>,
+                            (const void*)k_small_scale};
         for (const void* k : ks)
             MIP_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLdsMax));
         return 0;
@@ -2667,6 +2729,9 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
     int rc;
     if ((rc = check_rowptr(rpa, lp.m, nnz, "A"))) return rc;
     if ((rc = check_rowptr(rpat, lp.n, nnz, "A^T"))) return rc;
+    S.longest = 0;
+    for (int64_t i = 0; i < m; ++i) S.longest = std::max<int64_t>(S.longest, rpa[i + 1] - rpa[i]);
+    for (int64_t j = 0; j < n; ++j) S.longest = std::max<int64_t>(S.longest, rpat[j + 1] - rpat[j]);
     S.hpa = make_plan(rpa, lp.m, o.lanes_a, o.long_row);
     S.hpat = make_plan(rpat, lp.n, o.lanes_at, o.long_row);
     if (!S.hpa.long_rows.empty())
@@ -2690,8 +2755,6 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
         S.tat = make_tile_plan(lp.at_rowptr, w.tiles_at, (int32_t)(tat.size() / 4), lp.n, tnz_t, trows_t, srow_t);
         if ((rc = S.allow_tile_lds())) return rc;
         if ((rc = S.plan_persistent())) return rc;
-        for (int64_t i = 0; i < m; ++i) S.longest = std::max<int64_t>(S.longest, rpa[i + 1] - rpa[i]);
-        for (int64_t j = 0; j < n; ++j) S.longest = std::max<int64_t>(S.longest, rpat[j + 1] - rpat[j]);
         if (S.small() && (rc = S.allow_small_lds())) return rc;
         MIP_HIP(hipStreamSynchronize(stream));  // host vectors go out of scope
     }
@@ -2714,11 +2777,20 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
     }
 
     // --- scaling: Ruiz passes, then one Pock-Chambolle pass
-    hipLaunchKernelGGL(k_fill, dim3(grid_for(m)), dim3(kBlock), 0, stream, w.d_row, m, 1.0);
-    hipLaunchKernelGGL(k_fill, dim3(grid_for(n)), dim3(kBlock), 0, stream, w.d_col, n, 1.0);
-    MIP_LAUNCH_CHECK();
     const int passes = o.ruiz_iters + (o.pock_chambolle ? 1 : 0);
-    for (int ps = 0; ps < passes; ++ps) {
+    const int scale_lds = S.small() ? small_scale_lds(m, n, nnz).bytes : 0;
+    const bool small_scale = S.small() && scale_lds <= S.kSmallLdsMax;
+    if (small_scale) {
+        SmallMat sa{S.ta, lp.a_col, lp.m}, st{S.tat, lp.at_col, lp.n};  // the caller's matrix: row order
+        sa.tp.slot = st.tp.slot = nullptr;
+        hipLaunchKernelGGL(k_small_scale, dim3(1), dim3(kSmallBlock), scale_lds, stream, sa, st, lp.a_val, lp.at_val,
+                           o.ruiz_iters, passes, w.d_row, w.d_col);
+    } else {
+        hipLaunchKernelGGL(k_fill, dim3(grid_for(m)), dim3(kBlock), 0, stream, w.d_row, m, 1.0);
+        hipLaunchKernelGGL(k_fill, dim3(grid_for(n)), dim3(kBlock), 0, stream, w.d_col, n, 1.0);
+    }
+    MIP_LAUNCH_CHECK();
+    for (int ps = small_scale ? passes : 0; ps < passes; ++ps) {
         const bool maxmode = ps < o.ruiz_iters;
         if (maxmode) {
             hipLaunchKernelGGL((k_scale_stat<true>), dim3(gta), dim3(kBlock), tile_lds_bytes(S.ta, 8), stream, S.ta, lp.a_col, lp.a_val,

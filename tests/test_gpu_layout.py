@@ -130,6 +130,8 @@ def _small(name):
         return _planted(name, 513, [3] * 1025)
     if name == "rows_2048":
         return _planted(name, 2048, [2] * 2048)
+    if name == "scaling_outside":  # fits the iterations' LDS but not the scaling's
+        return _planted(name, 2048, [3] * 1300 + [2] * 748)
     if name == "rows_2049":  # past the one workgroup's rows
         return _planted(name, 2049, [2] * 1500)
     if name == "row_192":
@@ -141,7 +143,7 @@ def _small(name):
 
 @pytest.mark.parametrize("general", [False, True])
 @pytest.mark.parametrize("name", ["one", "empty_rows_and_columns", "lanes_8", "lanes_4", "lanes_2", "two_rows",
-                                  "rows_2048", "rows_2049", "row_192", "row_193"])
+                                  "rows_2048", "scaling_outside", "rows_2049", "row_192", "row_193"])
 def test_small_lp_in_one_workgroup_matches_oracle(name, general):
     lp = _small(name)
     kw = {}
