@@ -305,7 +305,7 @@ typedef struct mipdhg_info {
     double ms_primal, ms_dual;       /* with kernel_timing: mean duration per launch  */
     int64_t n_primal, n_dual;        /* with kernel_timing: launches timed            */
     int32_t lanes_a, lanes_at, long_a, long_at; /* SpMV plan used                   */
-    double ms_graph;        /* part of ms_iter spent capturing and instantiating the
+    double ms_graph;        /* part of ms_setup spent capturing and instantiating the
                                iteration block's hipGraph                            */
     int64_t rejected;       /* step_rule 1: attempts whose step was rejected        */
 } mipdhg_info;
