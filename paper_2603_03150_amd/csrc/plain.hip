@@ -2729,9 +2729,11 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
     int rc;
     if ((rc = check_rowptr(rpa, lp.m, nnz, "A"))) return rc;
     if ((rc = check_rowptr(rpat, lp.n, nnz, "A^T"))) return rc;
-    S.longest = 0;
-    for (int64_t i = 0; i < m; ++i) S.longest = std::max<int64_t>(S.longest, rpa[i + 1] - rpa[i]);
-    for (int64_t j = 0; j < n; ++j) S.longest = std::max<int64_t>(S.longest, rpat[j + 1] - rpat[j]);
+    if (std::max(m, n) <= (int64_t)kSmallRows * kSmallBlock) {  // (else not small, whatever its rows)
+        S.longest = 0;
+        for (int64_t i = 0; i < m; ++i) S.longest = std::max<int64_t>(S.longest, rpa[i + 1] - rpa[i]);
+        for (int64_t j = 0; j < n; ++j) S.longest = std::max<int64_t>(S.longest, rpat[j + 1] - rpat[j]);
+    }
     S.hpa = make_plan(rpa, lp.m, o.lanes_a, o.long_row);
     S.hpat = make_plan(rpat, lp.n, o.lanes_at, o.long_row);
     if (!S.hpa.long_rows.empty())
