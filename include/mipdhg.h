@@ -156,7 +156,16 @@ typedef struct mipdhg_options {
                                takes longer to build than 3's, so it pays on
                                long solves and the autotuner does not try
                                it); UNSUPPORTED when the matrix does not fit
-                               the layouts                                 [0] */
+                               the layouts.  0 with the default tile shapes (each
+                               field below and *_at at 0 or its default): an LP
+                               whose scaled copies fit one workgroup's LDS (at
+                               most 2,048 rows and columns, rows and columns of
+                               at most 192 entries) has the scaling, the power
+                               iteration and a block's iterations but its first
+                               and last run by that workgroup, without tiles; the
+                               sums of a row are then added in another order.  A
+                               kind or a tile shape named otherwise runs as named.
+                                                                           [0] */
     int32_t tile_nnz;       /* LDS tiles: nonzeros per tile, 256..8192 (0 = 2048) */
     int32_t tile_rows;      /* LDS tiles: rows per tile, 1..512 (0 = 512)           */
     int32_t short_row;      /* LDS tile row sums: 0 or -1 = every thread reduces an equal chunk of

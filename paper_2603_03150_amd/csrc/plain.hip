@@ -2321,15 +2321,22 @@ struct Solver {
     // than kSmallRows rows or columns, and no row is so long that its lanes
     // take more than the tile kernels' 13 us for an iteration (192 entries in
     // one lane at 0.15 us to eight of them, 3.6 us).  The adaptive step, the
-    // average of an epoch's points and the panel layouts keep their kernels.
+    // average of an epoch's points and the panel layouts keep their kernels,
+    // and so does a call that names a kernel or a tile shape of its own.
     static constexpr int kSmallRowLen = 192;
     static constexpr int kSmallLdsMax = 155 * 1024;
     int64_t longest = kSmallRowLen + 1;  // of the rows of A and of A^T, once they are known
     SmallLds small_layout() const { return small_lds(lp.m, lp.n, lp.nnz, sizeof(T), sizeof(V)); }
+    bool default_kernels() const {
+        return iter_kind(o, lp.m, lp.n) == 0 && tile_nnz_of(o) == kTileNnzDefault &&
+               tile_rows_of(o) == kTileRowsDefault && short_row_of(o) == kShortRowDefault &&
+               tile_nnz_at_of(o) == kTileNnzDefault && tile_rows_at_of(o) == kTileRowsDefault &&
+               short_row_at_of(o) == kShortRowDefault;
+    }
     bool small() const {
         const int64_t cap = (int64_t)kSmallRows * kSmallBlock;
-        return !adaptive() && !o.restart_avg && !panel() && lp.m <= cap && lp.n <= cap && longest <= kSmallRowLen &&
-               lp.nnz <= kSmallLdsMax && small_layout().bytes <= kSmallLdsMax;
+        return default_kernels() && !adaptive() && !o.restart_avg && lp.m <= cap && lp.n <= cap &&
+               longest <= kSmallRowLen && lp.nnz <= kSmallLdsMax && small_layout().bytes <= kSmallLdsMax;
     }
     SmallMat small_side(bool a) const {
         SmallMat s{a ? ta : tat, a ? (sorted() ? w.col_a : lp.a_col) : (sorted() ? w.col_at : lp.at_col),

@@ -1,0 +1,54 @@
+"""What the library's host code launches, where, and what it waits for, on the
+stand-in HIP runtime of hip_host_calls.c (no GPU)."""
+import os
+import shutil
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+pytestmark = pytest.mark.skipif(shutil.which("gcc") is None, reason="needs a C compiler")
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    shim = str(tmp_path_factory.mktemp("shim") / "libhiphost.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", shim, os.path.join(HERE, "hip_host_calls.c")], check=True)
+    sys.path.insert(0, ROOT)
+    from paper_2603_03150_amd import _lib
+    if not os.path.exists(_lib.LIB_PATH):
+        from paper_2603_03150_amd.build import build
+        build()
+
+    def go(code):
+        head = f"import sys; sys.path.insert(0, {HERE!r})\nfrom host_calls import *\nh = Host({shim!r})\n"
+        p = subprocess.run([sys.executable, "-c", head + textwrap.dedent(code)], capture_output=True, text=True,
+                           timeout=120)
+        assert p.returncode == 0, p.stdout + p.stderr
+
+    return go
+
+
+# --- the kernels of an LP that one workgroup holds -------------------------------------------------------------
+@pytest.mark.parametrize("opts,small", [
+    (dict(), True), (dict(gather_order=1), True), (dict(lanes_a=4, long_row=9), True),
+    (dict(tile_nnz=2048, tile_rows=512, short_row=-1), True),  # the defaults by their values
+    (dict(tile_nnz_at=2048, tile_rows_at=512, short_row_at=-1), True),
+    (dict(spmv_kind=1), False), (dict(spmv_kind=2), False), (dict(tile_nnz=1024), False), (dict(tile_rows=64), False),
+    (dict(short_row=32), False), (dict(tile_nnz_at=1024), False), (dict(tile_rows_at=64), False),
+    (dict(short_row_at=32), False),
+])
+def test_a_small_lp_runs_the_kernels_the_caller_asked_for(run, opts, small):
+    run(f"""
+    assert h.solve(h.lp(20, 60, [3] * 60), h.options(max_iter=128, **{opts!r})) >= 0
+    k = h.kernels()
+    for name in ("k_small_iters", "k_small_power", "k_small_scale"):
+        assert any(name in n for n in k) == {small}, name
+    kind = {opts!r}.get("spmv_kind", 0)
+    iters = ["k_iter_persist" if kind == 2 else "k_iter_tiled" if kind == 0 else "6k_iterI"]
+    assert any(iters[0] in n for n in k), sorted(set(k))
+    """)
