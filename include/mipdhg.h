@@ -179,11 +179,16 @@ typedef struct mipdhg_options {
                                1 = hipEvents around every launch of the solve (disables
                                graphs); 2 = after the solve, 256 back-to-back launches of
                                each kernel between two events (no per-launch event cost;
-                               the solve's outputs are not changed)             [0] */
+                               the solve's outputs are not changed).  Iterations that
+                               one launch runs for a small LP (see spmv_kind) count one
+                               launch of each kernel, with half their share of that
+                               launch's time                                    [0] */
     /* Debug trace of the scaled iterates after each of the first trace_iters
      * iterations (device float64 arrays, row-major [trace_iters][n or m]):
      * the state (x, y) after the update and the projected point (x_hat, y_hat).
-     * Any of the four may be NULL.  Tracing disables graphs. */
+     * Any of the four may be NULL.  Tracing disables graphs, and a small LP
+     * (see spmv_kind) then runs one iteration to a launch; the iterates are
+     * those of the solve without it. */
     int32_t trace_iters;    /*                                             [0] */
     double *trace_x, *trace_y, *trace_xhat, *trace_yhat;
     /* Optional warm start in the original space (device float64, may be NULL). */

@@ -711,7 +711,9 @@ struct SmallSide {
 };
 
 // `count` iterations from a.it on, none of them a block's first or last: the
-// arithmetic of IterEpi, the state in registers and LDS
+// arithmetic of IterEpi, the state in registers and LDS.  (A traced solve runs
+// them one to a launch, with the flag F_HAT: the same code and so the same
+// iterates.)
 template <typename T, typename V, typename Acc, bool GENP, bool GEND>
 __global__ __launch_bounds__(kSmallBlock) void k_small_iters(IterArgs<T, V> p, IterArgs<T, V> d, SmallMat ma,
                                                              SmallMat mat, int count) {
@@ -750,6 +752,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_iters(IterArgs<T, V> p, I
     for (int i = tid; i < m; i += kSmallBlock) vy[i] = d.state[i];
     const double tau = ctrl->tau, sig = ctrl->sigma, rho = p.rho, opr = 1.0 + p.rho;
     const int64_t k0 = ctrl->k_base + p.it;
+    const bool hat = (p.flags & F_HAT) != 0;
     if (tid == 0) {
         vy[m] = (T)0;
         vx[n] = (T)0;
@@ -778,6 +781,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_iters(IterArgs<T, V> p, I
                 dh = dh < -a0 ? -a0 : dh;
             }
             if (first_c) vx[j] = (T)(2.0 * dh - o);
+            if (hat && first_c) p.hat[j] = (T)(a0 + dh);
             u[r] = (T)(w * (opr * dh - rho * o));
         }
         __syncthreads();
@@ -793,6 +797,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_iters(IterArgs<T, V> p, I
                 else if (sense[r] == MIPDHG_SENSE_LE) dh = dh > -a0 ? -a0 : dh;
             }
             if (first_r) vy[i] = (T)(w * (opr * dh - rho * o));
+            if (hat && first_r) d.hat[i] = (T)((double)d.anchor[i] + dh);
         }
         __syncthreads();
     }
@@ -2354,10 +2359,11 @@ struct Solver {
             MIP_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLdsMax));
         return 0;
     }
-    int launch_small(int it, int count) {
+    // iterations it to it + count - 1 of a block, in one launch
+    int launch_small(int it, int count, int flags) {
         IterArgs<T, V> p, d;
-        fill_iter(p, true, it, 0);
-        fill_iter(d, false, it, 0);
+        fill_iter(p, true, it, flags);
+        fill_iter(d, false, it, flags);
         const SmallMat ma = small_side(true), mat = small_side(false);
         const int lds = small_layout().bytes;
         const bool gp = gen_primal(), gd = gen_dual();
@@ -2632,18 +2638,23 @@ struct Solver {
     // scaled iterates after iteration t_first + i are exported.
     int enqueue_block(int nit, int64_t t_first, bool trace) {
         int rc;
+        // a small LP's middle iterations: one launch, or traced one each
+        auto middle = [&](int it) { return small() && it > 0 && it < nit - 1; };
         for (int it = 0; it < nit; ++it) {
-            if (it == 1 && nit > 2 && small() && !trace && !timing) {
-                if ((rc = launch_small(1, nit - 2))) return rc;
-                it = nit - 1;
-            }
             const bool last = it == nit - 1;
             const int flags = (it == 0 ? F_FIRST : 0) | (last ? (F_EVAL | F_HAT) : 0) | (trace ? F_HAT : 0);
             if (timing) MIP_HIP(hipEventRecord(tev[3 * it], stream));
-            if ((rc = launch_primal(it, flags))) return rc;
-            if (timing) MIP_HIP(hipEventRecord(tev[3 * it + 1], stream));
-            if ((rc = launch_dual(it, flags))) return rc;
-            if (timing) MIP_HIP(hipEventRecord(tev[3 * it + 2], stream));
+            if (middle(it)) {
+                const int count = trace ? 1 : nit - 2;
+                if ((rc = launch_small(it, count, flags))) return rc;
+                if (timing) MIP_HIP(hipEventRecord(tev[3 * it + 2], stream));
+                it += count - 1;
+            } else {
+                if ((rc = launch_primal(it, flags))) return rc;
+                if (timing) MIP_HIP(hipEventRecord(tev[3 * it + 1], stream));
+                if ((rc = launch_dual(it, flags))) return rc;
+                if (timing) MIP_HIP(hipEventRecord(tev[3 * it + 2], stream));
+            }
             if (adaptive()) {
                 if ((rc = launch_step(it, flags))) return rc;
                 if (last && (nit & 1)) {  // an odd block ends in the second buffers
@@ -2680,6 +2691,13 @@ struct Solver {
             MIP_HIP(hipEventSynchronize(tev[3 * (nit - 1) + 2]));
             for (int it = 0; it < nit; ++it) {
                 float a = 0.f, b = 0.f;
+                if (middle(it)) {  // a launch's time, half to each step
+                    if (it > 1 && !trace) continue;
+                    MIP_HIP(hipEventElapsedTime(&a, tev[3 * it], tev[3 * it + 2]));
+                    ms_p += 0.5 * a;
+                    ms_d += 0.5 * a;
+                    continue;
+                }
                 MIP_HIP(hipEventElapsedTime(&a, tev[3 * it], tev[3 * it + 1]));
                 MIP_HIP(hipEventElapsedTime(&b, tev[3 * it + 1], tev[3 * it + 2]));
                 ms_p += a;
@@ -3180,9 +3198,14 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
         MIP_HIP(hipMemcpyAsync(&w.ctrl->status, &running, sizeof(int32_t), hipMemcpyHostToDevice, stream));
         S.stream = stream;
         MIP_HIP(hipEventRecord(te[0], stream));
-        for (int r = 0; r < R && !rc; ++r) rc = S.launch_primal(1, 0);
-        MIP_HIP(hipEventRecord(te[1], stream));
-        for (int r = 0; r < R && !rc; ++r) rc = S.launch_dual(1, 0);
+        if (S.small()) {  // R iterations in the one launch that such a solve runs, half the time to each step
+            rc = S.launch_small(1, R, 0);
+            MIP_HIP(hipEventRecord(te[1], stream));
+        } else {
+            for (int r = 0; r < R && !rc; ++r) rc = S.launch_primal(1, 0);
+            MIP_HIP(hipEventRecord(te[1], stream));
+            for (int r = 0; r < R && !rc; ++r) rc = S.launch_dual(1, 0);
+        }
         MIP_HIP(hipEventRecord(te[2], stream));
         MIP_HIP(hipMemcpyAsync(&w.ctrl->status, &cf.status, sizeof(int32_t), hipMemcpyHostToDevice, stream));
         const int32_t no = 0;  // the timing runs moved the iterates: not resumable
@@ -3192,6 +3215,7 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
         MIP_HIP(hipEventElapsedTime(&a, te[0], te[1]));
         MIP_HIP(hipEventElapsedTime(&b, te[1], te[2]));
         if (rc) return rc;
+        if (S.small()) a = b = 0.5f * a;
         S.ms_p = a;
         S.ms_d = b;
         S.n_p = S.n_d = R;

@@ -52,3 +52,24 @@ def test_a_small_lp_runs_the_kernels_the_caller_asked_for(run, opts, small):
     iters = ["k_iter_persist" if kind == 2 else "k_iter_tiled" if kind == 0 else "6k_iterI"]
     assert any(iters[0] in n for n in k), sorted(set(k))
     """)
+
+
+@pytest.mark.parametrize("opts,launches", [
+    (dict(), 2), (dict(use_graph=0), 2), (dict(kernel_timing=1), 2),
+    (dict(kernel_timing=2), 3),                # and one for the timing after the solve
+    (dict(trace_iters=128), 2 * 62), (dict(trace_iters=3, kernel_timing=1), 2 * 62),
+])
+def test_a_small_lp_traced_or_timed_is_the_same_solve(run, opts, launches):
+    run(f"""
+    assert h.solve(h.lp(20, 60, [3] * 60), h.options(max_iter=128, eval_every=64, **{opts!r})) >= 0
+    graph = sum(w == "graph" for w, _, _ in h.log())
+    k = h.kernels()
+    times = 2 if graph else 1  # the graph's launches are noted once
+    small = sum("k_small_iters" in n for n in k)
+    tiles = sum("k_iter_tiled" in n for n in k)
+    if graph:
+        assert graph == 2
+        small, tiles = small + 1, tiles + 4
+    # a block's first and last iteration on the tiles, primal and dual
+    assert (small, tiles) == ({launches}, 8), (small, tiles)
+    """)
