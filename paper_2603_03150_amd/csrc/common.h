@@ -23,6 +23,16 @@ constexpr int kMaxRowBlocks = kMaxShortBlocks + kMaxLongBlocks;
 void set_error(const char* fmt, ...);
 void clear_error();
 
+// Waits for a stream when the call that launched on it is left early: after an
+// error nothing may still write what the caller then frees or reuses.
+struct StreamDrain {
+    hipStream_t s = nullptr;
+    bool armed = true;
+    ~StreamDrain() {
+        if (armed) (void)hipStreamSynchronize(s);
+    }
+};
+
 #define MIP_HIP(expr)                                                              \
     do {                                                                           \
         hipError_t e_ = (expr);                                                    \

@@ -2731,6 +2731,41 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
     S.rdo = r_d;
     PlainWs& w = S.w;
     const int64_t m = lp.m, n = lp.n, nnz = lp.nnz;
+    // objects of the runtime that the solve uses, released on every return
+    // path, once the streams have been waited for (the destructors run from
+    // the last one declared)
+    // blocks in flight: one running and one queued behind it, so that the GPU
+    // never waits for the host, and one block (returning at once) runs past
+    // the one that ends the solve
+    constexpr int kDepth = 2;
+    struct LoopRes {
+        hipGraphExec_t gexec = nullptr;
+        hipGraph_t g = nullptr;
+        hipStream_t cap = nullptr;
+        Ctrl* ring = nullptr;  // pinned ring of status words, one per block in flight
+        hipEvent_t ev[kDepth] = {};
+        ~LoopRes() {
+            for (auto e : ev)
+                if (e) (void)hipEventDestroy(e);
+            if (ring) (void)hipHostFree(ring);
+            if (gexec) (void)hipGraphExecDestroy(gexec);
+            if (g) (void)hipGraphDestroy(g);
+            if (cap) (void)hipStreamDestroy(cap);
+        }
+    } res;
+    struct SideStream {
+        hipStream_t s = nullptr;
+        hipEvent_t scaled = nullptr, built = nullptr;
+        ~SideStream() {
+            if (scaled) (void)hipEventDestroy(scaled);
+            if (built) (void)hipEventDestroy(built);
+            if (s) {
+                (void)hipStreamSynchronize(s);
+                (void)hipStreamDestroy(s);
+            }
+        }
+    } side;
+    StreamDrain drain{stream};
     // a resumed solve checks the state's sizes and options before setup
     // writes to the workspace (the control block is at its start whatever
     // the layout), so that a refused resume leaves the state as it was
@@ -2856,15 +2891,6 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
     // A's panel layout for the dual step (same scaled values as the copies) is
     // built on a second stream, so that its host-side steps overlap the power
     // iteration; the first stream waits for it before the loop
-    struct SideStream {
-        hipStream_t s = nullptr;
-        hipEvent_t scaled = nullptr, built = nullptr;
-        ~SideStream() {
-            if (scaled) (void)hipEventDestroy(scaled);
-            if (built) (void)hipEventDestroy(built);
-            if (s) (void)hipStreamDestroy(s);
-        }
-    } side;
     if (S.panel()) {
         MIP_HIP(hipStreamCreateWithFlags(&side.s, hipStreamNonBlocking));
         MIP_HIP(hipEventCreateWithFlags(&side.scaled, hipEventDisableTiming));
@@ -2943,11 +2969,7 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
     if (S.panel()) {
         rc = panel_build<V>(rpa, lp.m, lp.n, nnz, lp.a_rowptr, lp.a_col, lp.a_val, (const double*)w.d_row,
                             (const double*)w.d_col, S.panel_w(), sizeof(T), w.pl, side.s);
-        if (rc) {
-            (void)hipStreamSynchronize(side.s);
-            (void)hipStreamSynchronize(stream);
-            return rc;
-        }
+        if (rc) return rc;
         if (S.rowpanel()) {
             int dev = 0, cus = 256;
             if (hipGetDevice(&dev) != hipSuccess ||
@@ -2955,11 +2977,7 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
                 cus = 256;
             rc = rowpanel_build<V>(rpat, lp.n, lp.m, nnz, lp.at_rowptr, lp.at_col, lp.at_val, lp.a_rowptr, lp.a_col,
                                    (const double*)w.d_col, (const double*)w.d_row, S.panel_w(), cus, w.rl, side.s);
-            if (rc) {
-                (void)hipStreamSynchronize(side.s);
-                (void)hipStreamSynchronize(stream);
-                return rc;
-            }
+            if (rc) return rc;
         }
         MIP_HIP(hipEventRecord(side.built, side.s));
         MIP_HIP(hipStreamWaitEvent(stream, side.built, 0));
@@ -2976,27 +2994,6 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
     const int E = o.eval_every;
     const bool trace = o.trace_iters > 0;
     const bool graph = o.use_graph && !trace && o.kernel_timing != 1;
-    // host objects of the loop, released on every return path (after the
-    // stream has been synchronised on the normal one)
-    // blocks in flight: one running and one queued behind it, so that the GPU
-    // never waits for the host, and one block (returning at once) runs past
-    // the one that ends the solve
-    constexpr int kDepth = 2;
-    struct LoopRes {
-        hipGraphExec_t gexec = nullptr;
-        hipGraph_t g = nullptr;
-        hipStream_t cap = nullptr;
-        Ctrl* ring = nullptr;  // pinned ring of status words, one per block in flight
-        hipEvent_t ev[kDepth] = {};
-        ~LoopRes() {
-            for (auto e : ev)
-                if (e) (void)hipEventDestroy(e);
-            if (ring) (void)hipHostFree(ring);
-            if (gexec) (void)hipGraphExecDestroy(gexec);
-            if (g) (void)hipGraphDestroy(g);
-            if (cap) (void)hipStreamDestroy(cap);
-        }
-    } res;
     // The block of iterations as a graph, built while the device still works
     // off the power iteration (the host is ahead of it there): 0.5 to 0.7 ms
     // that were idle time of the device after the set-up (256 iterations on a
@@ -3010,7 +3007,6 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
         rc = S.enqueue_block(E, 1, false);
         hipError_t ce = hipStreamEndCapture(res.cap, &res.g);
         S.stream = stream;
-        if (rc || ce != hipSuccess) (void)hipStreamSynchronize(stream);  // the set-up still runs
         if (rc) return rc;
         MIP_HIP(ce);
         MIP_HIP(hipGraphInstantiate(&res.gexec, res.g, nullptr, nullptr, 0));
@@ -3225,6 +3221,7 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
     if (d_row) MIP_HIP(hipMemcpyAsync(d_row, w.d_row, m * 8, hipMemcpyDeviceToDevice, stream));
     if (d_col) MIP_HIP(hipMemcpyAsync(d_col, w.d_col, n * 8, hipMemcpyDeviceToDevice, stream));
     MIP_HIP(hipStreamSynchronize(stream));
+    drain.armed = false;
     const auto t3 = clk::now();
     if (info) {
         memset(info, 0, sizeof(*info));

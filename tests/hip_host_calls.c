@@ -18,7 +18,7 @@ static char fail_[64];
 static int skip_;
 static uintptr_t next_ = 0x100;
 static hipStream_t masked_ = (hipStream_t)-1;
-static int ioctl_err_;
+static int last_err_;
 
 static void note(const char *what, const char *name, hipStream_t s) {
     char line[512];
@@ -31,12 +31,12 @@ static void note(const char *what, const char *name, hipStream_t s) {
 static hipError_t ret(const char *name) {
     if (!strcmp(fail_, name) && skip_-- == 0) {
         note("fail", name, 0);
-        return ioctl_err_ = 1;
+        return last_err_ = 1;
     }
     return 0;
 }
 const char *shim_log(void) { return log_ ? log_ : ""; }
-void shim_reset(void) { len_ = 0; if (log_) log_[0] = 0; fail_[0] = 0; }
+void shim_reset(void) { len_ = 0; last_err_ = 0; if (log_) log_[0] = 0; fail_[0] = 0; }
 void shim_fail(const char *name, int skip) { snprintf(fail_, sizeof(fail_), "%s", name); skip_ = skip; }
 void shim_mask(hipStream_t s) { masked_ = s; }
 
@@ -67,7 +67,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t sh
     return ret("hipLaunchKernel");
 }
 
-hipError_t hipGetLastError(void) { int e = ioctl_err_; ioctl_err_ = 0; return e; }
+hipError_t hipGetLastError(void) { int e = last_err_; last_err_ = 0; return e; }
 const char *hipGetErrorString(hipError_t e) { return e ? "made to fail" : "no error"; }
 hipError_t hipGetDevice(int *d) { *d = 0; return ret("hipGetDevice"); }
 hipError_t hipDeviceGetAttribute(int *v, int a, int d) { (void)a; (void)d; *v = 256; return ret("hipDeviceGetAttribute"); }

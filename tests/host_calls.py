@@ -68,6 +68,77 @@ class Host:
         info = self.L.InfoStruct()
         return self.lib.mipdhg_solve(C.byref(lp), C.byref(o), 1e-6, ws, nb.value, stream, *out, C.byref(info))
 
+    def batch(self, lps):
+        """A block-diagonal batch of m x n LPs given as (m, n, counts)."""
+        ms, ns, zs = ([f(l) for l in lps] for f in (lambda l: l[0], lambda l: l[1], lambda l: int(np.sum(l[2]))))
+        off = [np.concatenate([[0], np.cumsum(v)]) for v in (ms, ns, zs)]
+        rows, cols = [], []
+        for (m, n, counts), r0, c0 in zip(lps, off[0], off[1]):
+            rows += [r0 + np.sort((j + np.arange(k)) % m) for j, k in enumerate(counts)]
+            cols += [np.full(k, c0 + j) for j, k in enumerate(counts)]
+        rows, cols = np.concatenate(rows).astype(np.int32), np.concatenate(cols).astype(np.int32)
+        order = np.lexsort((cols, rows))
+        b = self.L.BatchStruct()
+        b.count = len(lps)
+        b.row_off, b.col_off = self.arr(off[0].astype(np.int32)), self.arr(off[1].astype(np.int32))
+        b.nnz_off = self.arr(off[2].astype(np.int64))
+        s = b.whole
+        s.m, s.n, s.nnz = int(off[0][-1]), int(off[1][-1]), int(off[2][-1])
+        s.a_rowptr = self.arr(np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=s.m))]).astype(np.int32))
+        s.at_rowptr = self.arr(np.concatenate([[0], np.cumsum(np.bincount(cols, minlength=s.n))]).astype(np.int32))
+        s.a_col, s.at_col = self.arr(cols[order]), self.arr(rows)
+        s.a_val, s.at_val = self.arr(np.ones(rows.size)), self.arr(np.ones(rows.size))
+        s.b, s.c = self.arr(np.ones(s.m)), self.arr(np.ones(s.n))
+        return b
+
+    def solve_batched(self, b, o, stream=0):
+        nb = C.c_size_t(0)
+        assert self.lib.mipdhg_batch_workspace_size(C.byref(b), C.byref(o), C.byref(nb)) == 0
+        w = b.whole
+        out = [self.buf(8 * k) for k in (w.n, w.m, w.n, w.m, w.n)]
+        eps = self.arr(np.full(b.count, 1e-6))
+        info = (self.L.InfoStruct * b.count)()
+        return self.lib.mipdhg_solve_batched(C.byref(b), C.byref(o), eps, self.buf(nb.value), nb.value, stream, *out,
+                                             info)
+
+    def unrolled(self, b, o, stream=0, K=20, ckpt=10):
+        nb = C.c_size_t(0)
+        assert self.lib.mipdhg_unrolled_tape_size(C.byref(b), C.byref(o), K, ckpt, C.byref(nb)) == 0
+        tape, w = self.buf(nb.value), b.whole
+        rc = self.lib.mipdhg_unrolled_forward(C.byref(b), C.byref(o), K, ckpt, 0, tape, nb.value, stream,
+                                              self.buf(8 * w.n))
+        if rc < 0:
+            return rc
+        return self.lib.mipdhg_unrolled_backward(C.byref(b), C.byref(o), K, ckpt, tape, nb.value, self.buf(8 * w.n),
+                                                 stream, self.buf(8 * w.n), self.buf(8 * w.m))
+
+    def errors_leave_nothing_running(self, call, names):
+        """call() with each call of each of the runtime functions `names` made to fail once: it reports the error, and
+        every stream that it launched a kernel on has been waited for since (a captured launch runs nothing).
+        Returns the number of failures tried."""
+        tried = 0
+        for name in names:
+            for skip in range(1000):
+                self.shim.shim_reset()
+                self.shim.shim_fail(name.encode(), skip)
+                rc = call()
+                log = self.log()
+                if not any(w == "fail" for w, _, _ in log):
+                    break
+                tried += 1
+                if rc >= 0:  # a failure that the call can do without
+                    continue
+                capturing, busy = set(), set()
+                for w, n, s in log:
+                    if w == "capture":
+                        (capturing.add if n == "begin" else capturing.discard)(s)
+                    elif (w == "kernel" and s not in capturing) or w == "graph":
+                        busy.add(s)
+                    elif w == "sync":
+                        busy.discard(s)
+                assert not busy, (name, skip, sorted(busy), log[-8:])
+        return tried
+
     def log(self):
         """The calls since the last reset, as (what, name, stream)."""
         lines = [l.split(" ") for l in self.shim.shim_log().decode().splitlines()]

@@ -73,3 +73,19 @@ def test_a_small_lp_traced_or_timed_is_the_same_solve(run, opts, launches):
     # a block's first and last iteration on the tiles, primal and dual
     assert (small, tiles) == ({launches}, 8), (small, tiles)
     """)
+
+
+# --- errors -----------------------------------------------------------------------------------------------------
+SETUP_CALLS = ("hipStreamCreateWithFlags", "hipStreamBeginCapture", "hipStreamEndCapture", "hipGraphInstantiate",
+               "hipHostMalloc", "hipEventCreateWithFlags", "hipMemcpyAsync", "hipGraphLaunch", "hipEventRecord",
+               "hipEventSynchronize", "hipFuncSetAttribute")
+
+
+@pytest.mark.parametrize("opts", [dict(), dict(spmv_kind=2, kernel_timing=1), dict(spmv_kind=3, panel_width=64),
+                                  dict(kernel_timing=2)])
+def test_an_error_in_a_solve_leaves_nothing_running(run, opts):
+    run(f"""
+    lp = h.lp(20, 60, [3] * 60)
+    o = h.options(max_iter=192, **{opts!r})
+    assert h.errors_leave_nothing_running(lambda: h.solve(lp, o, stream=7), {SETUP_CALLS!r}) >= 10
+    """)
