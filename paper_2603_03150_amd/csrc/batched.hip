@@ -608,6 +608,7 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
     if (lds > 150 * 1024 || max_m > kInstMaxDim || max_n > kInstMaxDim)
         return set_error("largest instance needs %d bytes of LDS (limit 150 KiB): m + n too large", lds),
                MIPDHG_ERR_UNSUPPORTED;
+    StreamDrain drain{stream};
     int dev = 0, cus = 256;
     MIP_HIP(hipGetDevice(&dev));
     MIP_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -749,12 +750,7 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
         else if (c == 1) rc = launch_class<T, V, Acc, kClassBs[1]>(ac, cus, cs);
         else if (c == 2) rc = launch_class<T, V, Acc, kClassBs[2]>(ac, cus, cs);
         else rc = launch_class<T, V, Acc, kClassBs[3]>(ac, cus, cs);
-        if (rc) {  // the launches before it still use the workspace
-            for (int q = 0; q < kClasses; ++q)
-                if (side.s[q]) (void)hipStreamSynchronize(side.s[q]);
-            (void)hipStreamSynchronize(stream);
-            return rc;
-        }
+        if (rc) return rc;
     }
     for (int c = 0; c < kClasses; ++c)
         if (side.s[c]) {
@@ -766,6 +762,7 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
     std::vector<BInst> res(B);
     MIP_HIP(hipMemcpyAsync(res.data(), w.info, sizeof(BInst) * B, hipMemcpyDeviceToHost, stream));
     MIP_HIP(hipStreamSynchronize(stream));
+    drain.armed = false;
     float kms = 0.f;
     MIP_HIP(hipEventElapsedTime(&kms, e0, e1));
     const auto t2 = clk::now();

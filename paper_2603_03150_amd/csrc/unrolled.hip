@@ -726,6 +726,7 @@ static int unrolled_impl(const mipdhg_batch& bt, const mipdhg_options& o, int K,
     const int lds = (int)(((size_t)max_m + (size_t)max_n) * sizeof(T) + 16);  // the vectors'
     if (lds > 150 * 1024 || max_m > kInstMaxDim || max_n > kInstMaxDim)
         return set_error("instance too large for LDS (%d bytes)", lds), MIPDHG_ERR_UNSUPPORTED;
+    StreamDrain drain{stream};
     const mipdhg_lp& lp = bt.whole;
     if (!backward) {
         std::vector<int32_t> wo(B + 1, 0);
@@ -840,6 +841,7 @@ static int unrolled_impl(const mipdhg_batch& bt, const mipdhg_options& o, int K,
     if (rc) return rc;
     MIP_LAUNCH_CHECK();
     MIP_HIP(hipStreamSynchronize(stream));
+    drain.armed = false;
     return 0;
 }
 

@@ -89,3 +89,25 @@ def test_an_error_in_a_solve_leaves_nothing_running(run, opts):
     o = h.options(max_iter=192, **{opts!r})
     assert h.errors_leave_nothing_running(lambda: h.solve(lp, o, stream=7), {SETUP_CALLS!r}) >= 10
     """)
+
+
+BATCH_CALLS = ("hipStreamCreateWithFlags", "hipEventCreate", "hipEventCreateWithFlags", "hipEventRecord",
+               "hipStreamWaitEvent", "hipFuncSetAttribute", "hipOccupancyMaxActiveBlocksPerMultiprocessor",
+               "hipMemcpyAsync", "hipDeviceGetAttribute", "hipEventElapsedTime")
+
+
+@pytest.mark.parametrize("opts", [dict(), dict(batch_split=400)])
+def test_an_error_in_a_batched_solve_leaves_nothing_running(run, opts):
+    run(f"""
+    # instances of every launch class (more than compute units)
+    lps = [(20, 50, [3] * 50)] * 300 + [(200, 500, [4] * 500)] * 2 + [(500, 1500, [4] * 1500), (2000, 5000, [4] * 5000)]
+    b, o = h.batch(lps), h.options("fp32", max_iter=64, **{opts!r})
+    assert h.errors_leave_nothing_running(lambda: h.solve_batched(b, o, stream=7), {BATCH_CALLS!r}) >= 20
+    """)
+
+
+def test_an_error_in_the_unrolled_map_leaves_nothing_running(run):
+    run(f"""
+    b, o = h.batch([(20, 50, [3] * 50)] * 3), h.options("fp32")
+    assert h.errors_leave_nothing_running(lambda: h.unrolled(b, o, stream=7), {BATCH_CALLS!r}) >= 10
+    """)
