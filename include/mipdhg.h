@@ -28,7 +28,9 @@
  *    the current HIP device) owned by the caller; the library neither frees nor
  *    retains them.  Structs (mipdhg_lp, mipdhg_options, mipdhg_info) live in
  *    host memory.  `stream` is a hipStream_t (NULL = the legacy default
- *    stream); all device work is enqueued on it.
+ *    stream); device work is enqueued on it, or (batched solve, panel layouts)
+ *    on streams of the library's own that start after it and that it waits
+ *    for.  The batched solve keeps to a stream that has a compute-unit mask.
  *  - Calls are synchronous with respect to the host: they return when the
  *    results are in the output buffers.
  *  - Inputs are float64 with int32 CSR indices (so nnz < 2^31).  A is CSR with

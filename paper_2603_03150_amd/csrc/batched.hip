@@ -557,6 +557,18 @@ static int lds_bytes_for(int max_m, int max_n, size_t ts) {
 constexpr int kClassBs[kClasses] = {1024, 512, 256, 64};
 constexpr int kClassLds[kClasses] = {162000, 81000, 40400, 9700};  // shares of 160 KB, less the static part
 
+// Whether work on other streams may use the compute units that work on this
+// one may (a stream can be made with a mask of them)
+static bool unmasked(hipStream_t s) {
+    if (!s) return true;
+    uint32_t own[64] = {}, all[64] = {};
+    if (hipExtStreamGetCUMask(s, 64, own) != hipSuccess || hipExtStreamGetCUMask(nullptr, 64, all) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return memcmp(own, all, sizeof(own)) == 0;
+}
+
 // One class's launches: as many workgroups as fit, never more than instances
 template <typename T, typename V, typename Acc, int BS>
 static int launch_class(const BArgs<T, V>& a, int cus, hipStream_t s) {
@@ -699,7 +711,8 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
     // one persistent launch per class with instances, all at once: the first
     // on the caller's stream, the others on side streams joined to it
     // (neither waits on another; each takes the compute units the others
-    // leave)
+    // leave); one after the other where the caller's stream is held to some of
+    // the compute units
     struct Sides {
         hipStream_t s[kClasses] = {};
         hipEvent_t fork = nullptr, join[kClasses] = {};
@@ -723,17 +736,18 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
     MIP_HIP(hipEventCreate(&side.e1));
     const hipEvent_t e0 = side.e0, e1 = side.e1;
     MIP_HIP(hipEventRecord(e0, stream));
+    const bool spread = unmasked(stream);
     int first = -1, begin = 0;
     for (int c = 0; c < kClasses; ++c) {
         if (!cl_count[c]) continue;
         hipStream_t cs = stream;
         if (first < 0) {
             first = c;
-            if (cl_count[c] < B) {
+            if (spread && cl_count[c] < B) {
                 MIP_HIP(hipEventCreateWithFlags(&side.fork, hipEventDisableTiming));
                 MIP_HIP(hipEventRecord(side.fork, stream));
             }
-        } else {
+        } else if (spread) {
             MIP_HIP(hipStreamCreateWithFlags(&side.s[c], hipStreamNonBlocking));
             MIP_HIP(hipEventCreateWithFlags(&side.join[c], hipEventDisableTiming));
             cs = side.s[c];

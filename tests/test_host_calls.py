@@ -111,3 +111,22 @@ def test_an_error_in_the_unrolled_map_leaves_nothing_running(run):
     b, o = h.batch([(20, 50, [3] * 50)] * 3), h.options("fp32")
     assert h.errors_leave_nothing_running(lambda: h.unrolled(b, o, stream=7), {BATCH_CALLS!r}) >= 10
     """)
+
+
+# --- the batched solve's streams --------------------------------------------------------------------------------
+@pytest.mark.parametrize("opts", [dict(), dict(batch_split=400)])
+@pytest.mark.parametrize("masked", [False, True])
+def test_a_batch_stays_on_a_stream_with_a_compute_unit_mask(run, opts, masked):
+    run(f"""
+    lps = [(20, 50, [3] * 50)] * 300 + [(200, 500, [4] * 500)] * 2 + [(500, 1500, [4] * 1500), (2000, 5000, [4] * 5000)]
+    b, o = h.batch(lps), h.options("fp32", max_iter=64, **{opts!r})
+    h.shim.shim_reset()
+    if {masked}:
+        h.shim.shim_mask(C.c_void_p(7))
+    assert h.solve_batched(b, o, stream=7) >= 0
+    on = [s for w, n, s in h.log() if w == "kernel" and "k_batched" in n]
+    assert len(on) >= 4 and (set(on) == {{7}}) == {masked}, on
+    # otherwise the others' streams start after the caller's work and it waits for them
+    waits = [s for w, n, s in h.log() if w == "wait"]
+    assert set(on) - {{7}} <= set(waits) and waits.count(7) == len(set(on)) - 1
+    """)
