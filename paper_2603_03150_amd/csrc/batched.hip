@@ -516,7 +516,10 @@ static uint64_t batch_fingerprint(const mipdhg_batch& bt, const mipdhg_options& 
     return h;
 }
 
-constexpr uint64_t kBatchStateMarker = 0x6d69706468672d62ull;
+// What the header says of the state's layout: another value for each (this one
+// has the vectors by position, with the positions kept; a workspace that was
+// kept from a library with another layout is refused)
+constexpr uint64_t kBatchStateMarker = 0x6d69706468672d63ull;
 
 static int check_batch(const mipdhg_batch* bt) {
     if (!bt) return set_error("batch is NULL"), MIPDHG_ERR_INVALID_ARG;

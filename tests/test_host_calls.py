@@ -130,3 +130,22 @@ def test_a_batch_stays_on_a_stream_with_a_compute_unit_mask(run, opts, masked):
     waits = [s for w, n, s in h.log() if w == "wait"]
     assert set(on) - {{7}} <= set(waits) and waits.count(7) == len(set(on)) - 1
     """)
+
+
+# --- a kept workspace -------------------------------------------------------------------------------------------
+def test_a_batch_state_of_the_former_layout_is_refused(run):
+    run("""
+    b, o = h.batch([(20, 50, [3] * 50)] * 3), h.options("fp32", max_iter=64, batch_block_iters=32)
+    nb = C.c_size_t(0)
+    assert h.lib.mipdhg_batch_workspace_size(C.byref(b), C.byref(o), C.byref(nb)) == 0
+    h.buf = lambda n, got={}, buf=h.buf: got.setdefault(n, buf(n))  # the second call's workspace is the first's
+    assert h.solve_batched(b, o) >= 0
+    o.resume = 1
+    assert h.solve_batched(b, o) >= 0
+    hdr = np.ctypeslib.as_array(C.cast(h.buf(nb.value), C.POINTER(C.c_uint64)), (2,))
+    kept = hdr.copy()
+    hdr[0] = 0x6d69706468672d62  # as written when the vectors lay by row and column
+    assert h.solve_batched(b, o) == -1 and b"does not hold the state" in h.lib.mipdhg_last_error()
+    hdr[:] = kept
+    assert h.solve_batched(b, o) >= 0
+    """)
