@@ -48,18 +48,18 @@ __global__ __launch_bounds__(kBlock) void k_ipm_spmv(const int32_t* rp, const in
     if (lane == 0) out[r] = (s0 ? s0[r] : 0.0) + sgn * acc - (s1 ? s1[r] : 0.0);
 }
 
-// scaled values (d_row[i] a_ij) d_col[j]; trans: the rows are A's columns
+// scaled values (d_row[i] a_ij) d_col[j] of A
 // (a wave to a row: with one thread its longest row's entries came one after
 // the other, 93 us on 1,000 x 4,000 and 203 us on 4,000 x 16,000 power-law LPs;
-// so 4.8 and 9.8 us (the two sides' mean))
+// so 4.8 and 9.8 us (the mean of A's and A^T's))
 __global__ void k_ipm_scale_vals(const int32_t* rp, const int32_t* col, const double* val, int32_t nrows,
-                                 const double* d_row, const double* d_col, int trans, double* out) {
+                                 const double* d_row, const double* d_col, double* out) {
     const int lane = threadIdx.x & (kWave - 1);
     const int64_t waves = (int64_t)gridDim.x * blockDim.x / kWave;
     for (int64_t r = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave; r < nrows; r += waves)
         for (int k = rp[r] + lane; k < rp[r + 1]; k += kWave) {
             const int32_t c = col[k];
-            const double dr = d_row ? d_row[trans ? c : r] : 1.0, dc = d_col ? d_col[trans ? r : c] : 1.0;
+            const double dr = d_row ? d_row[r] : 1.0, dc = d_col ? d_col[c] : 1.0;
             out[k] = (dr * val[k]) * dc;
         }
 }
@@ -75,7 +75,7 @@ __global__ void k_ipm_vscale(const double* v, const double* d, int div, int64_t 
 // Lower triangle of M = A~ diag(w) A~^T (w NULL: ones), a workgroup of one
 // wave per row i: the row is accumulated in LDS, column after column of A's
 // row i in its order, the lanes over the entries of that column (a row of
-// A~^T, whose rows k are distinct).  Every entry (i, k) is the sum over the
+// A~^T, whose rows k are distinct: the set-up has checked it).  Every entry (i, k) is the sum over the
 // common columns of i and k in increasing order, whatever the launch.  Rows
 // from m on (the padding up to ld) are those of the identity.
 // What bounds it: the loads of a column's entries, a chain of two; four
@@ -662,6 +662,55 @@ __global__ __launch_bounds__(kBlock) void k_ipm_ratio(const double* x, const dou
     block_partials<2>(v, true, part);
 }
 
+// The same of A^T, and what k_ipm_normal asks of it, against A (whose rows
+// have been checked and are in order): flags bit 1, a row pointer that is not
+// one; bit 2, an index out of range; bit 4, one that repeats in its row (of an
+// entry that A has; others are differences); and three sums for each block,
+// |a^T - a| over the entries of A^T (a = 0 where A has none), |a| of those that
+// A has, and |a| over A.  mark: an int for each entry of A, zero.  A row
+// pointer that is not one makes no access leave the arrays.
+__global__ __launch_bounds__(kBlock) void k_ipm_check_at(const int32_t* rp, const int32_t* col, const double* val,
+                                                         const int32_t* trp, const int32_t* tcol, const double* tval,
+                                                         int32_t m, int32_t n, int32_t nnz, const double* d_row,
+                                                         const double* d_col, int32_t* mark, int32_t* flags,
+                                                         double* out, double* part) {
+    const int lane = threadIdx.x & (kWave - 1);
+    const int64_t t = blockIdx.x * (int64_t)kBlock + threadIdx.x, step = (int64_t)gridDim.x * kBlock;
+    double v[3] = {0.0, 0.0, 0.0};
+    int f = t == 0 && (trp[0] != 0 || trp[n] != nnz) ? 1 : 0;
+    for (int64_t j = t / kWave; j < n; j += step / kWave) {
+        const int s0 = trp[j], e0 = trp[j + 1];
+        if (e0 < s0) f |= 1;
+        const int s = min(max(s0, 0), nnz), e = min(max(e0, s), nnz);
+        const double dc = d_col ? d_col[j] : 1.0;
+        for (int k = s + lane; k < e; k += kWave) {
+            const int i = tcol[k];
+            if (i < 0 || i >= m) {
+                f |= 2;
+                continue;
+            }
+            const double a = tval[k];
+            int lo = rp[i], hi = rp[i + 1] - 1;  // A's entry (i, j), if it has one
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (col[mid] < j) lo = mid + 1;
+                else hi = mid;
+            }
+            double b = 0.0;
+            if (lo == hi && col[lo] == j) {
+                b = val[lo];
+                if (atomicExch(mark + lo, 1)) f |= 4;
+                v[1] += fabs(b);
+            }
+            v[0] += fabs(a - b);
+            out[k] = ((d_row ? d_row[i] : 1.0) * a) * dc;
+        }
+    }
+    for (int64_t k = t; k < nnz; k += step) v[2] += fabs(val[k]);
+    if (f) atomicOr(flags, f);
+    block_partials<3>(v, false, part);
+}
+
 // sum (x + ap dx)(z + ad dz)
 __global__ __launch_bounds__(kBlock) void k_ipm_mu_at(const double* x, const double* dx, const double* z,
                                                       const double* dz, int64_t n, const double* bounds,
@@ -718,8 +767,9 @@ __global__ void k_ipm_step(double* x, const double* dx, int64_t n, double* y, co
         y[i] = y[i] + ad * dy[i];
 }
 
-__global__ void k_zero_flag(int32_t* f) {
+__global__ void k_zero_flag(int32_t* f, double* scal) {
     if (threadIdx.x < 4) f[threadIdx.x] = 0;
+    if (threadIdx.x < 16) scal[threadIdx.x] = 0.0;
 }
 
 // v + s for Mehrotra's shifts
@@ -1040,7 +1090,8 @@ int check_ipm(const mipdhg_lp* lp, const mipdhg_ipm_options* o) {
     return 0;
 }
 
-// the scaled LP in the workspace, after checking that A's rows are sorted
+// the scaled LP in the workspace, after checking that A's rows are sorted and
+// that A^T is its transpose, each entry once (in any order within a row)
 int ipm_setup(Ipm& P, const double* d_row, const double* d_col) {
     const mipdhg_lp& lp = P.lp;
     hipStream_t s = P.s;
@@ -1061,18 +1112,34 @@ int ipm_setup(Ipm& P, const double* d_row, const double* d_col) {
         }
     const IpmWs& w = P.w;
     if ((rc = P.allow_lds())) return rc;
+    hipLaunchKernelGGL(k_zero_flag, dim3(1), dim3(32), 0, s, w.flag, w.scal);
+    // (A's scaled values take the marks' place)
+    if (lp.nnz) MIP_HIP(hipMemsetAsync(w.av, 0, lp.nnz * sizeof(int32_t), s));
+    constexpr int kCheckSums = 7, kCheckFlags = 10;  // slots of w.scal
+    const int Gc = std::min(rows_grid(lp.n), kRedBlocks);
+    hipLaunchKernelGGL(k_ipm_check_at, dim3(Gc), dim3(kBlock), 0, s, lp.a_rowptr, lp.a_col, lp.a_val, lp.at_rowptr,
+                       lp.at_col, lp.at_val, lp.m, lp.n, (int32_t)lp.nnz, d_row, d_col, (int32_t*)w.av,
+                       (int32_t*)(w.scal + kCheckFlags), w.atv, w.part);
+    MIP_LAUNCH_CHECK();
+    if ((rc = P.reduce<3>(Gc, 0, kCheckSums))) return rc;
     hipLaunchKernelGGL(k_ipm_scale_vals, dim3(grid_for((int64_t)lp.m * kWave)), dim3(kBlock), 0, s, lp.a_rowptr, lp.a_col, lp.a_val,
-                       lp.m, d_row, d_col, 0, w.av);
-    hipLaunchKernelGGL(k_ipm_scale_vals, dim3(grid_for((int64_t)lp.n * kWave)), dim3(kBlock), 0, s, lp.at_rowptr, lp.at_col, lp.at_val,
-                       lp.n, d_row, d_col, 1, w.atv);
+                       lp.m, d_row, d_col, w.av);
     hipLaunchKernelGGL(k_ipm_vscale, dim3(grid_for(lp.m)), dim3(kBlock), 0, s, lp.b, d_row, 0, (int64_t)lp.m, w.bt);
     hipLaunchKernelGGL(k_ipm_vscale, dim3(grid_for(lp.n)), dim3(kBlock), 0, s, lp.c, d_col, 0, (int64_t)lp.n, w.ct);
-    hipLaunchKernelGGL(k_zero_flag, dim3(1), dim3(32), 0, s, w.flag);
     MIP_LAUNCH_CHECK();
-    double h[6];
+    double h[kCheckFlags + 1];
     if ((rc = P.sums3(w.bt, w.bt, w.bt, nullptr, lp.m, 0)) || (rc = P.sums3(w.ct, w.ct, w.ct, nullptr, lp.n, 3)) ||
-        (rc = P.fetch(h, 0, 6)))
+        (rc = P.fetch(h, 0, kCheckFlags + 1)))
         return rc;
+    int32_t bad;
+    memcpy(&bad, h + kCheckFlags, sizeof(bad));
+    if (bad & 1) return set_error("A^T: the row pointer does not rise from 0 to nnz"), MIPDHG_ERR_BAD_CSR;
+    if (bad & 2) return set_error("A^T: column index out of range"), MIPDHG_ERR_BAD_CSR;
+    if (bad & 4) return set_error("A^T: an index repeats in a row"), MIPDHG_ERR_BAD_CSR;
+    const double differ = h[kCheckSums] + (h[kCheckSums + 2] - h[kCheckSums + 1]);
+    if (differ > 1e-10 * h[kCheckSums + 2] + 1e-300)  // (false where a value is not finite: NUMERICAL, later)
+        return set_error("A^T does not match A (entries differ by %.3g of %.3g in sum)", differ, h[kCheckSums + 2]),
+               MIPDHG_ERR_TRANSPOSE;
     P.bnorm = sqrt(h[0]);
     P.cnorm = sqrt(h[3]);
     return 0;

@@ -166,3 +166,60 @@ def test_an_empty_row_is_one_replaced_pivot_per_factorization(row):
     # the row decouples: its dual stays 0 (its pivot is 1e128), the others are those of the LP without it
     assert abs(float(sol.y[row])) <= 1e-60
     assert torch.linalg.norm(sol.x - full.x) <= 1e-10 * (1 + torch.linalg.norm(full.x))
+
+
+def _corrupt(lp, what):
+    dlp = P.DeviceLP.from_lp(lp)
+    ptr = _np(dlp.at_rowptr)
+    j = int(np.argmax(np.diff(ptr) >= 2))  # a column with two entries or more
+    s = int(ptr[j])
+    if what == "decreasing row pointer":
+        dlp.at_rowptr[j + 1] = s - 1 if s else -1
+    elif what == "row pointer past the end":
+        dlp.at_rowptr[j + 1] = 10 * dlp.nnz
+    elif what == "row pointer's end":
+        dlp.at_rowptr[-1] -= 1
+    elif what == "index below":
+        dlp.at_col[s] = -1
+    elif what == "index above":
+        dlp.at_col[s] = dlp.m
+    elif what == "repeated index":
+        dlp.at_col[s + 1] = dlp.at_col[s]
+    elif what == "another row":
+        rows = set(_np(dlp.at_col)[s:int(ptr[j + 1])].tolist())
+        dlp.at_col[s] = next(i for i in range(dlp.m) if i not in rows)
+    elif what == "another value":
+        dlp.at_val[s] *= 2.0
+    return dlp
+
+
+@pytest.mark.parametrize("make", [lambda: lpgen.tiny(6, 14, 3, 0), lambda: lpgen.cfg2_sub(0, 100)])
+@pytest.mark.parametrize("what,code", [("decreasing row pointer", -2), ("row pointer past the end", -2),
+                                       ("row pointer's end", -2), ("index below", -2), ("index above", -2),
+                                       ("repeated index", -2), ("another row", -3), ("another value", -3)])
+def test_an_a_transpose_that_is_none_is_refused(make, what, code):
+    lp = make()
+    for call in (lambda d: P.ipm_solve(d),
+                 lambda d: P.ipm_warm(d, _PdhgPoint(lp.x_star, lp.y_star, lp.z_star, np.ones(lp.m), np.ones(lp.n)))):
+        with pytest.raises(P.MipdhgError) as e:
+            call(_corrupt(lp, what))
+        assert e.value.code == code and "A^T" in str(e.value)
+
+
+@pytest.mark.parametrize("m,n", [(1, 1), (1, 70), (64, 300), (65, 130)])
+def test_an_a_transpose_in_any_order_is_taken(m, n):
+    # every row of A^T reversed; the sums' order within a row changes, the normal matrix does not: rounding only
+    lp = lpgen.tiny(m, n, min(3, m), 5)
+    a = P.ipm_solve(P.DeviceLP.from_lp(lp), max_iter=3)
+    dlp = P.DeviceLP.from_lp(lp)
+    ptr = _np(dlp.at_rowptr)
+    order = np.concatenate([np.arange(e - 1, s - 1, -1) for s, e in zip(ptr[:-1], ptr[1:])])
+    order = torch.as_tensor(order, device="cuda")
+    dlp.at_col.copy_(dlp.at_col[order])
+    dlp.at_val.copy_(dlp.at_val[order])
+    b = P.ipm_solve(dlp, max_iter=3)
+    assert a.info["iters"] == b.info["iters"]
+    for u, v in ((a.x, b.x), (a.y, b.y), (a.z, b.z)):  # (1 x 1: Mehrotra's point is 0 / 0, whatever the order)
+        assert torch.equal(u.isnan(), v.isnan()) and (n == 1 or not bool(u.isnan().any()))
+        u, v = u.nan_to_num(), v.nan_to_num()
+        assert torch.linalg.norm(u - v) <= 1e-10 * (1 + torch.linalg.norm(u))
