@@ -72,6 +72,13 @@ __global__ void k_ipm_vscale(const double* v, const double* d, int div, int64_t 
     }
 }
 
+// What an infinite diagonal entry of M is stored as: an infinity among the B
+// operands of the factorization's products makes a NaN of every zero that it
+// meets.  Its row and column of the inverted factor, and with them the column of
+// the factor, are made zero, what the division by an infinite pivot gives: the
+// row decouples.
+constexpr double kInfPivot = 1.79769313486231570e308;
+
 // Lower triangle of M = A~ diag(w) A~^T (w NULL: ones), a workgroup of one
 // wave per row i: the row is accumulated in LDS, column after column of A's
 // row i in its order, the lanes over the entries of that column (a row of
@@ -128,7 +135,7 @@ __global__ __launch_bounds__(kWave) void k_ipm_normal(const int32_t* rp, const i
             }
         }
     }
-    for (int k = lane; k <= i; k += kWave) M[(int64_t)i * ld + k] = row[k];
+    for (int k = lane; k <= i; k += kWave) M[(int64_t)i * ld + k] = k == i && row[k] > kInfPivot ? kInfPivot : row[k];
 }
 
 // --- blocked Cholesky, lower triangle of a row-major ld x ld matrix in place,
@@ -261,12 +268,12 @@ __device__ __forceinline__ int factor16(double* B, int b, double* tr) {
     for (int r = 0; r < 4; ++r) {
         const bool ok = piv[r] > 1e-300;
         bad += __popcll(__ballot(!ok && l16 == 0));
-        tr[(lq + 4 * r) * kTs + l16] = E[r] * recip_sqrt(ok ? piv[r] : kBadPivot);
+        tr[(lq + 4 * r) * kTs + l16] = piv[r] >= kInfPivot ? 0.0 : E[r] * recip_sqrt(ok ? piv[r] : kBadPivot);
     }
     wave_lds_sync();
     d4 F;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) F[r] = tr[l16 * kTs + 4 * r + lq];
+    for (int r = 0; r < 4; ++r) F[r] = piv[r] >= kInfPivot ? 0.0 : tr[l16 * kTs + 4 * r + lq];
     store_frag(B, 10 + b, F);
     return bad;
 }

@@ -223,3 +223,31 @@ def test_an_a_transpose_in_any_order_is_taken(m, n):
         assert torch.equal(u.isnan(), v.isnan()) and (n == 1 or not bool(u.isnan().any()))
         u, v = u.nan_to_num(), v.nan_to_num()
         assert torch.linalg.norm(u - v) <= 1e-10 * (1 + torch.linalg.norm(u))
+
+
+@pytest.mark.parametrize("row", [0, 3, 17, 63, 64, 99])
+def test_a_row_whose_pivot_overflows_decouples(row):
+    # a row of 1e150 in a column of its own (x = 1, z = 1e-10: its pivot is 1e310) and of 1 in another: the factor's
+    # row and column divided by an infinite pivot are zeros, so the step is that of the LP without the row, with dy = 0
+    base = lpgen.tiny(99, 300, 4, 3)
+    rng = np.random.default_rng(5)
+    n = base.n + 1
+    y = rng.standard_normal(99)
+    x, z = np.append(rng.uniform(0.5, 2.0, base.n), 1.0), np.append(rng.uniform(0.5, 2.0, base.n), 1e-10)
+    c = np.append(base.c, 1e-10)
+    A0 = sp.csr_matrix(sp.hstack([base.A, sp.csr_matrix((99, 1))]))
+    extra = sp.csr_matrix(([1.0, 1e150], ([0, 0], [7, n - 1])), shape=(1, n))
+    A = sp.csr_matrix(sp.vstack([A0[:row], extra, A0[row:]]))
+    A.sort_indices()
+    AT = sp.csr_matrix(A.T)
+    AT.sort_indices()
+    start = (x, np.insert(y, row, 0.0), z)
+    sol = P.ipm_solve(P.DeviceLP(A, AT, np.insert(base.b, row, 1e150), c, "cuda"), start=[_dev(v) for v in start],
+                      max_iter=1)
+    ref = I.ipm(A0, base.b, c, (x, y, z), max_iter=1)
+    assert sol.info["iters"] == ref.iters == 1 and sol.info["pivots_replaced"] == 0
+    assert float(sol.y[row]) == 0.0
+    # (rounding of one well-conditioned Newton step, as in the tests above)
+    for got, want in ((_np(sol.x)[:-1], ref.x[:-1]), (_np(sol.x)[-1:], ref.x[-1:]), (np.delete(_np(sol.y), row), ref.y),
+                      (_np(sol.z), ref.z)):
+        assert np.linalg.norm(got - want) <= 1e-10 * (1 + np.linalg.norm(want))
