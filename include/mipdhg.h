@@ -74,7 +74,9 @@ extern "C" {
 #define MIPDHG_ERR_INVALID_ARG -1   /* null pointer, bad size or option       */
 #define MIPDHG_ERR_BAD_CSR -2       /* row pointers or column indices invalid */
 #define MIPDHG_ERR_TRANSPOSE -3     /* A^T is not the transpose of A          */
-#define MIPDHG_ERR_HIP -4           /* a HIP runtime call failed              */
+#define MIPDHG_ERR_HIP -4           /* a HIP runtime call failed, or a kernel's
+                                       bounded wait for another part of its
+                                       launch ran out (interior point)       */
 #define MIPDHG_ERR_WORKSPACE -5     /* workspace smaller than required        */
 #define MIPDHG_ERR_UNSUPPORTED -6   /* option combination not supported       */
 #define MIPDHG_ERR_NONFINITE -7     /* NaN/Inf in A, b or c                   */

@@ -482,7 +482,10 @@ __global__ __launch_bounds__(kCholBlock, 3) void k_chol_step(double* M, int32_t 
 // 64 x 64 products, of the newest block and of the inverted diagonal factor.
 // A workgroup waits only for workgroups that drew an earlier ticket, so they
 // have started and wait for none later; a wait is bounded all the same
-// (kMaxPolls), and a value that did not come is used as the NaN it is.
+// (kMaxPolls): a value that did not come is used as the NaN it is, and the
+// workgroup notes that in *late once it has passed its own values on (noted in
+// the wait itself it was 0.5 to 0.9 us of a solve's chain); the call that
+// launched this reports it as an error.
 // What bounds it: the chain over the 64-row blocks, 1.2 to 1.4 us each: 22 us
 // (lower) and 19 us (upper) at m = 1,000, 90 and 73 us at m = 4,000.  Before,
 // one workgroup swept the whole factor, a compute unit's read rate: 0.52 and
@@ -509,6 +512,7 @@ __device__ __forceinline__ double poll(const double* p) {
     }
     return __longlong_as_double((long long)v);
 }
+__device__ __forceinline__ bool unset(double v) { return (unsigned long long)__double_as_longlong(v) == kUnset; }
 __device__ __forceinline__ void publish(double* p, double v) {
     __hip_atomic_store((unsigned long long*)p, (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
@@ -516,7 +520,7 @@ __device__ __forceinline__ void publish(double* p, double v) {
 
 // y <- L^-1 b.  Thread 4 r + q: row r of the block, its columns 16 q .. 16 q + 15.
 __global__ __launch_bounds__(kBlock) void k_trsv_lower(const double* M, int32_t ld, const double* Linv, int32_t m,
-                                                       const double* b, double* y, int32_t* ticket) {
+                                                       const double* b, double* y, int32_t* ticket, int32_t* late) {
     __shared__ double xs[2][4 * 18];
     __shared__ int tk;
     if (threadIdx.x == 0) tk = atomicAdd(ticket, 1);
@@ -534,6 +538,7 @@ __global__ __launch_bounds__(kBlock) void k_trsv_lower(const double* M, int32_t 
 #pragma unroll
         for (int k = 0; k < 8; ++k) nx[k] = *(const d2*)(A + 2 * k);
     double acc = 0.0;
+    bool missed = false;
     for (int j = 0; j < i; ++j) {
 #pragma unroll
         for (int k = 0; k < 8; ++k) a[k] = nx[k];
@@ -541,8 +546,13 @@ __global__ __launch_bounds__(kBlock) void k_trsv_lower(const double* M, int32_t 
 #pragma unroll
             for (int k = 0; k < 8; ++k) nx[k] = *(const d2*)(A + (int64_t)(j + 1) * kNb + 2 * k);
         double* x = xs[j & 1];
-        if (threadIdx.x < kNb) x[18 * (threadIdx.x >> 4) + (threadIdx.x & 15)] = poll(y + (int64_t)j * kNb + threadIdx.x);
+        double got = 0.0;
+        if (threadIdx.x < kNb) {
+            got = poll(y + (int64_t)j * kNb + threadIdx.x);
+            x[18 * (threadIdx.x >> 4) + (threadIdx.x & 15)] = got;
+        }
         __syncthreads();
+        missed |= unset(got);
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
             const d2 v = *(const d2*)(x + 18 * q + 2 * k);
@@ -565,13 +575,14 @@ __global__ __launch_bounds__(kBlock) void k_trsv_lower(const double* M, int32_t 
     acc += __shfl_xor(acc, 1, kWave);
     acc += __shfl_xor(acc, 2, kWave);
     if (q == 0) publish(y + row, acc);
+    if (missed) atomicOr(late, 1);
 }
 
 // x <- L^-T b (b, y of ld entries; x of m).  Thread 64 w + c: column c of the
 // block, rows 16 w .. 16 w + 15.
 __global__ __launch_bounds__(kBlock) void k_trsv_upper_t(const double* M, int32_t ld, const double* Linv, int32_t nbk,
                                                          int32_t m, const double* b, double* y, double* x_out,
-                                                         int32_t* ticket) {
+                                                         int32_t* ticket, int32_t* late) {
     __shared__ double xs[2][kNb];
     __shared__ double part[4][kNb];
     __shared__ int tk;
@@ -588,6 +599,7 @@ __global__ __launch_bounds__(kBlock) void k_trsv_upper_t(const double* M, int32_
 #pragma unroll
         for (int k = 0; k < 16; ++k) nx[k] = A[((int64_t)(nbk - 1) * kNb + k) * L];
     double acc = 0.0;
+    bool missed = false;
     for (int j = nbk - 1; j > i; --j) {
 #pragma unroll
         for (int k = 0; k < 16; ++k) a[k] = nx[k];
@@ -595,8 +607,13 @@ __global__ __launch_bounds__(kBlock) void k_trsv_upper_t(const double* M, int32_
 #pragma unroll
             for (int k = 0; k < 16; ++k) nx[k] = A[((int64_t)(j - 1) * kNb + k) * L];
         double* x = xs[j & 1];
-        if (w == 0) x[c] = poll(y + (int64_t)j * kNb + c);
+        double got = 0.0;
+        if (w == 0) {
+            got = poll(y + (int64_t)j * kNb + c);
+            x[c] = got;
+        }
         __syncthreads();
+        missed |= unset(got);
 #pragma unroll
         for (int k = 0; k < 16; ++k) acc = fma(a[k], x[16 * w + k], acc);
     }
@@ -615,6 +632,7 @@ __global__ __launch_bounds__(kBlock) void k_trsv_upper_t(const double* M, int32_
         const int row = i * kNb + c;
         publish(y + row, v);
         if (row < m) x_out[row] = v;
+        if (missed) atomicOr(late, 1);
     }
 }
 
@@ -904,9 +922,10 @@ struct Ipm {
         hipLaunchKernelGGL(k_trsv_prepare, dim3((ld + kBlock - 1) / kBlock), dim3(kBlock), 0, s,
                            (unsigned long long*)w.y1, (unsigned long long*)w.y2, ld, w.ticket);
         hipLaunchKernelGGL(k_trsv_lower, dim3(nbk), dim3(kBlock), 0, s, (const double*)w.M, ld, (const double*)w.linv,
-                           (int32_t)m, (const double*)x, w.y1, w.ticket);
+                           (int32_t)m, (const double*)x, w.y1, w.ticket, w.flag + 1);
         hipLaunchKernelGGL(k_trsv_upper_t, dim3(nbk), dim3(kBlock), 0, s, (const double*)w.M, ld,
-                           (const double*)w.linv, nbk, (int32_t)m, (const double*)w.y1, w.y2, x, w.ticket + 1);
+                           (const double*)w.linv, nbk, (int32_t)m, (const double*)w.y1, w.y2, x, w.ticket + 1,
+                           w.flag + 1);
         MIP_LAUNCH_CHECK();
         return 0;
     }
@@ -1162,10 +1181,11 @@ int ipm_finish(Ipm& P, const double* d_row, const double* d_col, double* x, doub
     hipLaunchKernelGGL(k_ipm_vscale, dim3(grid_for(P.m)), dim3(kBlock), 0, s, (const double*)w.y, d_row, 0, P.m, y);
     hipLaunchKernelGGL(k_ipm_vscale, dim3(grid_for(P.n)), dim3(kBlock), 0, s, (const double*)w.z, d_col, 1, P.n, z);
     MIP_LAUNCH_CHECK();
-    int32_t piv = 0;
-    MIP_HIP(hipMemcpyAsync(&piv, w.flag, 4, hipMemcpyDeviceToHost, s));
+    int32_t flag[2] = {0, 0};  // pivots replaced, a triangular solve's wait that ran out
+    MIP_HIP(hipMemcpyAsync(flag, w.flag, sizeof(flag), hipMemcpyDeviceToHost, s));
     MIP_HIP(hipStreamSynchronize(s));
-    info->pivots_replaced = piv;
+    info->pivots_replaced = flag[0];
+    if (flag[1]) return set_error("a triangular solve gave up waiting for an earlier block of rows"), MIPDHG_ERR_HIP;
     return 0;
 }
 

@@ -149,3 +149,25 @@ def test_a_batch_state_of_the_former_layout_is_refused(run):
     hdr[:] = kept
     assert h.solve_batched(b, o) >= 0
     """)
+
+
+# --- the interior point's triangular solves ---------------------------------------------------------------------
+def test_a_triangular_solve_whose_wait_ran_out_is_an_error(run):
+    run("""
+    lp = h.lp(2, 3, [1, 2, 1])
+    nb = C.c_size_t(0)
+    assert h.lib.mipdhg_ipm_workspace_size(C.byref(lp), C.byref(nb)) == 0
+    ws = h.buf(nb.value)
+    words = np.ctypeslib.as_array(C.cast(ws, C.POINTER(C.c_int32)), (nb.value // 4,))
+    assert h.ipm(lp, ws, nb.value) >= 0
+    # the counters (replaced pivots, waits that ran out) start one of the workspace's slices, after the inverses: a
+    # kernel that noted a wait there (kernels do not run here) is reported, a replaced pivot is no error
+    found = []
+    for at in range(0, nb.value // 4, 64):
+        for word in (0, 1):
+            words[:] = 0
+            words[at + word] = 1
+            if h.ipm(lp, ws, nb.value) == -4 and b"gave up waiting" in h.lib.mipdhg_last_error():
+                found.append((at, word))
+    assert len(found) == 1 and found[0][1] == 1, found
+    """)
