@@ -583,8 +583,8 @@ __global__ __launch_bounds__(kBlock) void k_iter_persist(IterArgs<T, V> a, TileP
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallRows = 2;  // rows (and columns) a thread holds
 
-struct SmallMat {  // one side of the scaled copy, as the tile kernels read it
-    TilePlan tp;
+struct SmallMat {  // one side's rows (row-major, as the caller's)
+    const int32_t* rowptr;
     const int32_t* col;
     int32_t dim;
 };
@@ -605,18 +605,13 @@ __host__ __device__ inline SmallLds small_lds(int64_t m, int64_t n, int64_t nnz,
     return L;
 }
 
-// The side's entries into LDS in row order (from the sorted layout by slot)
+// The side's entries into LDS
 template <typename V>
 __device__ __forceinline__ void small_fill(const SmallMat& s, const V* val, V* lv, uint16_t* lc) {
-    for (int t = 0; t < s.tp.ntiles; ++t) {
-        const int4 d = s.tp.desc[t];
-        const int b = d.z, nz = d.w - d.z;
-        const bool sorted = s.tp.slot && nz <= s.tp.tile_nnz;
-        for (int j = threadIdx.x; j < nz; j += kSmallBlock) {
-            const int e = b + (sorted ? (int)s.tp.slot[b + j] : j);
-            lv[e] = val[b + j];
-            lc[e] = (uint16_t)s.col[b + j];
-        }
+    const int nnz = s.rowptr[s.dim];
+    for (int e = threadIdx.x; e < nnz; e += kSmallBlock) {
+        lv[e] = val[e];
+        lc[e] = (uint16_t)s.col[e];
     }
 }
 
@@ -667,8 +662,8 @@ struct SmallSide {
             const int i = row() + r * kSmallBlock;
             k[r] = e[r] = 0;
             if (i < s.dim) {
-                k[r] = s.tp.rowptr[i] + ((int)threadIdx.x & (step - 1));
-                e[r] = s.tp.rowptr[i + 1];
+                k[r] = s.rowptr[i] + ((int)threadIdx.x & (step - 1));
+                e[r] = s.rowptr[i + 1];
             }
 #pragma unroll
             for (int q = 0; q < kSmallRegs; ++q) {
@@ -721,7 +716,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_iters(IterArgs<T, V> p, I
     if (ctrl->status != ST_RUNNING) return;
     extern __shared__ __align__(16) unsigned char smem_t[];
     const int tid = threadIdx.x, m = ma.dim, n = mat.dim;
-    const SmallLds L = small_lds(m, n, ma.tp.rowptr[m], sizeof(T), sizeof(V));
+    const SmallLds L = small_lds(m, n, ma.rowptr[m], sizeof(T), sizeof(V));
     T* const vy = (T*)(smem_t + L.vy);
     T* const vx = (T*)(smem_t + L.vx);
     V* const av = (V*)(smem_t + L.av);
@@ -818,7 +813,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_power(SmallMat ma, SmallM
     extern __shared__ __align__(16) unsigned char smem_t[];
     __shared__ double part[2][kSmallBlock / kWave];
     const int tid = threadIdx.x, m = ma.dim, n = mat.dim;
-    const SmallLds L = small_lds(m, n, ma.tp.rowptr[m], sizeof(T), sizeof(V));
+    const SmallLds L = small_lds(m, n, ma.rowptr[m], sizeof(T), sizeof(V));
     T* const vy = (T*)(smem_t + L.vy);
     T* const vx = (T*)(smem_t + L.vx);
     V* const av = (V*)(smem_t + L.av);
@@ -895,7 +890,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_scale(SmallMat ma, SmallM
                                                              double* d_row, double* d_col) {
     extern __shared__ __align__(16) unsigned char smem_t[];
     const int tid = threadIdx.x, m = ma.dim, n = mat.dim;
-    const SmallLds L = small_scale_lds(m, n, ma.tp.rowptr[m]);
+    const SmallLds L = small_scale_lds(m, n, ma.rowptr[m]);
     double* dr = (double*)(smem_t + L.vy);
     double* dc = (double*)(smem_t + L.vx);
     double *dr2 = dr + m, *dc2 = dc + n;
@@ -913,9 +908,9 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_scale(SmallMat ma, SmallM
         const int lg = small_lanes(s.dim), step = 1 << lg;
         for (int i = tid >> lg; i < s.dim; i += kSmallBlock >> lg) {
             double a = 0.0;
-            const int e = s.tp.rowptr[i + 1];
+            const int e = s.rowptr[i + 1];
 #pragma unroll 4
-            for (int k = s.tp.rowptr[i] + (tid & (step - 1)); k < e; k += step) {
+            for (int k = s.rowptr[i] + (tid & (step - 1)); k < e; k += step) {
                 const double t = fabs(lv[k]) * other[lc[k]];
                 a = mx ? fmax(a, t) : a + t;
             }
@@ -2344,10 +2339,7 @@ struct Solver {
                longest <= kSmallRowLen && lp.nnz <= kSmallLdsMax && small_layout().bytes <= kSmallLdsMax;
     }
     SmallMat small_side(bool a) const {
-        SmallMat s{a ? ta : tat, a ? (sorted() ? w.col_a : lp.a_col) : (sorted() ? w.col_at : lp.at_col),
-                   a ? lp.m : lp.n};
-        s.tp.slot = sorted() ? (a ? w.slot_a : w.slot_at) : nullptr;
-        return s;
+        return a ? SmallMat{lp.a_rowptr, lp.a_col, lp.m} : SmallMat{lp.at_rowptr, lp.at_col, lp.n};
     }
     int allow_small_lds() {
         const void* ks[] = {(const void*)k_small_iters<T, V, Acc, false, false>,
@@ -2843,10 +2835,8 @@ static int solve_impl(const mipdhg_lp& lp, const mipdhg_options& o, double eps, 
     const int scale_lds = S.small() ? small_scale_lds(m, n, nnz).bytes : 0;
     const bool small_scale = S.small() && scale_lds <= S.kSmallLdsMax;
     if (small_scale) {
-        SmallMat sa{S.ta, lp.a_col, lp.m}, st{S.tat, lp.at_col, lp.n};  // the caller's matrix: row order
-        sa.tp.slot = st.tp.slot = nullptr;
-        hipLaunchKernelGGL(k_small_scale, dim3(1), dim3(kSmallBlock), scale_lds, stream, sa, st, lp.a_val, lp.at_val,
-                           o.ruiz_iters, passes, w.d_row, w.d_col);
+        hipLaunchKernelGGL(k_small_scale, dim3(1), dim3(kSmallBlock), scale_lds, stream, S.small_side(true),
+                           S.small_side(false), lp.a_val, lp.at_val, o.ruiz_iters, passes, w.d_row, w.d_col);
     } else {
         hipLaunchKernelGGL(k_fill, dim3(grid_for(m)), dim3(kBlock), 0, stream, w.d_row, m, 1.0);
         hipLaunchKernelGGL(k_fill, dim3(grid_for(n)), dim3(kBlock), 0, stream, w.d_col, n, 1.0);
