@@ -1234,6 +1234,7 @@ extern "C" int mipdhg_ipm_solve(const mipdhg_lp* lp, const double* d_row, const 
         return set_error("workspace too small: %zu bytes given, %zu needed", workspace_bytes, P.w.bytes),
                MIPDHG_ERR_WORKSPACE;
     memset(info, 0, sizeof(*info));
+    StreamDrain drain{P.s};
     if ((rc = ipm_setup(P, d_row, d_col))) return rc;
     if (cold) {
         if ((rc = P.cold_start())) return rc;
@@ -1244,6 +1245,7 @@ extern "C" int mipdhg_ipm_solve(const mipdhg_lp* lp, const double* d_row, const 
     }
     if ((rc = P.run(info))) return rc;
     if ((rc = ipm_finish(P, d_row, d_col, x, y, z, info))) return rc;
+    drain.armed = false;
     info->alpha_min = 0.0;
     info->ms_total = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
     return info->status;
@@ -1265,6 +1267,7 @@ extern "C" int mipdhg_ipm_warm(const mipdhg_lp* lp, const double* d_row, const d
         return set_error("workspace too small: %zu bytes given, %zu needed", workspace_bytes, P.w.bytes),
                MIPDHG_ERR_WORKSPACE;
     memset(info, 0, sizeof(*info));
+    StreamDrain drain{P.s};
     if ((rc = ipm_setup(P, d_row, d_col))) return rc;
     // Algorithm 1 on the scaled point (x / D_c, y / D_r, z D_c)
     double mu_t = 0.0;
@@ -1287,6 +1290,7 @@ extern "C" int mipdhg_ipm_warm(const mipdhg_lp* lp, const double* d_row, const d
         if ((rc = mipdhg_center_reclamp(lp->n, alpha, stream, P.w.xc, P.w.zc))) return rc;
     }
     if ((rc = ipm_finish(P, d_row, d_col, x, y, z, info))) return rc;
+    drain.armed = false;
     info->lifts = lifts;
     info->alpha_min = alpha;
     info->mu_target = mu_t;

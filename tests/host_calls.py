@@ -112,12 +112,13 @@ class Host:
         return self.lib.mipdhg_unrolled_backward(C.byref(b), C.byref(o), K, ckpt, tape, nb.value, self.buf(8 * w.n),
                                                  stream, self.buf(8 * w.n), self.buf(8 * w.m))
 
-    def ipm(self, lp, ws, nbytes, stream=0):
+    def ipm(self, lp, ws, nbytes, stream=0, call="mipdhg_ipm_solve", start=True):
         o, info = self.L.IpmOptionsStruct(), self.L.IpmInfoStruct()
         self.lib.mipdhg_ipm_default_options(C.byref(o))
         out = [self.buf(8 * k) for k in (lp.n, lp.m, lp.n)]
-        return self.lib.mipdhg_ipm_solve(C.byref(lp), None, None, *[self.arr(np.ones(k)) for k in (lp.n, lp.m, lp.n)],
-                                         C.byref(o), ws, nbytes, stream, *out, C.byref(info))
+        point = [self.arr(np.ones(k)) if start else None for k in (lp.n, lp.m, lp.n)]
+        return getattr(self.lib, call)(C.byref(lp), None, None, *point, C.byref(o), ws, nbytes, stream, *out,
+                                       C.byref(info))
 
     def errors_leave_nothing_running(self, call, names):
         """call() with each call of each of the runtime functions `names` made to fail once: it reports the error, and

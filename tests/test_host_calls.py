@@ -113,6 +113,22 @@ def test_an_error_in_the_unrolled_map_leaves_nothing_running(run):
     """)
 
 
+IPM_CALLS = ("hipMemcpyAsync", "hipMemsetAsync", "hipFuncSetAttribute", "hipStreamSynchronize", "hipLaunchKernel")
+
+
+@pytest.mark.parametrize("call,start", [("mipdhg_ipm_solve", True), ("mipdhg_ipm_solve", False),
+                                        ("mipdhg_ipm_warm", True)])
+def test_an_error_in_the_interior_point_method_leaves_nothing_running(run, call, start):
+    run(f"""
+    lp = h.lp(2, 3, [1, 2, 1])
+    nb = C.c_size_t(0)
+    assert h.lib.mipdhg_ipm_workspace_size(C.byref(lp), C.byref(nb)) == 0
+    ws = h.buf(nb.value)
+    # (kernels do not run here: the residuals are zeros and the method ends at its first test)
+    assert h.errors_leave_nothing_running(lambda: h.ipm(lp, ws, nb.value, 7, {call!r}, {start}), {IPM_CALLS!r}) >= 10
+    """)
+
+
 # --- the batched solve's streams --------------------------------------------------------------------------------
 @pytest.mark.parametrize("opts", [dict(), dict(batch_split=400)])
 @pytest.mark.parametrize("masked", [False, True])
