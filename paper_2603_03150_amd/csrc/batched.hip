@@ -547,10 +547,11 @@ static int lds_bytes_for(int max_m, int max_n, size_t ts) {
 // not depend on its class.  With more instances than compute units the class
 // follows from the LDS the instance needs with both matrices in it, so that
 // every class keeps 16 waves on a compute unit: up to a sixteenth of its LDS
-// one wave, up to a quarter 256 threads, up to a half 512, else 1,024 threads
-// and the whole LDS, from which the matrices' last levels are left out when
-// they do not fit.  With no more instances than compute units nothing is
-// gained by leaving room for others: about one thread per column.
+// one wave (but see one_wave), up to a quarter 256 threads, up to a half 512,
+// else 1,024 threads and the whole LDS, from which the matrices' last levels
+// are left out when they do not fit.  With no more instances than compute
+// units nothing is gained by leaving room for others: about one thread per
+// column.
 // Measured on 4,096 LPs of 20 to 2,000 rows, 2.5 times the columns, 4 entries
 // a column (FP32, 256 iterations, call with its host part): one launch of 256
 // threads sized by the largest instance, the matrices in L2, 32.3 ms; these
@@ -632,23 +633,31 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
     // its bytes to 256 threads and the others to 1,024
     std::vector<uint8_t> cls(B);
     int cl_count[kClasses] = {0, 0, 0, 0}, cl_lds[kClasses] = {0, 0, 0, 0};
+    auto rows = [&](int i) { return bt.row_off[i + 1] - bt.row_off[i]; };
+    auto columns = [&](int i) { return bt.col_off[i + 1] - bt.col_off[i]; };
+    auto full = [&](int i, int k) {  // LDS that holds all of it beside the registers of class k's threads
+        typedef RegShape<V> RS;
+        const int mi = rows(i), ni = columns(i);
+        const int64_t zi = bt.nnz_off[i + 1] - bt.nnz_off[i], zc = zi / std::max(ni, 1), zr = zi / std::max(mi, 1);
+        const int64_t nreg = std::min(ni, RS::RC * kClassBs[k]) * std::min<int64_t>(zc, RS::KC) +
+                             std::min(mi, RS::RR * kClassBs[k]) * std::min<int64_t>(zr, RS::KR);
+        return inst_full_bytes(mi, ni, zi, sizeof(T), sizeof(V), nreg);
+    };
+    int quarter = 0;  // instances that a quarter of a compute unit's LDS holds
     for (int i = 0; i < B; ++i) {
-        const int mi = bt.row_off[i + 1] - bt.row_off[i], ni = bt.col_off[i + 1] - bt.col_off[i];
-        const int64_t zi = bt.nnz_off[i + 1] - bt.nnz_off[i];
-        auto full = [&](int k) {  // LDS that holds all of it beside the registers of class k's threads
-            typedef RegShape<V> RS;
-            const int64_t zc = zi / std::max(ni, 1), zr = zi / std::max(mi, 1);
-            const int64_t nreg = std::min(ni, RS::RC * kClassBs[k]) * std::min<int64_t>(zc, RS::KC) +
-                                 std::min(mi, RS::RR * kClassBs[k]) * std::min<int64_t>(zr, RS::KR);
-            return inst_full_bytes(mi, ni, zi, sizeof(T), sizeof(V), nreg);
-        };
+        const int ni = columns(i);
         int c;
-        if (o.batch_split > 0) c = lds_bytes_for(mi, ni, sizeof(T)) <= o.batch_split ? 2 : 0;
+        if (o.batch_split > 0) c = lds_bytes_for(rows(i), ni, sizeof(T)) <= o.batch_split ? 2 : 0;
         else if (B <= cus) c = ni <= 64 ? 3 : ni <= 512 ? 2 : ni <= 1024 ? 1 : 0;
-        else c = full(3) <= kClassLds[3] ? 3 : full(2) <= kClassLds[2] ? 2 : full(1) <= kClassLds[1] ? 1 : 0;
-        const int64_t cap = B <= cus && o.batch_split == 0 ? kClassLds[0] : kClassLds[c];
-        const int need = (int)std::max<int64_t>(inst_vec_bytes(mi, ni, sizeof(T)), std::min(full(c), cap));
+        else c = full(i, 3) <= kClassLds[3] ? 3 : full(i, 2) <= kClassLds[2] ? 2 : full(i, 1) <= kClassLds[1] ? 1 : 0;
+        quarter += c >= 2;
         cls[i] = (uint8_t)c;
+    }
+    for (int i = 0; i < B; ++i) {
+        if (cls[i] == 3 && !one_wave(quarter, cus, columns(i))) cls[i] = 2;
+        const int c = cls[i];
+        const int64_t cap = B <= cus && o.batch_split == 0 ? kClassLds[0] : kClassLds[c];
+        const int need = (int)std::max<int64_t>(inst_vec_bytes(rows(i), columns(i), sizeof(T)), std::min(full(i, c), cap));
         ++cl_count[c];
         cl_lds[c] = std::max(cl_lds[c], need);
     }

@@ -815,7 +815,7 @@ static int unrolled_impl(const mipdhg_batch& bt, const mipdhg_options& o, int K,
     // One launch of workgroups shaped for the largest instance: with no more
     // instances than compute units about one thread per column and all the
     // LDS the instance can use; with more, as many waves as keep 16 on a
-    // compute unit (see kClassBs in batched.hip).
+    // compute unit (see kClassBs in batched.hip, and one_wave).
     int64_t full[3] = {0, 0, 0};
     const int bs[3] = {1024, 256, 64};
     const int64_t share[3] = {162000, 40400, 9700};
@@ -830,7 +830,7 @@ static int unrolled_impl(const mipdhg_batch& bt, const mipdhg_options& o, int K,
         }
     int c;
     if (B <= cus) c = max_n <= 64 ? 2 : max_n <= 512 ? 1 : 0;
-    else c = full[2] <= share[2] ? 2 : full[1] <= share[1] ? 1 : 0;
+    else c = full[2] <= share[2] && one_wave(B, cus, max_n) ? 2 : full[1] <= share[1] ? 1 : 0;
     a.lds = (int)std::max<int64_t>(inst_vec_bytes(max_m, max_n, sizeof(T)),
                                    std::min(full[c], B <= cus ? share[0] : share[c]));
     hipLaunchKernelGGL(k_zero_bytes, dim3(1), dim3(64), 0, stream, (uint8_t*)t.counter, (int64_t)256);

@@ -148,6 +148,21 @@ def test_a_batch_stays_on_a_stream_with_a_compute_unit_mask(run, opts, masked):
     """)
 
 
+@pytest.mark.parametrize("count,m,n,threads", [
+    (1, 20, 64, 64), (256, 20, 64, 64), (256, 20, 65, 256),  # no more than compute units: a thread to a column
+    (257, 20, 64, 64), (257, 20, 65, 256), (1024, 80, 200, 256), (1025, 80, 200, 64), (1025, 120, 300, 256),
+])
+def test_one_wave_takes_what_256_threads_cannot_hold_at_once(run, count, m, n, threads):
+    run(f"""
+    b, o = h.batch([({m}, {n}, [4] * {n})] * {count}), h.options("fp32", max_iter=64)
+    for call in (h.solve_batched, h.unrolled):
+        h.shim.shim_reset()
+        assert call(b, o) >= 0
+        k = [n for n in h.kernels() if "k_batched" in n or "k_unrolled" in n]
+        assert k and all("Li{threads}E" in n for n in k), k
+    """)
+
+
 # --- a kept workspace -------------------------------------------------------------------------------------------
 def test_a_batch_state_of_the_former_layout_is_refused(run):
     run("""
