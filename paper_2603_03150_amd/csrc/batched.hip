@@ -551,7 +551,10 @@ static int lds_bytes_for(int max_m, int max_n, size_t ts) {
 // else 1,024 threads and the whole LDS, from which the matrices' last levels
 // are left out when they do not fit.  With no more instances than compute
 // units nothing is gained by leaving room for others: about one thread per
-// column.
+// column (a thread holds three).  48 LPs, 256 iterations, FP32: at 62 columns 64
+// threads 0.95 ms, 256 0.92; at 80 1.04 and 0.92; at 255 256 threads 1.01, 512
+// 1.01; at 400 1.24 and 1.15; at 900 512 threads 1.40, 1,024 1.42; at 1,300 1.88 and
+// 1.58.
 // Measured on 4,096 LPs of 20 to 2,000 rows, 2.5 times the columns, 4 entries
 // a column (FP32, 256 iterations, call with its host part): one launch of 256
 // threads sized by the largest instance, the matrices in L2, 32.3 ms; these
@@ -648,13 +651,13 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
         const int ni = columns(i);
         int c;
         if (o.batch_split > 0) c = lds_bytes_for(rows(i), ni, sizeof(T)) <= o.batch_split ? 2 : 0;
-        else if (B <= cus) c = ni <= 64 ? 3 : ni <= 512 ? 2 : ni <= 1024 ? 1 : 0;
+        else if (B <= cus) c = std::max(rows(i), ni) <= 64 ? 3 : ni <= 256 ? 2 : ni <= 1024 ? 1 : 0;
         else c = full(i, 3) <= kClassLds[3] ? 3 : full(i, 2) <= kClassLds[2] ? 2 : full(i, 1) <= kClassLds[1] ? 1 : 0;
         quarter += c >= 2;
         cls[i] = (uint8_t)c;
     }
     for (int i = 0; i < B; ++i) {
-        if (cls[i] == 3 && !one_wave(quarter, cus, columns(i))) cls[i] = 2;
+        if (cls[i] == 3 && !one_wave(quarter, cus, rows(i), columns(i))) cls[i] = 2;
         const int c = cls[i];
         const int64_t cap = B <= cus && o.batch_split == 0 ? kClassLds[0] : kClassLds[c];
         const int need = (int)std::max<int64_t>(inst_vec_bytes(rows(i), columns(i), sizeof(T)), std::min(full(i, c), cap));

@@ -400,15 +400,18 @@ inline int64_t inst_full_bytes(int64_t m, int64_t n, int64_t nnz, int ts, int vs
     return inst_vec_bytes((int)m, (int)n, ts) + (rest > sort ? rest : sort);
 }
 
-// Whether one wave is to run an instance of n columns that a sixteenth of a
-// compute unit's LDS holds, and not 256 threads; count: the instances that a
-// quarter of it holds.  No more than one column to a lane, or more instances than
+// Whether one wave is to run an m x n instance that a sixteenth of a compute
+// unit's LDS holds, and not 256 threads; count: the instances that a quarter of
+// it holds.  No more than one row and column to a lane, or more instances than
 // 256-thread workgroups hold at once (four to a compute unit), where a wave
 // keeps four times as many in flight.  256 iterations in FP32, one wave against
 // 256 threads: 1,024 instances of 62 columns 1.15 and 1.15 ms, of 150 columns
 // 1.67 and 1.43, of 200 columns 2.26 and 1.39; 2,048 of them 1.46 and 1.96,
 // 1.96 and 2.35, 2.69 and 2.48; 4,096 1.91 and 3.50, 2.64 and 4.10, 3.52 and 4.45.
-inline bool one_wave(int64_t count, int cus, int n) { return n <= kWave || count > 4 * (int64_t)cus; }
+// (11 of 65 x 45, FP64: 1.55 and 1.24, the 65th row being a second pass.)
+inline bool one_wave(int64_t count, int cus, int m, int n) {
+    return (m > n ? m : n) <= kWave || count > 4 * (int64_t)cus;
+}
 
 // perm <- the positions' rows: rows by decreasing length, equal lengths in
 // order (a bitonic sort of (length, row) keys in LDS, skipped when all

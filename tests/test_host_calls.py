@@ -151,6 +151,7 @@ def test_a_batch_stays_on_a_stream_with_a_compute_unit_mask(run, opts, masked):
 @pytest.mark.parametrize("count,m,n,threads", [
     (1, 20, 64, 64), (256, 20, 64, 64), (256, 20, 65, 256),  # no more than compute units: a thread to a column
     (257, 20, 64, 64), (257, 20, 65, 256), (1024, 80, 200, 256), (1025, 80, 200, 64), (1025, 120, 300, 256),
+    (11, 65, 45, 256), (300, 65, 45, 256), (1, 100, 256, 256),
 ])
 def test_one_wave_takes_what_256_threads_cannot_hold_at_once(run, count, m, n, threads):
     run(f"""
@@ -160,6 +161,18 @@ def test_one_wave_takes_what_256_threads_cannot_hold_at_once(run, count, m, n, t
         assert call(b, o) >= 0
         k = [n for n in h.kernels() if "k_batched" in n or "k_unrolled" in n]
         assert k and all("Li{threads}E" in n for n in k), k
+    """)
+
+
+@pytest.mark.parametrize("n,batched,unrolled", [(257, 512, 1024), (512, 512, 1024), (1024, 512, 1024), (1025, 1024, 1024)])
+def test_few_instances_get_about_a_thread_to_a_column(run, n, batched, unrolled):
+    run(f"""
+    b, o = h.batch([(100, {n}, [4] * {n})] * 3), h.options("fp32", max_iter=64)
+    for call, threads in ((h.solve_batched, {batched}), (h.unrolled, {unrolled})):
+        h.shim.shim_reset()
+        assert call(b, o) >= 0
+        k = [n for n in h.kernels() if "k_batched" in n or "k_unrolled" in n]
+        assert k and all(f"Li{{threads}}E" in n for n in k), k
     """)
 
 
