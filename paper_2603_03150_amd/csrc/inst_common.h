@@ -6,6 +6,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace mip {
@@ -179,12 +181,26 @@ __device__ __forceinline__ Acc side_dot(const Side<V>& s, const unsigned char* l
 // the columns are byte offsets into the gathered vector, two to a register.
 // Absent entries are a zero value and the vector's extra zero entry.  Three
 // columns of six and one row of sixteen entries are 51 registers in FP32, of
-// the 128 that four waves to a SIMD leave a thread.
+// the 128 that four waves to a SIMD leave a thread (the compiler spills 35 to
+// 64 others in the iteration kernels and 41 to 82 in the reverse sweep; in FP32
+// nearly all of that lies outside the loop).  16-bit values lie two to a
+// register as well: with one each, 81 and 124 were spilled, in the loop too,
+// and maps of near-dense instances took longer than from L2 (307 of 37 x 55, 30
+// entries a column, K = 150: 3.62 ms from L2, 4.11, so 3.58; 4,096 LPs of 20 to
+// 2,000 rows, 256 iterations: 31.7, 22.2, 16.7).
 template <typename V, int R, int K>
 struct RegSide {
-    V v[R][K];
+    static constexpr bool kPacked = sizeof(V) == 2;
+    typedef typename std::conditional<kPacked, uint32_t, V>::type W;
+    static constexpr int KW = kPacked ? K / 2 : K;
+    W v[R][KW];
     uint32_t c[R][K / 2];
     int len[R];
+    // entry k of slot r
+    __device__ __forceinline__ auto value(int r, int k) const {
+        if constexpr (kPacked) return __uint_as_float((k & 1) ? v[r][k / 2] & 0xffff0000u : v[r][k / 2] << 16);
+        else return v[r][k];
+    }
     // Called in the loop that uses them: the entries as they are stored stay
     // in the registers (their conversions and offsets, computed ahead of the
     // loop, would take twice as many and spill)
@@ -192,7 +208,7 @@ struct RegSide {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
 #pragma unroll
-            for (int k = 0; k < K; ++k) asm volatile("" : "+v"(v[r][k]));
+            for (int k = 0; k < KW; ++k) asm volatile("" : "+v"(v[r][k]));
 #pragma unroll
             for (int k = 0; k < K / 2; ++k) asm volatile("" : "+v"(c[r][k]));
         }
@@ -216,17 +232,25 @@ __device__ __forceinline__ void reg_load(RegSide<V, R, K>& g, const Side<V>& s, 
         const int l = any && p < dim ? len[min(p, dim - 1)] : 0;
         g.len[r] = l;
         uint32_t c[K];
+        V w[K];
         // (branch-free: absent entries load the instance's first one)
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int e = k < l ? (int)kp[k] + p : 0;
             const V v = any ? s.val[e] : (V)0;
             const uint32_t cc = any ? (uint32_t)s.col[e] * (uint32_t)sizeof(T) : none;
-            g.v[r][k] = k < l ? v : (V)0;
+            w[k] = k < l ? v : (V)0;
             c[k] = k < l ? cc : none;
         }
 #pragma unroll
         for (int k = 0; k < K; k += 2) g.c[r][k / 2] = c[k] | (c[k + 1] << 16);
+        if constexpr (RegSide<V, R, K>::kPacked) {
+#pragma unroll
+            for (int k = 0; k < K; k += 2) g.v[r][k / 2] = (uint32_t)w[k] | ((uint32_t)w[k + 1] << 16);
+        } else {
+#pragma unroll
+            for (int k = 0; k < K; ++k) g.v[r][k] = w[k];
+        }
     }
 }
 
@@ -240,7 +264,7 @@ __device__ __forceinline__ Acc reg_terms(const RegSide<V, R, K>& g, const X* xl,
         x[k] = *(const X*)((const unsigned char*)xl + ((k & 1) ? g.c[r][k / 2] >> 16 : g.c[r][k / 2] & 0xffffu));
     Acc acc = 0;
 #pragma unroll
-    for (int k = 0; k < KE; ++k) acc += (Acc)ld_val_cached(&g.v[r][k], 0) * (Acc)x[k];
+    for (int k = 0; k < KE; ++k) acc += (Acc)g.value(r, k) * (Acc)x[k];
     return acc;
 }
 
