@@ -129,7 +129,7 @@ __device__ void setup_instance(const BArgs<T, V>& a, int inst, unsigned char* ld
 // T: u = x - x0, v = y - y0 (in LDS), rc = c~ - A~^T y0, rb = b~ - A~ x0:
 // x_hat = x0 + max(u - tau (rc - A~^T v), -x0),
 // y_hat = y0 + v + sigma (rb - A~ (x_bar - x0)).
-template <typename T, typename V, typename Acc, int BS>
+template <typename T, typename V, typename Acc, int BS, bool LONG>
 __device__ __forceinline__ void plain_iterations(const BArgs<T, V>& a, const Inst<T, V>& I, unsigned char* lds, int count,
                                                  int64_t k, double tau, double sig) {
     typedef RegShape<V> RS;
@@ -137,8 +137,8 @@ __device__ __forceinline__ void plain_iterations(const BArgs<T, V>& a, const Ins
     const int m = I.m, n = I.n, c0 = I.c0, r0 = I.r0;
     T *const yL = I.yl, *const xbL = I.xl;
     const double rho = a.rho, opr = 1.0 + a.rho;
-    RegSide<V, RS::RC, RS::KC> gt;
-    RegSide<V, RS::RR, RS::KR> ga;
+    RegSide<V, RS::RC, RS::KC, LONG> gt;
+    RegSide<V, RS::RR, RS::KR, LONG> ga;
     reg_load<BS, T>(gt, I.AT, lds, n, m);
     reg_load<BS, T>(ga, I.A, lds, m, n);
     T ur[RS::RC], x0r[RS::RC], rcr[RS::RC], rbr[RS::RR];
@@ -189,7 +189,7 @@ __device__ __forceinline__ void plain_iterations(const BArgs<T, V>& a, const Ins
 // The iterations of an instance from the state in the workspace (set up, or
 // suspended at the end of a block): the scaled matrix, b~, c~, the scaling, x,
 // the anchors and the report's set-up fields, y and the scalars.
-template <typename T, typename V, typename Acc, int BS>
+template <typename T, typename V, typename Acc, int BS, bool LONG>
 __device__ void solve_instance(const BArgs<T, V>& a, int inst, unsigned char* lds, double* sh) {
     const int tid = threadIdx.x;
     BState& st = a.state[inst];
@@ -226,7 +226,7 @@ __device__ void solve_instance(const BArgs<T, V>& a, int inst, unsigned char* ld
         // first and the evaluated one
         const int plain = k == 0 ? 0 : to_eval - 1;
         if (plain > 0) {
-            plain_iterations<T, V, Acc, BS>(a, I, lds, plain, k, tau, sig);
+            plain_iterations<T, V, Acc, BS, LONG>(a, I, lds, plain, k, tau, sig);
             t += plain;
             k += plain;
             to_eval -= plain;
@@ -241,7 +241,7 @@ __device__ void solve_instance(const BArgs<T, V>& a, int inst, unsigned char* ld
         for (int p = et; p < n; p += BS) {
             const int g = c0 + p, j = I.column(p);
             const double u = (double)a.x[g], x0 = (double)a.x0[g], rc = (double)a.ct[g];
-            const Acc s = side_dot<Acc>(I.AT, lds, yL, p, RS::RC * BS, RS::KC);
+            const Acc s = side_dot<LONG, Acc>(I.AT, lds, yL, p, RS::RC * BS, RS::KC);
             double uh = u - tau * (rc - (double)s);
             uh = uh < -x0 ? -x0 : uh;
             xbL[p] = (T)(2.0 * uh - u);
@@ -258,7 +258,7 @@ __device__ void solve_instance(const BArgs<T, V>& a, int inst, unsigned char* ld
         for (int p = et; p < m; p += BS) {
             const int g = r0 + p, i = I.row(p);
             const double rb = (double)a.bt[g];
-            const Acc s = side_dot<Acc>(I.A, lds, xbL, p, RS::RR * BS, RS::KR);
+            const Acc s = side_dot<LONG, Acc>(I.A, lds, xbL, p, RS::RR * BS, RS::KR);
             const double v = (double)yL[p];
             const double vh = v + sig * (rb - (double)s);
             yL[p] = (T)(w * (opr * vh - rho * v));
@@ -422,7 +422,7 @@ __device__ void solve_instance(const BArgs<T, V>& a, int inst, unsigned char* ld
 // Four waves to a SIMD in every class of launch: at most 128 registers.  The
 // set-up is a launch of its own, so that its code takes no registers from the
 // iterations.
-template <typename T, typename V, typename Acc, int BS, bool SETUP>
+template <typename T, typename V, typename Acc, int BS, bool SETUP, bool LONG = false>
 __global__ __launch_bounds__(BS, 4) void k_batched(BArgs<T, V> a) {
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ double sh[BS / kWave > 12 ? BS / kWave : 12];
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(BS, 4) void k_batched(BArgs<T, V> a) {
         if (qi >= a.B) break;  // uniform: every wave leaves once the queue is empty
         const int inst = __builtin_amdgcn_readfirstlane(a.order[qi]);
         if constexpr (SETUP) setup_instance<T, V, BS>(a, inst, lds, sh);
-        else solve_instance<T, V, Acc, BS>(a, inst, lds, sh);
+        else solve_instance<T, V, Acc, BS, LONG>(a, inst, lds, sh);
         __syncthreads();  // the next instance takes over the LDS
     }
 }
@@ -578,18 +578,17 @@ static bool unmasked(hipStream_t s) {
 
 // One class's launches: as many workgroups as fit, never more than instances
 template <typename T, typename V, typename Acc, int BS>
-static int launch_class(const BArgs<T, V>& a, int cus, hipStream_t s) {
+static int launch_class(const BArgs<T, V>& a, bool rests, int cus, hipStream_t s) {
     auto* ks = k_batched<T, V, Acc, BS, true>;
-    auto* k = k_batched<T, V, Acc, BS, false>;
+    auto* k = rests ? k_batched<T, V, Acc, BS, false, LongRows<V>::ok> : k_batched<T, V, Acc, BS, false, false>;
     // (the largest class's bytes whatever this launch's: the attribute is the process's)
     MIP_HIP(hipFuncSetAttribute((const void*)ks, hipFuncAttributeMaxDynamicSharedMemorySize, kClassLds[0]));
     MIP_HIP(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, kClassLds[0]));
     int per_cu = 1;
     MIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, BS, a.lds));
     const int grid = std::max(1, std::min(a.B, cus * std::max(per_cu, 1)));
-    if (!a.resume)
-        hipLaunchKernelGGL((k_batched<T, V, Acc, BS, true>), dim3(grid), dim3(BS), a.lds, s, a);
-    hipLaunchKernelGGL((k_batched<T, V, Acc, BS, false>), dim3(grid), dim3(BS), a.lds, s, a);
+    if (!a.resume) hipLaunchKernelGGL(ks, dim3(grid), dim3(BS), a.lds, s, a);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(BS), a.lds, s, a);
     MIP_LAUNCH_CHECK();
     return 0;
 }
@@ -636,6 +635,7 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
     // its bytes to 256 threads and the others to 1,024
     std::vector<uint8_t> cls(B);
     int cl_count[kClasses] = {0, 0, 0, 0}, cl_lds[kClasses] = {0, 0, 0, 0};
+    int64_t cl_m[kClasses] = {}, cl_n[kClasses] = {}, cl_nnz[kClasses] = {};
     auto rows = [&](int i) { return bt.row_off[i + 1] - bt.row_off[i]; };
     auto columns = [&](int i) { return bt.col_off[i + 1] - bt.col_off[i]; };
     auto full = [&](int i, int k) {  // LDS that holds all of it beside the registers of class k's threads
@@ -662,6 +662,9 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
         const int64_t cap = B <= cus && o.batch_split == 0 ? kClassLds[0] : kClassLds[c];
         const int need = (int)std::max<int64_t>(inst_vec_bytes(rows(i), columns(i), sizeof(T)), std::min(full(i, c), cap));
         ++cl_count[c];
+        cl_m[c] += rows(i);
+        cl_n[c] += columns(i);
+        cl_nnz[c] += bt.nnz_off[i + 1] - bt.nnz_off[i];
         cl_lds[c] = std::max(cl_lds[c], need);
     }
     std::vector<int32_t> order(B);
@@ -774,11 +777,12 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
         ac.counter = w.counter + c;
         ac.lds = cl_lds[c];
         begin += cl_count[c];
+        const bool rests = LongRows<V>::pays(cl_m[c], cl_n[c], cl_nnz[c]);
         int rc;
-        if (c == 0) rc = launch_class<T, V, Acc, kClassBs[0]>(ac, cus, cs);
-        else if (c == 1) rc = launch_class<T, V, Acc, kClassBs[1]>(ac, cus, cs);
-        else if (c == 2) rc = launch_class<T, V, Acc, kClassBs[2]>(ac, cus, cs);
-        else rc = launch_class<T, V, Acc, kClassBs[3]>(ac, cus, cs);
+        if (c == 0) rc = launch_class<T, V, Acc, kClassBs[0]>(ac, rests, cus, cs);
+        else if (c == 1) rc = launch_class<T, V, Acc, kClassBs[1]>(ac, rests, cus, cs);
+        else if (c == 2) rc = launch_class<T, V, Acc, kClassBs[2]>(ac, rests, cus, cs);
+        else rc = launch_class<T, V, Acc, kClassBs[3]>(ac, rests, cus, cs);
         if (rc) return rc;
     }
     for (int c = 0; c < kClasses; ++c)

@@ -100,8 +100,11 @@ struct Side {
 
 typedef int32_t ii2 __attribute__((ext_vector_type(2)));
 
-// acc + the terms of position p from level k on (k even); len: its row's length
-template <typename Acc, typename V, typename X>
+// acc + the terms of position p from level k on (k even); len: its row's
+// length.  Four levels are three trips to LDS, one after the other; LONG: one,
+// the next four levels' columns and values and the offsets of those after being
+// read under a group's gathers (see LongRows).
+template <bool LONG, typename Acc, typename V, typename X>
 __device__ __forceinline__ Acc side_rest(const Side<V>& s, const unsigned char* lds, const X* xl, int p, int len, int k,
                                          Acc acc) {
     const uint32_t* kp = (const uint32_t*)(lds + s.o_kp);
@@ -109,6 +112,42 @@ __device__ __forceinline__ Acc side_rest(const Side<V>& s, const unsigned char* 
     const V* lv = (const V*)(lds + s.o_val);
     const uint16_t* lc = (const uint16_t*)(lds + s.o_col);
     const int kr = min(len, s.K0);
+    if constexpr (LONG) {
+        if (k + 4 <= kr) {
+            ii2 oa = *(const ii2*)(kl + k), ob = *(const ii2*)(kl + k + 2);
+            int c[4] = {lc[oa[0] + p], lc[oa[1] + p], lc[ob[0] + p], lc[ob[1] + p]};
+            V v[4] = {lv[oa[0] + p], lv[oa[1] + p], lv[ob[0] + p], lv[ob[1] + p]};
+            bool more = k + 8 <= kr;
+            if (more) {
+                oa = *(const ii2*)(kl + k + 4);
+                ob = *(const ii2*)(kl + k + 6);
+            }
+            for (;;) {
+                X x[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x[q] = xl[c[q]];
+                // (the last group reads its own entries again)
+                V w[4] = {lv[oa[0] + p], lv[oa[1] + p], lv[ob[0] + p], lv[ob[1] + p]};
+                c[0] = lc[oa[0] + p];
+                c[1] = lc[oa[1] + p];
+                c[2] = lc[ob[0] + p];
+                c[3] = lc[ob[1] + p];
+                k += 4;
+                const bool next = more;
+                more = k + 8 <= kr;
+                if (more) {
+                    oa = *(const ii2*)(kl + k + 4);
+                    ob = *(const ii2*)(kl + k + 6);
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    acc += (Acc)ld_val_cached(&v[q], 0) * (Acc)x[q];
+                    v[q] = w[q];
+                }
+                if (!next) break;
+            }
+        }
+    }
     for (; k + 4 <= kr; k += 4) {
         const ii2 oa = *(const ii2*)(kl + k), ob = *(const ii2*)(kl + k + 2);
         const int o[4] = {oa[0], oa[1], ob[0], ob[1]};
@@ -147,7 +186,7 @@ __device__ __forceinline__ Acc side_rest(const Side<V>& s, const unsigned char* 
 
 // The whole row at position p, none of it in registers; the positions below
 // P0 have their first KK levels only in the workspace
-template <typename Acc, typename V, typename X>
+template <bool LONG, typename Acc, typename V, typename X>
 __device__ __forceinline__ Acc side_dot(const Side<V>& s, const unsigned char* lds, const X* xl, int p, int P0, int KK) {
     if (!s.levels) return row_dot4<Acc>(s.val, s.col, xl, s.rowptr[p] - s.z0, s.rowptr[p + 1] - s.z0);
     const int len = ((const uint16_t*)(lds + s.o_len))[p];
@@ -174,7 +213,7 @@ __device__ __forceinline__ Acc side_dot(const Side<V>& s, const unsigned char* l
         }
         if (len <= KK) return acc;
     }
-    return side_rest<Acc>(s, lds, xl, p, len, k, acc);
+    return side_rest<LONG, Acc>(s, lds, xl, p, len, k, acc);
 }
 
 // Rows and entries per row that a thread holds: R rows of K entries, of which
@@ -188,7 +227,7 @@ __device__ __forceinline__ Acc side_dot(const Side<V>& s, const unsigned char* l
 // and maps of near-dense instances took longer than from L2 (307 of 37 x 55, 30
 // entries a column, K = 150: 3.62 ms from L2, 4.11, so 3.58; 4,096 LPs of 20 to
 // 2,000 rows, 256 iterations: 31.7, 22.2, 16.7).
-template <typename V, int R, int K>
+template <typename V, int R, int K, bool LONG = false>
 struct RegSide {
     static constexpr bool kPacked = sizeof(V) == 2;
     typedef typename std::conditional<kPacked, uint32_t, V>::type W;
@@ -220,8 +259,8 @@ struct RegShape {  // columns (rows of A^T) and rows (of A)
     static constexpr int RR = 1, KR = sizeof(V) == 8 ? 8 : 16;
 };
 
-template <int BS, typename T, typename V, int R, int K>
-__device__ __forceinline__ void reg_load(RegSide<V, R, K>& g, const Side<V>& s, const unsigned char* lds, int dim, int other) {
+template <int BS, typename T, typename V, int R, int K, bool LONG>
+__device__ __forceinline__ void reg_load(RegSide<V, R, K, LONG>& g, const Side<V>& s, const unsigned char* lds, int dim, int other) {
     const uint32_t* kp = (const uint32_t*)(lds + s.o_kp);
     const uint16_t* len = (const uint16_t*)(lds + s.o_len);
     const bool any = s.levels && len[0] > 0;  // uniform
@@ -244,7 +283,7 @@ __device__ __forceinline__ void reg_load(RegSide<V, R, K>& g, const Side<V>& s, 
         }
 #pragma unroll
         for (int k = 0; k < K; k += 2) g.c[r][k / 2] = c[k] | (c[k + 1] << 16);
-        if constexpr (RegSide<V, R, K>::kPacked) {
+        if constexpr (RegSide<V, R, K, LONG>::kPacked) {
 #pragma unroll
             for (int k = 0; k < K; k += 2) g.v[r][k / 2] = (uint32_t)w[k] | ((uint32_t)w[k + 1] << 16);
         } else {
@@ -256,8 +295,8 @@ __device__ __forceinline__ void reg_load(RegSide<V, R, K>& g, const Side<V>& s, 
 
 // The first KE entries of register slot r: the gathers are issued together,
 // the terms added in order
-template <int KE, typename Acc, typename V, typename X, int R, int K>
-__device__ __forceinline__ Acc reg_terms(const RegSide<V, R, K>& g, const X* xl, int r) {
+template <int KE, typename Acc, typename V, typename X, int R, int K, bool LONG>
+__device__ __forceinline__ Acc reg_terms(const RegSide<V, R, K, LONG>& g, const X* xl, int r) {
     X x[KE];
 #pragma unroll
     for (int k = 0; k < KE; ++k)
@@ -270,15 +309,15 @@ __device__ __forceinline__ Acc reg_terms(const RegSide<V, R, K>& g, const X* xl,
 
 // The row of register slot r.  The wave's longest row is its first lane's, so
 // a wave of short rows issues no more gathers than it needs, in steps.
-template <typename Acc, typename V, typename X, int R, int K>
-__device__ __forceinline__ Acc reg_dot(const RegSide<V, R, K>& g, const Side<V>& s, const unsigned char* lds,
+template <typename Acc, typename V, typename X, int R, int K, bool LONG>
+__device__ __forceinline__ Acc reg_dot(const RegSide<V, R, K, LONG>& g, const Side<V>& s, const unsigned char* lds,
                                        const X* xl, int r, int p) {
     const int longest = __builtin_amdgcn_readfirstlane(g.len[r]);
     if (K > 4 && longest <= 4) return reg_terms<(K > 4 ? 4 : K), Acc>(g, xl, r);
     if (K > 8 && longest <= 8) return reg_terms<(K > 8 ? 8 : K), Acc>(g, xl, r);
     if (K > 12 && longest <= 12) return reg_terms<(K > 12 ? 12 : K), Acc>(g, xl, r);
     Acc acc = reg_terms<K, Acc>(g, xl, r);
-    if (longest > K) acc = side_rest<Acc>(s, lds, xl, p, g.len[r], K, acc);
+    if (longest > K) acc = side_rest<LONG, Acc>(s, lds, xl, p, g.len[r], K, acc);
     return acc;
 }
 
@@ -436,6 +475,22 @@ inline int64_t inst_full_bytes(int64_t m, int64_t n, int64_t nnz, int ts, int vs
 inline bool one_wave(int64_t count, int cus, int m, int n) {
     return (m > n ? m : n) <= kWave || count > 4 * (int64_t)cus;
 }
+
+// Whether a launch's instances take the LONG form of side_rest: where their rows
+// or columns go on past the registers for 8 entries on average.  FP32, 200 LPs
+// of 200 rows and 400 columns, 256 iterations, without and with it: 8 entries a
+// row 1.11 and 1.17 ms, 16 1.63 and 1.59, 24 2.05 and 1.91, 32 2.59 and 2.29; 64
+// maps of the same, K = 150: 1.75 and 1.84, 2.43 and 2.42, 3.01 and 2.88, 3.69 and
+// 3.40 (21 of 95 x 380, 64 entries a row: 5.01 and 4.19, from L2 4.62).  Not for
+// values of eight bytes, whose registers it takes (64 maps in FP64, 16 entries a
+// row 2.14 and 2.35, 24 2.70 and 2.74, 32 3.25 and 3.21).
+template <typename V>
+struct LongRows {
+    static constexpr bool ok = sizeof(V) < 8;
+    static bool pays(int64_t m, int64_t n, int64_t nnz) {
+        return ok && (nnz >= m * (RegShape<V>::KR + 8) || nnz >= n * (RegShape<V>::KC + 8));
+    }
+};
 
 // perm <- the positions' rows: rows by decreasing length, equal lengths in
 // order (a bitonic sort of (length, row) keys in LDS, skipped when all
@@ -614,8 +669,8 @@ __device__ void inst_load(Inst<T, V>& I, const InstMat& M, const InstStore<V>& S
 // f(p, r, sum) for every row at position p of one side, its sum over the
 // gathered vector xl: the rows in registers (slot r), then the others (r = -1).
 // A wave leaves out the slots whose positions all lie past the end.
-template <int BS, int R, typename Acc, typename V, typename X, int K, class F>
-__device__ __forceinline__ void inst_rows(bool levels, int dim, const RegSide<V, R, K>& g, const Side<V>& s,
+template <int BS, int R, typename Acc, typename V, typename X, int K, bool LONG, class F>
+__device__ __forceinline__ void inst_rows(bool levels, int dim, const RegSide<V, R, K, LONG>& g, const Side<V>& s,
                                           const unsigned char* lds, const X* xl, F f) {
     const int tid = threadIdx.x;
     const int w0 = __builtin_amdgcn_readfirstlane(tid & ~(kWave - 1));
@@ -630,7 +685,7 @@ __device__ __forceinline__ void inst_rows(bool levels, int dim, const RegSide<V,
         }
         p += R * BS;
     }
-    for (; p < dim; p += BS) f(p, -1, side_dot<Acc>(s, lds, xl, p, 0, 0));
+    for (; p < dim; p += BS) f(p, -1, side_dot<LONG, Acc>(s, lds, xl, p, 0, 0));
 }
 
 template <typename V>

@@ -80,7 +80,7 @@ struct UArgs {
 // Halpern weight from k.  want_q: the sums' entries x - x^, x^ - x0 (by column)
 // and y - y^, y^ - y0 (by row) go to pu, xK and pav, lbt; keep_hat: x^, y^ are
 // kept; last: x_K is written; maskrow (or NULL): the projection masks.
-template <typename T, typename V, typename Acc, int BS>
+template <typename T, typename V, typename Acc, int BS, bool LONG>
 __device__ __forceinline__ void u_iterate(const UArgs<T, V>& a, const Inst<T, V>& I, const unsigned char* lds, int64_t k,
                                           double tau, double sig, bool want_q, bool keep_hat, bool last,
                                           uint64_t* maskrow) {
@@ -92,7 +92,7 @@ __device__ __forceinline__ void u_iterate(const UArgs<T, V>& a, const Inst<T, V>
     for (int p = tid; p < n; p += BS) {
         const int g = c0 + p;
         const double o = (double)a.x[g], an = (double)a.x0[g], ctg = (double)a.ct[g];
-        const Acc s = side_dot<Acc>(I.AT, lds, I.yl, p, RS::RC * BS, RS::KC);
+        const Acc s = side_dot<LONG, Acc>(I.AT, lds, I.yl, p, RS::RC * BS, RS::KC);
         const double v = o - tau * (ctg - (double)s);
         const double hh = v < 0.0 ? 0.0 : v;
         if (maskrow) {
@@ -115,7 +115,7 @@ __device__ __forceinline__ void u_iterate(const UArgs<T, V>& a, const Inst<T, V>
     for (int p = tid; p < m; p += BS) {
         const int g = r0 + p;
         const double an = (double)a.y0[g], btg = (double)a.bt[g];
-        const Acc s = side_dot<Acc>(I.A, lds, I.xl, p, RS::RR * BS, RS::KR);
+        const Acc s = side_dot<LONG, Acc>(I.A, lds, I.xl, p, RS::RR * BS, RS::KR);
         const double o = (double)I.yl[p];
         const double hh = o + sig * (btg - (double)s);
         I.yl[p] = (T)(w * (opr * hh - rho * o) + omw * an);
@@ -132,7 +132,7 @@ __device__ __forceinline__ void u_iterate(const UArgs<T, V>& a, const Inst<T, V>
 // `count` such iterations with none of these extras (but the masks, W words
 // from one iteration's to the next), from iteration k of the epoch on: the
 // threads' rows and their vectors' entries stay in registers.
-template <typename T, typename V, typename Acc, int BS>
+template <typename T, typename V, typename Acc, int BS, bool LONG>
 __device__ __forceinline__ void u_plain(const UArgs<T, V>& a, const Inst<T, V>& I, const unsigned char* lds, int count,
                                         int64_t k, double tau, double sig, uint64_t* maskrow) {
     typedef RegShape<V> RS;
@@ -140,8 +140,8 @@ __device__ __forceinline__ void u_plain(const UArgs<T, V>& a, const Inst<T, V>& 
     const int m = I.m, n = I.n, c0 = I.c0, r0 = I.r0, W = a.W;
     T *const yL = I.yl, *const xbL = I.xl;
     const double rho = a.rho, opr = 1.0 + a.rho;
-    RegSide<V, RS::RC, RS::KC> gt;
-    RegSide<V, RS::RR, RS::KR> ga;
+    RegSide<V, RS::RC, RS::KC, LONG> gt;
+    RegSide<V, RS::RR, RS::KR, LONG> ga;
     reg_load<BS, T>(gt, I.AT, lds, n, m);
     reg_load<BS, T>(ga, I.A, lds, m, n);
     T xr[RS::RC], x0r[RS::RC], ctr[RS::RC], y0r[RS::RR], btr[RS::RR];
@@ -240,7 +240,7 @@ __device__ __forceinline__ void reload_instance(const UArgs<T, V>& a, Inst<T, V>
     inst_load<T, V, BS>(I, a.M, a.S, lds, a.lds, true);
 }
 
-template <typename T, typename V, typename Acc, int BS>
+template <typename T, typename V, typename Acc, int BS, bool LONG>
 __device__ void forward_instance(const UArgs<T, V>& a, Inst<T, V>& I, int i, unsigned char* lds, double* sh) {
     const int tid = threadIdx.x, B = a.B;
     const int m = I.m, n = I.n, r0 = I.r0, c0 = I.c0;
@@ -281,7 +281,7 @@ __device__ void forward_instance(const UArgs<T, V>& a, Inst<T, V>& I, int i, uns
             const int to_cp = a.ckpt - (t - 1) % a.ckpt, to_ev = a.E - (t - 1) % a.E - 1, to_end = a.K - t;
             const int plain = min(to_cp, min(to_ev, to_end));
             if (plain > 0) {
-                u_plain<T, V, Acc, BS>(a, I, lds, plain, k, tau, sig, nullptr);
+                u_plain<T, V, Acc, BS, LONG>(a, I, lds, plain, k, tau, sig, nullptr);
                 t += plain;
                 k += plain;
                 if (plain == to_cp) continue;
@@ -290,7 +290,7 @@ __device__ void forward_instance(const UArgs<T, V>& a, Inst<T, V>& I, int i, uns
         const bool at_eval = (t % a.E == 0) && t < a.K;
         const bool first = k == 0;
         const bool need_q = !a.replay && (first || at_eval) && t < a.K;
-        u_iterate<T, V, Acc, BS>(a, I, lds, k, tau, sig, need_q, at_eval, t == a.K, nullptr);
+        u_iterate<T, V, Acc, BS, LONG>(a, I, lds, k, tau, sig, need_q, at_eval, t == a.K, nullptr);
         double qx[2] = {0.0, 0.0}, qy[2] = {0.0, 0.0};  // ||x - x^||^2, ||x^ - x0||^2 and the same of y
         if (need_q) {
             inst_sums<BS, 2>(n, sh, qx, [&](int j, double(&s)[2]) {
@@ -349,7 +349,7 @@ __device__ void forward_instance(const UArgs<T, V>& a, Inst<T, V>& I, int i, uns
 // state in the workspace before and after, in the threads' registers between;
 // yL holds lam_yhat, xbL holds lam_g.  The iterations' numbers (k, tau, sigma,
 // restart) are loaded 64 at a time, one to a lane.
-template <typename T, typename V, typename Acc, int BS>
+template <typename T, typename V, typename Acc, int BS, bool LONG>
 __device__ __forceinline__ void u_reverse(const UArgs<T, V>& a, const Inst<T, V>& I, const unsigned char* lds, int i,
                                           int tb, int te) {
     typedef RegShape<V> RS;
@@ -357,8 +357,8 @@ __device__ __forceinline__ void u_reverse(const UArgs<T, V>& a, const Inst<T, V>
     const int m = I.m, n = I.n, c0 = I.c0, r0 = I.r0, B = a.B;
     T *const lyhL = I.yl, *const lgL = I.xl;
     const double rho = a.rho, opr = 1.0 + a.rho;
-    RegSide<V, RS::RC, RS::KC> gt;
-    RegSide<V, RS::RR, RS::KR> ga;
+    RegSide<V, RS::RC, RS::KC, LONG> gt;
+    RegSide<V, RS::RR, RS::KR, LONG> ga;
     reg_load<BS, T>(gt, I.AT, lds, n, m);
     reg_load<BS, T>(ga, I.A, lds, m, n);
     T lxr[RS::RC], lx0r[RS::RC], lyr[RS::RR], ly0r[RS::RR];
@@ -470,7 +470,7 @@ __device__ __forceinline__ void u_reverse(const UArgs<T, V>& a, const Inst<T, V>
     }
 }
 
-template <typename T, typename V, typename Acc, int BS>
+template <typename T, typename V, typename Acc, int BS, bool LONG>
 __device__ void backward_instance(const UArgs<T, V>& a, Inst<T, V>& I, int i, unsigned char* lds) {
     const int tid = threadIdx.x, B = a.B;
     const int m = I.m, n = I.n, r0 = I.r0, c0 = I.c0;
@@ -516,14 +516,14 @@ __device__ void backward_instance(const UArgs<T, V>& a, Inst<T, V>& I, int i, un
             uint64_t* const masks = a.masks + (int64_t)(t - tb - 1) * a.W + a.word_off[i];
             if (plain > 0) {
                 note(t - tb - 1, plain);
-                u_plain<T, V, Acc, BS>(a, I, lds, plain, k, tau, sig, masks);
+                u_plain<T, V, Acc, BS, LONG>(a, I, lds, plain, k, tau, sig, masks);
                 t += plain;
                 k += plain;
                 continue;
             }
             note(t - tb - 1, 1);
             const bool rs = a.restart[(int64_t)(t - 1) * B + i] != 0;
-            u_iterate<T, V, Acc, BS>(a, I, lds, k, tau, sig, false, rs, false, masks);
+            u_iterate<T, V, Acc, BS, LONG>(a, I, lds, k, tau, sig, false, rs, false, masks);
             ++t;
             ++k;
             if (rs) {
@@ -533,7 +533,7 @@ __device__ void backward_instance(const UArgs<T, V>& a, Inst<T, V>& I, int i, un
             }
         }
         __syncthreads();  // the iterations' numbers and masks are read by all
-        u_reverse<T, V, Acc, BS>(a, I, lds, i, tb, te);
+        u_reverse<T, V, Acc, BS, LONG>(a, I, lds, i, tb, te);
         __syncthreads();
     }
     for (int p = opaque(tid); p < n; p += BS) {
@@ -549,7 +549,7 @@ __device__ void backward_instance(const UArgs<T, V>& a, Inst<T, V>& I, int i, un
 
 enum { kPrepare = 0, kForward = 1, kBackward = 2 };
 
-template <typename T, typename V, typename Acc, int BS, int PHASE>
+template <typename T, typename V, typename Acc, int BS, int PHASE, bool LONG>
 __global__ __launch_bounds__(BS, 4) void k_unrolled(UArgs<T, V> a) {
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ double sh[BS / kWave > 12 ? BS / kWave : 12];
@@ -570,8 +570,8 @@ __global__ __launch_bounds__(BS, 4) void k_unrolled(UArgs<T, V> a) {
         I.yl = (T*)lds;
         I.xl = (T*)(lds + inst_align((I.m + 1) * (int)sizeof(T)));
         if (PHASE == kPrepare) prepare_instance<T, V, BS>(a, I, qi, lds, sh);
-        else if (PHASE == kBackward) backward_instance<T, V, Acc, BS>(a, I, qi, lds);
-        else forward_instance<T, V, Acc, BS>(a, I, qi, lds, sh);
+        else if (PHASE == kBackward) backward_instance<T, V, Acc, BS, LONG>(a, I, qi, lds);
+        else forward_instance<T, V, Acc, BS, LONG>(a, I, qi, lds, sh);
         __syncthreads();  // the next instance takes over the LDS
     }
 }
@@ -692,21 +692,22 @@ static int check_unrolled(const mipdhg_batch* bt, const mipdhg_options* o, int K
 }
 
 template <typename T, typename V, typename Acc, int BS, int PHASE>
-static int launch_phase(const UArgs<T, V>& a, int cus, hipStream_t s) {
+static int launch_phase(const UArgs<T, V>& a, bool rests, int cus, hipStream_t s) {
+    auto* k = rests ? k_unrolled<T, V, Acc, BS, PHASE, LongRows<V>::ok && PHASE != kPrepare>
+                    : k_unrolled<T, V, Acc, BS, PHASE, false>;
     int per_cu = 1;
-    MIP_HIP(hipFuncSetAttribute((const void*)k_unrolled<T, V, Acc, BS, PHASE>,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 162000));
-    MIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_unrolled<T, V, Acc, BS, PHASE>, BS, a.lds));
+    MIP_HIP(hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, 162000));
+    MIP_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, BS, a.lds));
     const int grid = std::max(1, std::min(a.B, cus * std::max(per_cu, 1)));
-    hipLaunchKernelGGL((k_unrolled<T, V, Acc, BS, PHASE>), dim3(grid), dim3(BS), a.lds, s, a);
+    hipLaunchKernelGGL(k, dim3(grid), dim3(BS), a.lds, s, a);
     MIP_LAUNCH_CHECK();
     return 0;
 }
 template <typename T, typename V, typename Acc, int BS>
-static int launch_unrolled(const UArgs<T, V>& a, int cus, bool backward, hipStream_t s) {
-    if (backward) return launch_phase<T, V, Acc, BS, kBackward>(a, cus, s);
-    if (int rc = launch_phase<T, V, Acc, BS, kPrepare>(a, cus, s)) return rc;
-    return launch_phase<T, V, Acc, BS, kForward>(a, cus, s);
+static int launch_unrolled(const UArgs<T, V>& a, bool rests, int cus, bool backward, hipStream_t s) {
+    if (backward) return launch_phase<T, V, Acc, BS, kBackward>(a, rests, cus, s);
+    if (int rc = launch_phase<T, V, Acc, BS, kPrepare>(a, rests, cus, s)) return rc;
+    return launch_phase<T, V, Acc, BS, kForward>(a, rests, cus, s);
 }
 
 template <typename T, typename V, typename Acc>
@@ -836,10 +837,11 @@ static int unrolled_impl(const mipdhg_batch& bt, const mipdhg_options& o, int K,
     a.lds = (int)std::max<int64_t>(inst_vec_bytes(max_m, max_n, sizeof(T)),
                                    std::min(full[c], B <= cus ? share[0] : share[c]));
     hipLaunchKernelGGL(k_zero_bytes, dim3(1), dim3(64), 0, stream, (uint8_t*)t.counter, (int64_t)256);
+    const bool rests = LongRows<V>::pays(lp.m, lp.n, lp.nnz);
     int rc;
-    if (c == 0) rc = launch_unrolled<T, V, Acc, 1024>(a, cus, backward, stream);
-    else if (c == 1) rc = launch_unrolled<T, V, Acc, 256>(a, cus, backward, stream);
-    else rc = launch_unrolled<T, V, Acc, 64>(a, cus, backward, stream);
+    if (c == 0) rc = launch_unrolled<T, V, Acc, 1024>(a, rests, cus, backward, stream);
+    else if (c == 1) rc = launch_unrolled<T, V, Acc, 256>(a, rests, cus, backward, stream);
+    else rc = launch_unrolled<T, V, Acc, 64>(a, rests, cus, backward, stream);
     if (rc) return rc;
     MIP_LAUNCH_CHECK();
     MIP_HIP(hipStreamSynchronize(stream));

@@ -198,3 +198,47 @@ def test_batch_check_finds(what, code, text):
     with pytest.raises(P.MipdhgError) as e:
         P.solve_batched(batch, 1e-4, "fp32", max_iter=3)
     assert e.value.code == code and text in str(e.value), str(e.value)
+
+
+def _rests(name):
+    rng = lpgen.rng_for(82, len(name))
+    if name == "rows_24":  # at the line for four- and two-byte values
+        return _planted(name, 60, [12] * 120)
+    if name == "rests_0_to_9":  # rows of 12 to 34 entries, every remainder past the registers' 16
+        return _planted(name, 23, [1] * 60, extra=lambda j: [i for i in range(23) if j < 12 + i])
+    if name == "columns_14":  # by its columns
+        return _planted(name, 90, [14] * 40)
+    if name == "two_slots":  # rows past the registers' slots, in two passes
+        return _planted(name, 300, rng.integers(20, 40, size=250))
+    raise ValueError(name)
+
+
+@pytest.mark.parametrize("name", ["rows_24", "rests_0_to_9", "columns_14", "two_slots"])
+def test_long_rests_match_the_oracle_and_the_short_forms_bits(name):
+    # alone these take the form for long rests, among many short rows the other: the same sums in the same order.
+    # FP32 against the oracle: 40 iterations from 0, each some four roundings to float32 (6e-8) of matrix and vectors,
+    # not amplified by the iteration in its weighted norm: 1e-5, and ten times that for the weights
+    lp, T = _rests(name), 40
+    ref = oracle.solve(lp.A, lp.AT, lp.b, lp.c, 1e-14, opts=OracleOptions(max_iter=T))
+    fill = [_planted("fill", 60, [2] * 150)] * 40 + [_planted("small", 20, [2] * 50)] * 40
+    batch = P.DeviceBatch.from_lps([lp] + fill)
+    for prec, tol in (("fp64", 1e-10), ("fp32", 1e-4), ("fp32acc32", None), ("bf16", None)):
+        one = P.solve_batched(P.DeviceBatch.from_lps([lp]), 1e-14, prec, max_iter=T)
+        many = P.solve_batched(batch, 1e-14, prec, max_iter=T).split(batch, 0)
+        assert np.array_equal(_np(one.x), _np(many["x"])) and np.array_equal(_np(one.y), _np(many["y"])), prec
+        if tol:
+            assert _rel(_np(one.x), ref.meas.x) <= tol and _rel(_np(one.y), ref.meas.y) <= tol, prec
+
+    def grads(lps, prec):
+        b = P.DeviceBatch.from_lps(lps)
+        umap = P.UnrolledMap(b, K=30, ckpt_every=12, precision=prec)
+        c, r = b.lp.c.clone(), b.lp.b.clone()
+        xK, tape = umap.forward_raw(c, r)
+        g = torch.zeros_like(c)
+        g[:lp.c.size] = 1.0
+        gc, gb = umap.backward_raw(c, r, tape, g)
+        return _np(xK)[:lp.c.size], _np(gc)[:lp.c.size], _np(gb)[:lp.b.size]
+
+    for prec in ("fp32", "fp32acc32", "bf16"):
+        for a, b in zip(grads([lp], prec), grads([lp] + fill, prec)):
+            assert np.array_equal(a, b), prec
