@@ -635,7 +635,7 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
     // its bytes to 256 threads and the others to 1,024
     std::vector<uint8_t> cls(B);
     int cl_count[kClasses] = {0, 0, 0, 0}, cl_lds[kClasses] = {0, 0, 0, 0};
-    int64_t cl_m[kClasses] = {}, cl_n[kClasses] = {}, cl_nnz[kClasses] = {};
+    int64_t cl_m[kClasses] = {}, cl_nnz[kClasses] = {};
     auto rows = [&](int i) { return bt.row_off[i + 1] - bt.row_off[i]; };
     auto columns = [&](int i) { return bt.col_off[i + 1] - bt.col_off[i]; };
     auto full = [&](int i, int k) {  // LDS that holds all of it beside the registers of class k's threads
@@ -663,7 +663,6 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
         const int need = (int)std::max<int64_t>(inst_vec_bytes(rows(i), columns(i), sizeof(T)), std::min(full(i, c), cap));
         ++cl_count[c];
         cl_m[c] += rows(i);
-        cl_n[c] += columns(i);
         cl_nnz[c] += bt.nnz_off[i + 1] - bt.nnz_off[i];
         cl_lds[c] = std::max(cl_lds[c], need);
     }
@@ -777,7 +776,7 @@ static int batched_impl(const mipdhg_batch& bt, const mipdhg_options& o, const d
         ac.counter = w.counter + c;
         ac.lds = cl_lds[c];
         begin += cl_count[c];
-        const bool rests = LongRows<V>::pays(cl_m[c], cl_n[c], cl_nnz[c]);
+        const bool rests = LongRows<V>::pays(cl_m[c], cl_nnz[c]);
         int rc;
         if (c == 0) rc = launch_class<T, V, Acc, kClassBs[0]>(ac, rests, cus, cs);
         else if (c == 1) rc = launch_class<T, V, Acc, kClassBs[1]>(ac, rests, cus, cs);

@@ -477,19 +477,18 @@ inline bool one_wave(int64_t count, int cus, int m, int n) {
 }
 
 // Whether a launch's instances take the LONG form of side_rest: where their rows
-// or columns go on past the registers for 8 entries on average.  FP32, 200 LPs
+// go on past the registers for 8 entries on average.  FP32, 200 LPs
 // of 200 rows and 400 columns, 256 iterations, without and with it: 8 entries a
 // row 1.11 and 1.17 ms, 16 1.63 and 1.59, 24 2.05 and 1.91, 32 2.59 and 2.29; 64
 // maps of the same, K = 150: 1.75 and 1.84, 2.43 and 2.42, 3.01 and 2.88, 3.69 and
 // 3.40 (21 of 95 x 380, 64 entries a row: 5.01 and 4.19, from L2 4.62).  Not for
 // values of eight bytes, whose registers it takes (64 maps in FP64, 16 entries a
-// row 2.14 and 2.35, 24 2.70 and 2.74, 32 3.25 and 3.21).
+// row 2.14 and 2.35, 24 2.70 and 2.74, 32 3.25 and 3.21), and not for long columns
+// alone (31 LPs of 212 x 212, 16 entries a column and a row, 1.92 and 2.03).
 template <typename V>
 struct LongRows {
     static constexpr bool ok = sizeof(V) < 8;
-    static bool pays(int64_t m, int64_t n, int64_t nnz) {
-        return ok && (nnz >= m * (RegShape<V>::KR + 8) || nnz >= n * (RegShape<V>::KC + 8));
-    }
+    static bool pays(int64_t m, int64_t nnz) { return ok && nnz >= m * (RegShape<V>::KR + 8); }
 };
 
 // perm <- the positions' rows: rows by decreasing length, equal lengths in

@@ -837,7 +837,7 @@ static int unrolled_impl(const mipdhg_batch& bt, const mipdhg_options& o, int K,
     a.lds = (int)std::max<int64_t>(inst_vec_bytes(max_m, max_n, sizeof(T)),
                                    std::min(full[c], B <= cus ? share[0] : share[c]));
     hipLaunchKernelGGL(k_zero_bytes, dim3(1), dim3(64), 0, stream, (uint8_t*)t.counter, (int64_t)256);
-    const bool rests = LongRows<V>::pays(lp.m, lp.n, lp.nnz);
+    const bool rests = LongRows<V>::pays(lp.m, lp.nnz);
     int rc;
     if (c == 0) rc = launch_unrolled<T, V, Acc, 1024>(a, rests, cus, backward, stream);
     else if (c == 1) rc = launch_unrolled<T, V, Acc, 256>(a, rests, cus, backward, stream);
