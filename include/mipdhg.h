@@ -276,9 +276,10 @@ typedef struct mipdhg_options {
      * x_bar (the vectors kept in LDS) fit in batch_split bytes run in
      * 256-thread workgroups; the others run in 1024-thread workgroups (four
      * times the threads on each row and column).  0 = concurrent launches of
-     * workgroups of 64 to 1,024 threads, each instance by the LDS it needs
-     * with its matrices.  An instance's results do not depend on the
-     * workgroup that ran it.  mipdhg_autotune_batched picks the fastest.    [0] */
+     * workgroups of 64 to 1,024 threads, each instance by its size, the LDS it
+     * needs with its matrices and the number of instances.  An instance's
+     * results do not depend on the workgroup that ran it.
+     * mipdhg_autotune_batched picks the fastest.                            [0] */
     int32_t batch_split;
     /* Batched solve, > 0: iterations per call.  Each unfinished instance
      * stops at its first evaluation at least batch_block_iters iterations

@@ -82,12 +82,13 @@ constexpr double kInfPivot = 1.79769313486231570e308;
 // Lower triangle of M = A~ diag(w) A~^T (w NULL: ones), a workgroup of one
 // wave per row i: the row is accumulated in LDS, column after column of A's
 // row i in its order, the lanes over the entries of that column (a row of
-// A~^T, whose rows k are distinct: the set-up has checked it).  Every entry (i, k) is the sum over the
-// common columns of i and k in increasing order, whatever the launch.  Rows
-// from m on (the padding up to ld) are those of the identity.
+// A~^T, whose rows k are distinct: the set-up has checked it).  Every entry
+// (i, k) is the sum over the common columns of i and k in increasing order,
+// whatever the launch.  Rows from m on (the padding up to ld) are those of the
+// identity.
 // What bounds it: the loads of a column's entries, a chain of two; four
-// columns' loads are in flight together.  26 us at 1,000 x 4,000 (32,000
-// nonzeros) and 146 us at 4,000 x 16,000 (128,000); one thread per entry
+// columns' loads are in flight together.  27 us at 1,000 x 4,000 (32,000
+// nonzeros) and 150 us at 4,000 x 16,000 (128,000); one thread per entry
 // merging the two sorted rows, the form before, walked both rows for every
 // pair, mostly without a common column: 131 us and 2.0 ms.
 __global__ __launch_bounds__(kWave) void k_ipm_normal(const int32_t* rp, const int32_t* col, const double* val,
@@ -157,11 +158,11 @@ __global__ __launch_bounds__(kWave) void k_ipm_normal(const int32_t* rp, const i
 // B[l / 16][l % 16] and, in register r, C[l / 16 + 4 r][l % 16], so a C block
 // is its own B operand of the next product, and the row solves
 // X^T <- L^-1 X^T keep X^T in registers throughout.
-// What bounds it: the diagonal factors, about 6,000 clocks for 16 pivots and
-// 28,000 of a launch's 45,000, the rest the panel's loads and products before
-// them and the row solve after; at m = 4,000 also the trailing update, which
-// reads and writes 128 MB in the first launches.  A launch takes 21.7 us at
-// m = 1,000 (27.8 us mean at 4,000), a factorization 0.35 and 1.75 ms.  The
+// What bounds it: the diagonal factors, a chain of 64 pivots and more than half
+// of a launch, the rest the panel's loads and products before them and the row
+// solve after; at m = 4,000 also the trailing update, which reads and writes
+// 128 MB in the first launches.  A launch takes 21.5 us at m = 1,000 (27.8 us
+// mean at 4,000), a factorization 0.34 and 1.75 ms.  The
 // form before (a diagonal, a panel and an update launch per block, on vector
 // FMAs, the diagonal one column at a time through LDS) took 2.2 and 10.2 ms.
 // Measured beside it: the pivots of a block eliminated by lane reads in a row
@@ -487,7 +488,7 @@ __global__ __launch_bounds__(kCholBlock, 3) void k_chol_step(double* M, int32_t 
 // the wait itself it was 0.5 to 0.9 us of a solve's chain); the call that
 // launched this reports it as an error.
 // What bounds it: the chain over the 64-row blocks, 1.2 to 1.4 us each: 22 us
-// (lower) and 19 us (upper) at m = 1,000, 90 and 73 us at m = 4,000.  Before,
+// (lower) and 19 us (upper) at m = 1,000, 90 and 74 us at m = 4,000.  Before,
 // one workgroup swept the whole factor, a compute unit's read rate: 0.52 and
 // 0.62 ms, 5.8 and 10.0 ms.
 constexpr unsigned long long kUnset = 0x7ff4a55a5aa5a55aull;

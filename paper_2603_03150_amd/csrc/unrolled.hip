@@ -30,7 +30,7 @@
 // latency of its gathers and two barriers (the reverse sweep: three).
 // Measured at 256 instances of 500 x 1,500, 5 entries a column, FP32, K = 400:
 // with 256 threads reading the matrices and the state from L2, 4.9 ms forward
-// and 9.3 ms backward; so, 0.86 (set-up) + 1.75 and 3.55 ms.
+// and 9.3 ms backward; so, 0.80 (set-up) + 1.72 and 3.50 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
