@@ -707,9 +707,9 @@ struct SmallSide {
 
 // `count` iterations from a.it on, none of them a block's first or last: the
 // arithmetic of IterEpi, the state in registers and LDS.  (A traced solve runs
-// them one to a launch, with the flag F_HAT: the same code and so the same
-// iterates.)
-template <typename T, typename V, typename Acc, bool GENP, bool GEND>
+// them one to a launch, HAT: the same source, with the projected points stored
+// as well; asked for in the loop, that was 80.5 us for 62 iterations, so 73.8.)
+template <typename T, typename V, typename Acc, bool GENP, bool GEND, bool HAT>
 __global__ __launch_bounds__(kSmallBlock) void k_small_iters(IterArgs<T, V> p, IterArgs<T, V> d, SmallMat ma,
                                                              SmallMat mat, int count) {
     const Ctrl* ctrl = p.ctrl;
@@ -747,7 +747,6 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_iters(IterArgs<T, V> p, I
     for (int i = tid; i < m; i += kSmallBlock) vy[i] = d.state[i];
     const double tau = ctrl->tau, sig = ctrl->sigma, rho = p.rho, opr = 1.0 + p.rho;
     const int64_t k0 = ctrl->k_base + p.it;
-    const bool hat = (p.flags & F_HAT) != 0;
     if (tid == 0) {
         vy[m] = (T)0;
         vx[n] = (T)0;
@@ -776,7 +775,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_iters(IterArgs<T, V> p, I
                 dh = dh < -a0 ? -a0 : dh;
             }
             if (first_c) vx[j] = (T)(2.0 * dh - o);
-            if (hat && first_c) p.hat[j] = (T)(a0 + dh);
+            if (HAT && first_c) p.hat[j] = (T)(a0 + dh);
             u[r] = (T)(w * (opr * dh - rho * o));
         }
         __syncthreads();
@@ -792,7 +791,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small_iters(IterArgs<T, V> p, I
                 else if (sense[r] == MIPDHG_SENSE_LE) dh = dh > -a0 ? -a0 : dh;
             }
             if (first_r) vy[i] = (T)(w * (opr * dh - rho * o));
-            if (hat && first_r) d.hat[i] = (T)((double)d.anchor[i] + dh);
+            if (HAT && first_r) d.hat[i] = (T)((double)d.anchor[i] + dh);
         }
         __syncthreads();
     }
@@ -2342,11 +2341,11 @@ struct Solver {
         return a ? SmallMat{lp.a_rowptr, lp.a_col, lp.m} : SmallMat{lp.at_rowptr, lp.at_col, lp.n};
     }
     int allow_small_lds() {
-        const void* ks[] = {(const void*)k_small_iters<T, V, Acc, false, false>,
-                            (const void*)k_small_iters<T, V, Acc, true, false>,
-                            (const void*)k_small_iters<T, V, Acc, false, true>,
-                            (const void*)k_small_iters<T, V, Acc, true, true>, (const void*)k_small_power<T, V>,
-                            (const void*)k_small_scale};
+#define MIP_SMALL(GP, GD) \
+    (const void*)k_small_iters<T, V, Acc, GP, GD, false>, (const void*)k_small_iters<T, V, Acc, GP, GD, true>
+        const void* ks[] = {MIP_SMALL(false, false), MIP_SMALL(true, false), MIP_SMALL(false, true),
+                            MIP_SMALL(true, true),   (const void*)k_small_power<T, V>, (const void*)k_small_scale};
+#undef MIP_SMALL
         for (const void* k : ks)
             MIP_HIP(hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLdsMax));
         return 0;
@@ -2358,10 +2357,10 @@ struct Solver {
         fill_iter(d, false, it, flags);
         const SmallMat ma = small_side(true), mat = small_side(false);
         const int lds = small_layout().bytes;
-        const bool gp = gen_primal(), gd = gen_dual();
-#define MIP_SMALL(GP, GD)                                                                                         \
-    hipLaunchKernelGGL((k_small_iters<T, V, Acc, GP, GD>), dim3(1), dim3(kSmallBlock), lds, stream, p, d, ma, mat, \
-                       count)
+        const bool gp = gen_primal(), gd = gen_dual(), hat = (flags & F_HAT) != 0;
+#define MIP_SMALL(GP, GD)                                                                                    \
+    hipLaunchKernelGGL((hat ? k_small_iters<T, V, Acc, GP, GD, true> : k_small_iters<T, V, Acc, GP, GD, false>), \
+                       dim3(1), dim3(kSmallBlock), lds, stream, p, d, ma, mat, count)
         if (gp && gd) MIP_SMALL(true, true);
         else if (gp) MIP_SMALL(true, false);
         else if (gd) MIP_SMALL(false, true);
